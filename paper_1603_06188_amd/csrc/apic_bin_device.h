@@ -221,7 +221,7 @@ __device__ __forceinline__ void batch_items(const BatchQueue &q, Fn &&fn) {
             __syncthreads();
             if (threadIdx.x == 0) item = atomicAdd(q.ctr, 1u) - q.base;
             __syncthreads();
-            const uint32_t it = item;
+            const uint32_t it = (uint32_t)__builtin_amdgcn_readfirstlane((int)item);
             if (it >= q.items) break;
             fn(it);
         }
@@ -232,7 +232,9 @@ template <typename T>
 __device__ __forceinline__ BatchStep<T> batch_step(const SceneDesc<T> *descs, const int32_t *start, int n, int k,
                                                    uint32_t item) {
     BatchStep<T> b;
-    const int s = scene_of_block(start, n, item);
+    // the scene is the same for the whole block: held in scalar registers, and
+    // with it every pointer of its table entry
+    const int s = __builtin_amdgcn_readfirstlane(scene_of_block(start, n, item));
     b.d = descs + s;
     const uint32_t gen0[2] = {b.d->lists[0].gen, b.d->lists[1].gen};
     b.sp = step_parity(b.d->cur0, b.d->where0, gen0, k);

@@ -327,20 +327,6 @@ struct SlabMap {
             if (b == e) pos = in_block(b, l);
         return pos;
     }
-    // region coordinates of position j (0 <= j < RN); c is left as is for j >= RN
-    __host__ __device__ static void coords(int j, int *c) {
-#pragma unroll
-        for (int e = 0; e < (1 << DIM); ++e) {
-            if (j >= start(e) && j < start(e) + size(e)) {
-                int l = j - start(e);
-#pragma unroll
-                for (int a = 0; a < DIM; ++a) {
-                    c[a] = l % edge(e, a) + (((e >> a) & 1) ? TE : 0);
-                    l /= edge(e, a);
-                }
-            }
-        }
-    }
 };
 
 // ---------------------------------------------------------------------------
@@ -624,6 +610,45 @@ __device__ __forceinline__ WaveWalk wave_walk(uint32_t blk, uint32_t nblk, uint3
 template <typename T>
 __device__ __forceinline__ T &plane_at(T *plane, uint32_t boff) {
     return *(T *)((char *)plane + boff);
+}
+
+// The planes of particles read from a scene table, held in scalar registers
+// (the same for the whole block).
+template <typename P>
+__device__ __forceinline__ P *scalar_pointer(P *p) {
+    const uint64_t a = (uint64_t)p;
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
+    return (P *)(((uint64_t)hi << 32) | lo);
+}
+template <typename T>
+__device__ __forceinline__ Parts<T> scalar_parts(const Parts<T> &p) {
+    Parts<T> q;
+    q.cell = scalar_pointer(p.cell);
+    q.off = scalar_pointer(p.off);
+    q.v = scalar_pointer(p.v);
+    q.B = scalar_pointer(p.B);
+    q.F = scalar_pointer(p.F);
+    q.m = scalar_pointer(p.m);
+    q.id = scalar_pointer(p.id);
+    q.n = (int64_t)scalar_pointer((char *)p.n);
+    q.s = (int64_t)scalar_pointer((char *)p.s);
+    return q;
+}
+
+// Element at byte offset `boff` of a plane whose base is held in scalar
+// registers: the planes of a particle are then addressed by one 32-bit lane
+// offset beside scalar bases.  (Left alone, the compiler adds the plane stride
+// to a 64-bit lane address, a vector add per plane.)
+template <typename T>
+using GlobalPtr = T __attribute__((address_space(1))) *;
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> scalar_plane(T *plane, uint32_t boff) {
+    GlobalPtr<char> p = (GlobalPtr<char>)plane;
+#ifdef __HIP_DEVICE_COMPILE__
+    asm("" : "+s"(p));  // (the host compiler knows no scalar register)
+#endif
+    return (GlobalPtr<T>)(p + boff);
 }
 
 // Exact error of a + b (Knuth two-sum).

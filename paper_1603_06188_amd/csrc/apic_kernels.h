@@ -7,6 +7,9 @@ namespace apic {
 
 constexpr int kDiagBlocks = 1024;
 
+// The transfer to grid takes a block per tile (else a wavefront).
+constexpr bool p2g_block_per_tile(int dim, int deg) { return dim == 3 && deg >= 2; }
+
 // --- generic ---------------------------------------------------------------
 template <typename T>
 void launch_fill(T *p, int64_t count, T val, hipStream_t st);

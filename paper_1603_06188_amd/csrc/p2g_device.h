@@ -3,6 +3,8 @@
 // terms, the factored tensor-product accumulation of its node contributions
 // into a key's register sums, and the padded LDS slab.
 #pragma once
+#include <type_traits>
+
 #include "apic_bin_device.h"
 
 namespace apic {
@@ -28,17 +30,69 @@ template <typename T, int DIM, bool ABS = false>
 __device__ __forceinline__ void p2g_load(const Parts<T> &P, uint32_t q, P2GRaw<T, DIM> &r) {
     const int64_t s = P.s;
     const uint32_t qb = q * (uint32_t)sizeof(T);
-    r.cell = ABS ? 0u : P.cell[q];
-    r.m = plane_at(P.m, qb);
+    r.cell = ABS ? 0u : *scalar_plane(P.cell, q * 4u);
+    r.m = *scalar_plane(P.m, qb);
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        r.off[a] = plane_at(P.off + a * s, qb);
-        r.v[a] = plane_at(P.v + a * s, qb);
+        r.off[a] = *scalar_plane(P.off + a * s, qb);
+        r.v[a] = *scalar_plane(P.v + a * s, qb);
     }
 #pragma unroll
     for (int k = 0; k < DIM * DIM; ++k) {
-        r.B[k] = plane_at(P.B + k * s, qb);
-        r.F[k] = plane_at(P.F + k * s, qb);
+        r.B[k] = *scalar_plane(P.B + k * s, qb);
+        r.F[k] = *scalar_plane(P.F + k * s, qb);
+    }
+}
+
+// Whether every value of a loaded particle is finite.  x * 0 is NaN exactly
+// when x is infinite or NaN, and +-0 otherwise, so the sum of all of them is
+// zero exactly when every value is finite (one multiply-add per value instead
+// of a class test and a mask merge).
+template <typename T, int DIM>
+__device__ __forceinline__ bool p2g_finite(const P2GRaw<T, DIM> &r) {
+    T z = r.m * T(0);
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        z = fma_t(r.off[a], T(0), z);
+        z = fma_t(r.v[a], T(0), z);
+    }
+#pragma unroll
+    for (int k = 0; k < DIM * DIM; ++k) {
+        z = fma_t(r.B[k], T(0), z);
+        z = fma_t(r.F[k], T(0), z);
+    }
+    return z == T(0);
+}
+
+// Ac = -dt V_p tau_p / dx of a particle (symmetric: the upper triangle row by
+// row), 0 without a force model or for an inverted particle (flagged).
+template <typename T, int DIM>
+__device__ __forceinline__ void p2g_force(const T *F, T m, const StepParams<T> &prm, T inv_dx, uint32_t *flags, T *A) {
+    constexpr int NA = DIM * (DIM + 1) / 2;
+#pragma unroll
+    for (int k = 0; k < NA; ++k) A[k] = T(0);
+    if (prm.model != 1) return;
+    T J;
+    if constexpr (DIM == 3)
+        J = F[0] * (F[4] * F[8] - F[5] * F[7]) - F[1] * (F[3] * F[8] - F[5] * F[6]) + F[2] * (F[3] * F[7] - F[4] * F[6]);
+    else
+        J = F[0] * F[3] - F[1] * F[2];
+    if (J > T(0)) {
+        const T lnJ = log_t(J);
+        const T sc = -prm.dt * m * prm.inv_rho0 * inv_dx;
+        int at = 0;
+#pragma unroll
+        for (int r = 0; r < DIM; ++r)
+#pragma unroll
+            for (int c = r; c < DIM; ++c) {
+                T ff = T(0);
+#pragma unroll
+                for (int k = 0; k < DIM; ++k) ff += F[r * DIM + k] * F[c * DIM + k];
+                const T tau = r == c ? prm.mu * (ff - T(1)) + prm.lam * lnJ : prm.mu * ff;
+                A[at++] = sc * tau;
+            }
+    } else {
+        atomicOr(flags, FLAG_INVERTED);
     }
 }
 
@@ -52,29 +106,18 @@ __device__ __forceinline__ bool p2g_prepare(const P2GRaw<T, DIM> &r, const int *
     int ci[3] = {0, 0, 0};
     T off[DIM], v[DIM], B[DIM * DIM], F[DIM * DIM];
     const T m = r.m;
-    // x * 0 is NaN exactly when x is infinite or NaN, and +-0 otherwise, so
-    // the sum of all of them is zero exactly when every value is finite (one
-    // multiply-add per value instead of a class test and a mask merge)
-    T z = m * T(0);
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        v[a] = r.v[a];
-        z = fma_t(r.off[a], T(0), z);
-        z = fma_t(v[a], T(0), z);
+    if (!p2g_finite<T, DIM>(r)) {
+        atomicOr(flags, FLAG_NONFINITE);
+        return false;
     }
-    particle_cells<T, DIM, ABS>(r.cell, r.off, inv_dx, ci, off);
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) v[a] = r.v[a];
 #pragma unroll
     for (int k = 0; k < DIM * DIM; ++k) {
         B[k] = r.B[k];
         F[k] = r.F[k];
-        z = fma_t(B[k], T(0), z);
-        z = fma_t(F[k], T(0), z);
     }
-    const bool finite = z == T(0);
-    if (!finite) {
-        atomicOr(flags, FLAG_NONFINITE);
-        return false;
-    }
+    particle_cells<T, DIM, ABS>(r.cell, r.off, inv_dx, ci, off);
     bool same = true;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
@@ -96,35 +139,14 @@ __device__ __forceinline__ bool p2g_prepare(const P2GRaw<T, DIM> &r, const int *
 #pragma unroll
     for (int a = 0; a < DIM; ++a) pp.p[a] = m * (v[a] - uref[a]);
 #pragma unroll
-    for (int k = 0; k < DIM * DIM; ++k) {
-        pp.Qc[k] = qs * B[k];
-        pp.Ac[k] = T(0);
-    }
-    if (prm.model == 1) {
-        T J;
-        if constexpr (DIM == 3)
-            J = F[0] * (F[4] * F[8] - F[5] * F[7]) - F[1] * (F[3] * F[8] - F[5] * F[6]) +
-                F[2] * (F[3] * F[7] - F[4] * F[6]);
-        else
-            J = F[0] * F[3] - F[1] * F[2];
-        if (J > T(0)) {
-            const T lnJ = log_t(J);
-            const T sc = -prm.dt * m * prm.inv_rho0 * inv_dx;
+    for (int k = 0; k < DIM * DIM; ++k) pp.Qc[k] = qs * B[k];
+    T A[DIM * (DIM + 1) / 2];
+    p2g_force<T, DIM>(F, m, prm, inv_dx, flags, A);
+    int at = 0;
 #pragma unroll
-            for (int r = 0; r < DIM; ++r)
+    for (int i = 0; i < DIM; ++i)
 #pragma unroll
-                for (int c = r; c < DIM; ++c) {
-                    T ff = T(0);
-#pragma unroll
-                    for (int k = 0; k < DIM; ++k) ff += F[r * DIM + k] * F[c * DIM + k];
-                    const T tau = r == c ? prm.mu * (ff - T(1)) + prm.lam * lnJ : prm.mu * ff;
-                    pp.Ac[r * DIM + c] = sc * tau;
-                    pp.Ac[c * DIM + r] = sc * tau;
-                }
-        } else {
-            atomicOr(flags, FLAG_INVERTED);
-        }
-    }
+        for (int c = i; c < DIM; ++c) pp.Ac[i * DIM + c] = pp.Ac[c * DIM + i] = A[at++];
     return true;
 }
 
@@ -225,14 +247,29 @@ struct SlabLds {
     static constexpr int SY = DIM == 3 ? 8 : 40;
     static constexpr int SZ = DIM == 3 ? 68 : 0;
     static constexpr int PLANE = DIM == 3 ? SZ * RE : SY * RE;
-    __device__ static constexpr int at(int x, int y, int z) { return x + SY * y + SZ * z; }
-    // global position j -> padded index
-    __device__ static int from_global(int j) {
-        int c[3] = {0, 0, 0};
-        SlabMap<DIM, DEG>::coords(j, c);
-        return at(c[0], c[1], c[2]);
+    __host__ __device__ static constexpr int at(int x, int y, int z) { return x + SY * y + SZ * z; }
+};
+
+// Padded index in LDS of every slab position of global memory, formed at
+// compile time (dozens of instructions per position otherwise).
+template <int DIM, int DEG>
+struct SlabPadTable {
+    uint16_t at[Geo<DIM, DEG>::RN];
+    __host__ __device__ constexpr SlabPadTable() : at() {
+        using M = SlabMap<DIM, DEG>;
+        for (int e = 0; e < (1 << DIM); ++e)
+            for (int i = 0; i < M::size(e); ++i) {
+                int c[3] = {0, 0, 0}, l = i;
+                for (int a = 0; a < DIM; ++a) {
+                    c[a] = l % M::edge(e, a) + (((e >> a) & 1) ? Geo<DIM, DEG>::TE : 0);
+                    l /= M::edge(e, a);
+                }
+                at[M::start(e) + i] = (uint16_t)SlabLds<DIM, DEG>::at(c[0], c[1], c[2]);
+            }
     }
 };
+template <int DIM, int DEG>
+__device__ constexpr SlabPadTable<DIM, DEG> kSlabPad{};
 
 // All NC planes of one node: every read first, then the sums and writes
 // (one wait for the LDS per node instead of one per plane).
@@ -260,12 +297,20 @@ constexpr int p2g_slices() {
     return DIM == 2 ? K : (per_slice * K <= 128 ? K : (per_slice * 2 <= 128 ? 2 : 1));
 }
 
+// Type of a node's sum over the keys in LDS: compensated binary32 sums are one
+// binary64 number, stored as a value and its error term (two instructions per
+// add instead of a two-sum's eight; multilinear cube of 1M particles: 28 -> 27
+// us); the others are kept in T, compensated binary64 with an error term beside.
+template <typename T, bool COMP>
+using SlabSum = typename std::conditional<COMP && sizeof(T) == 4, double, T>::type;
+
 // Adds a lane's register sums for z-slices [C0, C0+CZ) of its key's support
 // into the slab in K*K*CZ rounds; the lanes of one round touch distinct
-// nodes (distinct keys), so a plain read-modify-write is safe.
-template <typename T, int DEG, bool COMP, int C0, int CZ>
+// nodes (distinct keys), so a plain read-modify-write is safe.  PAIR: the sums
+// have an error term beside them.
+template <typename T, int DEG, bool PAIR, int C0, int CZ, typename U>
 __device__ __forceinline__ void slab_flush3(const int *lcoord, const T (&acc_m)[CZ][DEG + 1][DEG + 1],
-                                            const T (&acc_v)[3][CZ][DEG + 1][DEG + 1], T *lds) {
+                                            const T (&acc_v)[3][CZ][DEG + 1][DEG + 1], U *lds) {
     using Gm = Geo<3, DEG>;
     using SL = SlabLds<3, DEG>;
     constexpr int K = DEG + 1, NC = Gm::NC, LP = SL::PLANE;
@@ -276,8 +321,8 @@ __device__ __forceinline__ void slab_flush3(const int *lcoord, const T (&acc_m)[
 #pragma unroll
             for (int a = 0; a < K; ++a) {
                 const int idx = SL::at(lcoord[0] + a, lcoord[1] + b, lcoord[2] + C0 + c);
-                const T x[NC] = {acc_m[c][b][a], acc_v[0][c][b][a], acc_v[1][c][b][a], acc_v[2][c][b][a]};
-                slab_add_node<T, COMP, LP, NC>(lds, idx, x);
+                const U x[NC] = {(U)acc_m[c][b][a], (U)acc_v[0][c][b][a], (U)acc_v[1][c][b][a], (U)acc_v[2][c][b][a]};
+                slab_add_node<U, PAIR, LP, NC>(lds, idx, x);
                 wave_lds_sync();
             }
 }
@@ -293,12 +338,37 @@ __device__ __forceinline__ void slab_store(const T *lds, T *out) {
     const int lane = lane_id();
     int pad[R];
 #pragma unroll
-    for (int k = 0; k < R; ++k) pad[k] = SL::from_global(lane + 64 * k);
+    for (int k = 0; k < R; ++k) pad[k] = lane + 64 * k < RN ? kSlabPad<DIM, DEG>.at[lane + 64 * k] : 0;
 #pragma unroll
     for (int q = 0; q < NP; ++q)
 #pragma unroll
         for (int k = 0; k < R; ++k)
             if (lane + 64 * k < RN) out[q * RN + lane + 64 * k] = lds[q * LP + pad[k]];
+}
+
+// The same from sums that are one number each.
+template <typename T, int DIM, int DEG, bool COMP>
+__device__ __forceinline__ void slab_store_sums(const SlabSum<T, COMP> *lds, T *out) {
+    if constexpr (COMP && sizeof(T) == 8) {
+        slab_store<T, DIM, DEG, COMP>(lds, out);
+    } else {
+        using Gm = Geo<DIM, DEG>;
+        constexpr int RN = Gm::RN, LP = SlabLds<DIM, DEG>::PLANE, NC = Gm::NC, R = (RN + 63) / 64;
+        const int lane = lane_id();
+#pragma unroll
+        for (int k = 0; k < R; ++k) {
+            const int at = lane + 64 * k;
+            if (at >= RN) continue;
+            const int pad = kSlabPad<DIM, DEG>.at[at];
+#pragma unroll
+            for (int q = 0; q < NC; ++q) {
+                const SlabSum<T, COMP> sum = lds[q * LP + pad];
+                const T v = (T)sum;
+                out[q * RN + at] = v;
+                if constexpr (COMP) out[(NC + q) * RN + at] = (T)(sum - (SlabSum<T, COMP>)v);
+            }
+        }
+    }
 }
 
 template <typename T, int DIM, int DEG, bool COMP>
@@ -309,7 +379,7 @@ __device__ __forceinline__ void slab_load(const T *in, T *lds) {
     const int lane = lane_id();
     int pad[R];
 #pragma unroll
-    for (int k = 0; k < R; ++k) pad[k] = SL::from_global(lane + 64 * k);
+    for (int k = 0; k < R; ++k) pad[k] = lane + 64 * k < RN ? kSlabPad<DIM, DEG>.at[lane + 64 * k] : 0;
 #pragma unroll
     for (int q = 0; q < NP; ++q)
 #pragma unroll
@@ -363,11 +433,12 @@ __device__ __forceinline__ void tile_uref(uint32_t t, const GridState<T> &g, T *
 // particles of each key (its movers), levels [0, jend).  Momenta are taken
 // relative to the tile's reference velocity uref; DERIVE: uref is first set
 // from the level-0 particles this pass loads (reference_of_level0).
-template <typename T, int DEG, bool COMP, int C0, int CZ, bool MOV = false, bool DERIVE = false, bool ABS = false>
+template <typename T, int DEG, bool PAIR, int C0, int CZ, bool MOV = false, bool DERIVE = false, bool ABS = false,
+          typename U = T>
 __device__ __forceinline__ void p2g_pass3(const Parts<T> &P, const int *key, int lcoord[3], uint32_t start,
                                           uint32_t kstart, uint32_t cnt, uint32_t maxc, uint32_t act, uint32_t jend,
                                           const StepParams<T> &prm, T inv_dx, uint32_t *flags, T *uref,
-                                          T *lds) {
+                                          U *lds) {
     constexpr int K = DEG + 1;
     const int lane = lane_id();
     const uint32_t n_act = MOV ? act : cnt, j_end = MOV ? jend : maxc;
@@ -407,7 +478,7 @@ __device__ __forceinline__ void p2g_pass3(const Parts<T> &P, const int *key, int
         level_step(raw, raw_b, j);
         if (j + 1 < j_end) level_step(raw_b, raw, j + 1);
     }
-    slab_flush3<T, DEG, COMP, C0, CZ>(lcoord, acc_m, acc_v, lds);
+    slab_flush3<T, DEG, PAIR, C0, CZ>(lcoord, acc_m, acc_v, lds);
 }
 
 }  // namespace apic
