@@ -114,8 +114,8 @@ Layout make_layout(const apic_grid_desc *g, int64_t cap) {
     L.o_vt = take(dim * G * e);
     L.o_uref = take(dim * TT * e);
     L.o_flags = take(64);
-    L.o_vmax = take((size_t)kVmaxSlots * 4);
-    L.o_cfl = take((size_t)kVmaxSlots * 8);
+    L.o_vmax = take(TT * 16);
+    L.o_cfl = take((size_t)kCflSlots * 8);
     L.o_dt = take(2 * sizeof(double));
     L.o_diag_out = take(8 * sizeof(double));
     L.o_diag_part = take((size_t)kDiagBlocks * 8 * sizeof(double));
@@ -464,7 +464,7 @@ View<T> make_view(const apic_scene *s, int64_t cap, const SceneState &ss) {
     v.g.vt = (T *)(w + L.o_vt);
     v.g.uref = (T *)(w + L.o_uref);
     v.g.flags = (uint32_t *)(w + L.o_flags);
-    v.g.vmax = (uint32_t *)(w + L.o_vmax);
+    v.g.vmax = (float *)(w + L.o_vmax);
     v.g.cfl = nullptr;
     v.g.cfl_c = cfl_factor(s->grid);
     v.g.d = L.d;
@@ -716,7 +716,7 @@ apic_status run_steps(apic_scene *s, int64_t cap, int32_t n_steps, int32_t sort_
                 const int nb = launch_cfl_partials<T, DIM>(bufs[where], cfl_factor(s->grid), v.diag_part, st);
                 launch_adapt_dt(v.diag_part, nb, cfl_slots, s->prm.dt, nu_dx, dt_state, st);
             } else {
-                launch_adapt_dt((const double *)cfl_slots, kVmaxSlots, cfl_slots, s->prm.dt, nu_dx, dt_state, st);
+                launch_adapt_dt((const double *)cfl_slots, kCflSlots, cfl_slots, s->prm.dt, nu_dx, dt_state, st);
             }
         }
         if (!slabs_ready) {
@@ -989,6 +989,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
     double updates = 0.0;
     int64_t all = 0;
     for (int32_t i = 0; i < n; ++i) all += scenes[i].p.n;
+    const int kwaves = key_waves(all), gwaves = g2p_waves<T, DIM, DEG>(all);
     for (int32_t i = 0; i < n; ++i) {
         int64_t cap = 0;
         (void)check_scene(&scenes[i], &cap);
@@ -1038,13 +1039,17 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         const int64_t np = scenes[i].p.n;
         updates += (double)np * (double)n_steps;
         const int pb = plan.per_block;
-        // A block of the transfer to grid takes one tile at a time, not four:
-        // half the particles per block for a batch that fills the chip several
-        // times over (512 bodies of 19M particles: 1154 us against 1193 with a
-        // quarter), a quarter for a small one (24 bodies of 0.2M: 37 us against 48)
-        const int pb_grid = p2g_block_per_tile(DIM, DEG) ? (all >= ((int64_t)1 << 21) ? pb / 2 : pb / 4) : pb;
-        const int share[BK_COUNT] = {share_blocks(np, pb_grid, 4096), share_blocks(np, pb, 8192), share_blocks(np, pb, 2048),
-                                     share_blocks(np, pb, 1024), share_blocks(np, pb, 4096), share_blocks(np, 1024, 4096),
+        // Blocks that take one tile at a time, not four: half the particles
+        // per block for a batch that fills the chip several times over
+        // (transfer to grid of 512 bodies, 19M particles: 1154 us against 1193
+        // with a quarter), a quarter for a small one (24 bodies, 0.2M: 37 us
+        // against 48)
+        const int pb_tile = all >= ((int64_t)1 << 21) ? pb / 2 : pb / 4;
+        const int pb_grid = p2g_block_per_tile(DIM, DEG) ? pb_tile : pb;
+        const int pb_keys = kwaves == 4 ? pb_tile : pb, pb_part = gwaves == 4 ? pb_tile : pb;
+        const int share[BK_COUNT] = {share_blocks(np, pb_grid, 4096), share_blocks(np, pb, 8192),
+                                     share_blocks(np, pb_keys, 4096), share_blocks(np, pb, 1024),
+                                     share_blocks(np, pb_part, 4096), share_blocks(np, 1024, 4096),
                                      // finalize: one block per ~65k particles (a few hundred records)
                                      share_blocks(np, 65536, 128)};
         for (int k = 0; k < BK_COUNT; ++k) {
@@ -1118,14 +1123,14 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
             timed(APIC_PHASE_BIN, s, [&] {
                 int nk = 0, nr = 0;
                 const BatchQueue qk = queue_of(BK_KEYS, nk);
-                launch_bin_keys_moved_batch<T, DIM, DEG>(dd, start_of(BK_KEYS), n, k, qk, nk, s);
+                launch_bin_keys_moved_batch<T, DIM, DEG>(dd, start_of(BK_KEYS), n, k, qk, nk, kwaves, s);
                 const BatchQueue qr = queue_of(BK_RECORDS, nr);
                 launch_bin_records_batch<T, DIM>(dd, start_of(BK_RECORDS), n, k, qr, nr, s);
                 launch_bin_finalize_batch<T>(dd, start_of(BK_FINAL), n, k, total[BK_FINAL], s);
             });
             q = queue_of(BK_G2P, nb);
             timed(APIC_PHASE_G2P, s,
-                  [&] { launch_g2p_batch<T, DIM, DEG>(dd, start_of(BK_G2P), n, k, q, nb, adaptive, s); });
+                  [&] { launch_g2p_batch<T, DIM, DEG>(dd, start_of(BK_G2P), n, k, q, nb, adaptive, gwaves, s); });
         }
         launch_copy_back_batch<T, DIM>(dd, start_of(BK_COPY), n, n_steps, total[BK_COPY], s);
     };
@@ -1156,6 +1161,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         key_put(key, DIM * 100 + DEG * 10 + (COMP ? 1 : 0));
         key_put(key, (int)adaptive);
         key_put(key, qblocks);
+        key_put(key, kwaves * 8 + gwaves);
         key.append((const char *)starts.data(), starts.size() * 4);
         auto it = g_graphs.find(key);
         if (it == g_graphs.end()) {

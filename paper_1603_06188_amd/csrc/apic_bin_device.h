@@ -56,6 +56,24 @@ __device__ __forceinline__ uint32_t wave_max_u32(uint32_t x) {
     return x;
 }
 
+// The maximum over the wavefront, on its last lane (row shifts and row
+// broadcasts in registers; lanes without a source read 0).
+__device__ __forceinline__ uint32_t wave_max_last(uint32_t x) {
+#define APIC_DPP_MAX(ctrl, rows)                                                                          \
+    {                                                                                                     \
+        const uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xf, true);       \
+        x = x > y ? x : y;                                                                                \
+    }
+    APIC_DPP_MAX(0x111, 0xf)  // row_shr 1, 2, 4, 8
+    APIC_DPP_MAX(0x112, 0xf)
+    APIC_DPP_MAX(0x114, 0xf)
+    APIC_DPP_MAX(0x118, 0xf)
+    APIC_DPP_MAX(0x142, 0xa)  // lane 15 of rows 0 and 2 to rows 1 and 3
+    APIC_DPP_MAX(0x143, 0xc)  // lane 31 to rows 2 and 3
+#undef APIC_DPP_MAX
+    return x;
+}
+
 // True for exactly one lane among the active lanes holding each value of t.
 __device__ __forceinline__ bool first_lane_of_value(uint32_t t, bool active) {
     const int lane = lane_id();
@@ -237,13 +255,14 @@ __device__ __forceinline__ BatchStep<T> batch_step(const SceneDesc<T> *descs, co
     const int s = __builtin_amdgcn_readfirstlane(scene_of_block(start, n, item));
     b.d = descs + s;
     const uint32_t gen0[2] = {b.d->lists[0].gen, b.d->lists[1].gen};
-    b.sp = step_parity(b.d->cur0, b.d->where0, gen0, k);
-    b.cur = b.d->lists[b.sp.cur];
+    b.sp = scalar_struct(step_parity(b.d->cur0, b.d->where0, gen0, k));
+    b.cur = scalar_struct(b.d->lists[b.sp.cur]);
     b.cur.gen = b.sp.gen_cur;
-    b.nxt = b.d->lists[b.sp.nxt];
+    b.nxt = scalar_struct(b.d->lists[b.sp.nxt]);
     b.nxt.gen = b.sp.gen_nxt;
-    b.blk = item - (uint32_t)start[s];
-    b.nblk = (uint32_t)(start[s + 1] - start[s]);
+    const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane(start[s]);
+    b.blk = item - first;
+    b.nblk = (uint32_t)__builtin_amdgcn_readfirstlane(start[s + 1]) - first;
     return b;
 }
 

@@ -39,8 +39,7 @@ namespace apic {
 
 constexpr int kBuckets = 1024;   // 4 per thread of a 256-thread block
 constexpr int kMaxLevels = 32;
-constexpr int kVmaxSlots = 1024;
-constexpr int kKeyChunks = 8;     // key pass: chunks of 64 particles loaded together
+constexpr int kCflSlots = 1024;
 
 struct GridDims {
     int dim, deg;
@@ -95,7 +94,9 @@ constexpr uint32_t kFullTile = 4 * 64;
 // atomics ran in.
 struct TileTables {
     uint32_t *kcount;      // [tiles * 64] particles per key
-    uint32_t *kmov;        // [tiles * 64] of which movers
+    uint32_t *kmov;        // [tiles * 64] of which movers; once the next layout is being built, the
+                           // levels whose particle leaves the key (bit j: level j; tiles of at most
+                           // kMaxLevels levels)
     uint32_t *kprefix;     // [tiles * 64] exclusive prefix of kcount in the tile
     uint32_t *maxc;        // [tiles] largest per-key count
     uint32_t *tcount;      // [tiles] particles in the tile
@@ -162,8 +163,8 @@ struct GridState {
     T *vt;              // dim planes of G nodes: updated velocity
     T *uref;            // dim planes of `tiles`: reference velocity of each listed key tile
     uint32_t *flags;
-    uint32_t *vmax;     // [kVmaxSlots] binary32 bits; their max bounds max_i |vt_i|
-    // [kVmaxSlots] binary64 bits; the transfer to particles raises them to
+    float *vmax;        // [tiles][4]: bound of |vt_i| over the nodes of a node tile, per axis
+    // [kCflSlots] binary64 bits; the transfer to particles raises them to
     // max_p (|v_p| + cfl_c |B_p|_F) of the state it writes (null: it does not)
     unsigned long long *cfl;
     double cfl_c;       // 6 sqrt(d) / dx (Sec. 4.3)
@@ -612,28 +613,19 @@ __device__ __forceinline__ T &plane_at(T *plane, uint32_t boff) {
     return *(T *)((char *)plane + boff);
 }
 
-// The planes of particles read from a scene table, held in scalar registers
-// (the same for the whole block).
-template <typename P>
-__device__ __forceinline__ P *scalar_pointer(P *p) {
-    const uint64_t a = (uint64_t)p;
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32));
-    return (P *)(((uint64_t)hi << 32) | lo);
-}
-template <typename T>
-__device__ __forceinline__ Parts<T> scalar_parts(const Parts<T> &p) {
-    Parts<T> q;
-    q.cell = scalar_pointer(p.cell);
-    q.off = scalar_pointer(p.off);
-    q.v = scalar_pointer(p.v);
-    q.B = scalar_pointer(p.B);
-    q.F = scalar_pointer(p.F);
-    q.m = scalar_pointer(p.m);
-    q.id = scalar_pointer(p.id);
-    q.n = (int64_t)scalar_pointer((char *)p.n);
-    q.s = (int64_t)scalar_pointer((char *)p.s);
-    return q;
+// A struct read from a scene table, held in scalar registers (the same for the
+// whole block): loaded by vector loads, its pointers would take two vector
+// registers each.
+template <typename S>
+__device__ __forceinline__ S scalar_struct(const S &s) {
+    static_assert(sizeof(S) % 4 == 0, "whole words");
+    struct Words {
+        int w[sizeof(S) / 4];
+    };
+    Words x = __builtin_bit_cast(Words, s);
+#pragma unroll
+    for (size_t i = 0; i < sizeof(S) / 4; ++i) x.w[i] = __builtin_amdgcn_readfirstlane(x.w[i]);
+    return __builtin_bit_cast(S, x);
 }
 
 // Element at byte offset `boff` of a plane whose base is held in scalar

@@ -7,6 +7,30 @@ namespace apic {
 
 constexpr int kDiagBlocks = 1024;
 
+// Wavefronts per tile of the key pass and of the transfer to particles of a
+// scene (or batch) of n particles.  The results are the same bits.
+// A small scene has fewer tiles than the chip has wavefront slots, and a tile's
+// chain of loads and chunks is its time: four wavefronts share it (transfer to
+// particles of 4,096 particles 34 -> 14 us, of 238,328 42 -> 21, 24 bodies 63 ->
+// 32; key pass 10 -> 8, 13.6 -> 9).  A large one pays for the tile's prologue in
+// every wavefront, and in the key pass for a round of resolving in each:
+//   key pass: 512,000 particles 13 us with four, 16 with one; 884,736: 21 and
+//   17; 2D 1.19M: 29 and 23; cubic 9.0M: 235 and 163 (153 since the bounds of
+//   |vt| are one load).
+//   transfer to particles: 884,736 binary32 quadratic 45 with four; 2,097,152:
+//   108 and 91.  The others (two or three wavefronts per SIMD by their
+//   registers, or small 2D tiles) keep four: cubic 9.0M 727 against 735, 2D
+//   1.19M 49 against 69, binary64 cubic 1.12M 167 against 178.
+constexpr int key_waves(int64_t n) { return n >= ((int64_t)1 << 19) ? 1 : 4; }
+template <typename T, int DIM, int DEG>
+constexpr bool g2p_waves_choice() {
+    return sizeof(T) == 4 && DIM == 3 && DEG <= 2;
+}
+template <typename T, int DIM, int DEG>
+constexpr int g2p_waves(int64_t n) {
+    return g2p_waves_choice<T, DIM, DEG>() && n >= ((int64_t)1 << 20) ? 1 : 4;
+}
+
 // The transfer to grid takes a block per tile (else a wavefront).
 constexpr bool p2g_block_per_tile(int dim, int deg) { return dim == 3 && deg >= 2; }
 
@@ -97,13 +121,13 @@ void launch_grid_update_batch(const SceneDesc<T> *descs, const int32_t *start, i
                               int blocks, hipStream_t st);
 template <typename T, int DIM, int DEG>
 void launch_bin_keys_moved_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
-                                 int blocks, hipStream_t st);
+                                 int blocks, int waves, hipStream_t st);
 template <typename T, int DIM>
 void launch_bin_records_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
                               int blocks, hipStream_t st);
 template <typename T, int DIM, int DEG>
 void launch_g2p_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q, int blocks,
-                      bool adapt, hipStream_t st);
+                      bool adapt, int waves, hipStream_t st);
 // Adaptive batched steps: before each step, every scene's dt from its bound
 // slots (first: the slots cleared and raised by a pass over the particles
 // each scene starts the call with; blocks as the copy-back table).

@@ -130,7 +130,7 @@ __device__ __forceinline__ void cfl_fold64(const T *v, const T *B, double c, dou
 }
 
 // Wave-wide: the maximum of m over the wavefront raised into one of the
-// kVmaxSlots bound slots (non-negative binary64 values order as their bits;
+// kCflSlots bound slots (non-negative binary64 values order as their bits;
 // a NaN's bits exceed every finite value's).
 __device__ __forceinline__ void cfl_raise(unsigned long long *slots, uint32_t slot, double m) {
     for (int o = 32; o > 0; o >>= 1) {
@@ -138,7 +138,7 @@ __device__ __forceinline__ void cfl_raise(unsigned long long *slots, uint32_t sl
         m = y > m || y != y ? y : m;
     }
     if (lane_id() == 0 && m != 0.0)
-        atomicMax(slots + slot % (uint32_t)kVmaxSlots, (unsigned long long)__double_as_longlong(m));
+        atomicMax(slots + slot % (uint32_t)kCflSlots, (unsigned long long)__double_as_longlong(m));
 }
 
 // Support index of the node nearest the particle along one axis, from the
@@ -155,38 +155,55 @@ __device__ __forceinline__ int nearest_node(const T (&w)[DEG + 1]) {
         return w[1] >= w[2] ? 1 : 2;
 }
 
-// Bound of max_i |vt_i| over the slots the grid update raised (wave-wide).
-__device__ __forceinline__ float wave_vmax(const uint32_t *slots) {
-    static_assert(kVmaxSlots == 16 * 64, "16 slots per lane");
-    const uint4 *q = (const uint4 *)(slots + 16 * lane_id());
-    uint32_t m = 0u;
+// Largest displacement of this step along each axis, in cell units, of a
+// particle whose support lies in the node tiles around key tile t: |v_p| is at
+// most the largest |vt_i| there, since the weights are a partition of unity.
+// With a margin for rounding; ABS: and for that of a coordinate of up to n
+// cells.  (Per tile and axis, not over the whole grid: the fewer particles are
+// near enough to a key boundary to be resolved.)
+template <typename T, int DIM, bool ABS>
+__device__ __forceinline__ void tile_reach(uint32_t t, const GridState<T> &g, const StepParams<T> &prm, T *reach) {
+    const int lane = lane_id();
+    int64_t tau = 0, mul = 1;
+    bool ok = lane < (1 << DIM);
+    uint32_t rest = t;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const uint4 v = q[i];
-        const uint32_t a = v.x > v.y ? v.x : v.y, c = v.z > v.w ? v.z : v.w;
-        m = m > a ? m : a;
-        m = m > c ? m : c;
+    for (int a = 0; a < DIM; ++a) {
+        const uint32_t n = (uint32_t)g.d.TN[a];
+        const int c = (int)(a + 1 < DIM ? rest % n : rest) + ((lane >> a) & 1);
+        rest /= n;
+        ok = ok && c < (int)n;
+        tau += (int64_t)c * mul;
+        mul *= n;
     }
-    return __uint_as_float(wave_max_u32(m));
-}
-
-// Largest displacement this step in cell units, with a margin for rounding:
-// |v_p| <= max_i |vt_i| since the weights are a partition of unity.
-template <typename T>
-__device__ __forceinline__ T step_reach(float vbound, const StepParams<T> &prm, T inv_dx) {
-    return (T)vbound * prm.dt * inv_dx * T(1.0001) + T(1e-6);
+    const float4 v4 = ok ? ((const float4 *)g.vmax)[tau] : float4{0.f, 0.f, 0.f, 0.f};
+    const float vm[3] = {v4.x, v4.y, v4.z};
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        uint32_t x = ok ? __float_as_uint(vm[a]) : 0u;  // bits order as the values
+        // over the first 2^DIM lanes: within the pairs, the quad, its neighbour
+        uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true);
+        x = x > y ? x : y;
+        y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xf, 0xf, true);
+        x = x > y ? x : y;
+        y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xf, 0xf, true);
+        x = x > y ? x : y;
+        reach[a] = (T)__uint_as_float((uint32_t)__builtin_amdgcn_readfirstlane((int)x)) * prm.dt * g.inv_dx * T(1.0001) +
+                   T(1e-6) + (ABS ? (T)g.d.n[a] * T(2.4e-7) : T(0));
+    }
 }
 
 // True when the particle is farther than `reach` from every offset where its
-// base node changes (1/2 for quadratic, 0 and 1 for cubic): it keeps its key.
+// base node changes (1/2 for quadratic, 0 and 1 for the others): it keeps its
+// key.  False for a NaN offset or reach.
 template <typename T, int DIM, int DEG>
-__device__ __forceinline__ bool keeps_key(const T *off, T reach) {
-    bool far = reach < T(0.5);
+__device__ __forceinline__ bool keeps_key(const T *off, const T *reach) {
+    bool far = true;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
         const T dist = DEG == 2 ? (off[a] < T(0.5) ? T(0.5) - off[a] : off[a] - T(0.5))
                                 : (off[a] < T(0.5) ? off[a] : T(1) - off[a]);
-        far = far && dist > reach;
+        far = far && dist > reach[a];
     }
     return far;
 }
@@ -200,9 +217,6 @@ __device__ __forceinline__ uint32_t dead_chunks(int64_t n, uint32_t live) {
 // Grid velocities of the 2^DIM node tiles from the key tile on, in LDS:
 // 3D 8x8x8 nodes at x + 8 y + 68 z (the z pad spreads a wavefront's 4x4x4
 // reads over the banks), 2D 16x16 nodes at x + 16 y; component-major.
-// Grid velocities of the 2^DIM node tiles from the key tile on, in LDS:
-// 3D 8x8x8 nodes at x + 8 y + 68 z (the z pad spreads a wavefront's 4x4x4
-// reads over the banks), 2D 16x16 nodes at x + 16 y; component-major.
 template <int DIM>
 struct VtRegion {
     static constexpr int SY = DIM == 3 ? 8 : 16;
@@ -211,8 +225,11 @@ struct VtRegion {
     __device__ static constexpr int at(int x, int y, int z) { return x + SY * y + SZ * z; }
 };
 
+// Stages them, the corners c with c mod parts == part (the wavefronts of a block
+// share the work).
 template <typename T, int DIM>
-__device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> &g, T *reg) {
+__device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> &g, T *reg, int part = 0,
+                                                 int parts = 1) {
     using R = VtRegion<DIM>;
     constexpr int TE = DIM == 3 ? 4 : 8;
     const int lane = lane_id();
@@ -228,6 +245,7 @@ __device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> 
     local_coords<DIM>(lane, lc);
 #pragma unroll
     for (int corner = 0; corner < (1 << DIM); ++corner) {
+        if (corner % parts != part) continue;
         bool ok = true;
         int64_t tau = 0, mul = 1;
         int rc[3] = {0, 0, 0};
@@ -266,13 +284,35 @@ template <typename T, int DIM, bool ABS = false>
 __device__ __forceinline__ void g2p_load(const Parts<T> &src, uint32_t p, G2PRaw<T, DIM> &r) {
     const int64_t ss = src.s;
     const uint32_t pb = p * (uint32_t)sizeof(T);
-    r.cell = ABS ? 0u : src.cell[p];
-    r.m = plane_at(src.m, pb);
-    r.id = src.id ? plane_at(src.id, p * 4u) : 0;
+    r.cell = ABS ? 0u : *scalar_plane(src.cell, p * 4u);
+    r.m = *scalar_plane(src.m, pb);
+    r.id = src.id ? *scalar_plane(src.id, p * 4u) : 0;
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) r.off[a] = plane_at(src.off + a * ss, pb);
+    for (int a = 0; a < DIM; ++a) r.off[a] = *scalar_plane(src.off + a * ss, pb);
 #pragma unroll
-    for (int k = 0; k < DIM * DIM; ++k) r.F[k] = plane_at(src.F + k * ss, pb);
+    for (int k = 0; k < DIM * DIM; ++k) r.F[k] = *scalar_plane(src.F + k * ss, pb);
+}
+
+// Writes a particle's new state at q of dst (position planes: on, or the
+// coordinates of ABS).
+template <typename T, int DIM>
+__device__ __forceinline__ void g2p_store(const Parts<T> &dst, uint32_t q, uint32_t cell, const G2PRaw<T, DIM> &raw,
+                                          bool ids, const T *x, const T *vn, const T *Bs, const T *Fn) {
+    const int64_t ds = dst.s;
+    const uint32_t qb = q * (uint32_t)sizeof(T);
+    *scalar_plane(dst.cell, q * 4u) = cell;
+    *scalar_plane(dst.m, qb) = raw.m;
+    if (ids) *scalar_plane(dst.id, q * 4u) = raw.id;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        *scalar_plane(dst.off + a * ds, qb) = x[a];
+        *scalar_plane(dst.v + a * ds, qb) = vn[a];
+    }
+#pragma unroll
+    for (int k = 0; k < DIM * DIM; ++k) {
+        *scalar_plane(dst.B + k * ds, qb) = Bs[k];
+        *scalar_plane(dst.F + k * ds, qb) = Fn[k];
+    }
 }
 
 // The update of one particle from the grid velocities staged in LDS around
@@ -440,6 +480,14 @@ __device__ __forceinline__ void velocity_lds(const T *reg, const int *lk, const 
 #pragma unroll
                 for (int k = 0; k < DIM; ++k)
                     tx[k][a] = fma_t(wyz, reg[k * R::SIZE + idx] - cref[k], tx[k][a]);
+            }
+            // slice by slice: the values of a slice are in flight together, not
+            // those of the whole support (81 registers)
+            if (b == K - 1) {
+#pragma unroll
+                for (int k = 0; k < DIM; ++k)
+#pragma unroll
+                    for (int a = 0; a < K; ++a) asm volatile("" : "+v"(tx[k][a]));
             }
         }
     velocity_from_tx<T, DIM, DEG>(tx, w, cref, vn);

@@ -138,9 +138,9 @@ __global__ __launch_bounds__(256) void k_bin_records_batch(const SceneDesc<T> *d
         const SceneDesc<T> &d = *b.d;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const TileTables tab = d.tab[b.sp.nxt];
-        const BinScratch sc = d.sc;
-        const GridDims dims = d.g.d;
+        const TileTables tab = scalar_struct(d.tab[b.sp.nxt]);
+        const BinScratch sc = scalar_struct(d.sc);
+        const GridDims dims = scalar_struct(d.g.d);
         records_body<DIM>(b.nxt, tab, sc, dims, b.blk, b.nblk);
     });
 }

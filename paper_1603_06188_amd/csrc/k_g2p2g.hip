@@ -62,7 +62,6 @@ __device__ __forceinline__ void g2p2g_body(const Parts<T> &src, const Parts<T> &
     const uint32_t live_nxt = nxt.bpre[kBuckets];
     const uint32_t items = walk.nrec + dead_chunks(src.n, walk.live);
     const T dt_inv_dx = prm.dt * g.inv_dx, gs = prm.dt * g.inv_dx;
-    const T reach = step_reach<T>(wave_vmax(g.vmax), prm, g.inv_dx);
     const int64_t ds = dst.s;
     uint32_t hj = 0;  // hand-over slots used so far (alternating buffers)
     for (uint32_t r = blk; r < items; r += nblk) {
@@ -106,11 +105,8 @@ __device__ __forceinline__ void g2p2g_body(const Parts<T> &src, const Parts<T> &
                     T on[3], vn[3], Bs[9], Fn[9];
                     g2p_update<T, 3, DEG>(raw, L.vt, origin, g, dt_inv_dx, gs, lk, cn, on, vn, Bs, Fn, prm.transfer);
                     const uint32_t mykey = t * 64 + (uint32_t)local_of<3>(lk);
-                    stays = keeps_key<T, 3, DEG>(raw.off, reach);
-                    if (!stays) {
-                        bool finite;
-                        stays = key_of<T, 3, DEG>(cn, on, g.d, finite) == mykey;
-                    }
+                    bool finite;
+                    stays = key_of<T, 3, DEG>(cn, on, g.d, finite) == mykey;
                     uint32_t dkey, drank, base;
                     if (stays) {
                         dkey = mykey;
@@ -240,7 +236,6 @@ __device__ __forceinline__ void p2g_movers_body(const Parts<T> &P, const BinList
         // layout the next step builds (the one just read) starts from empty
         // lists
         for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
-            g.vmax[i] = 0u;
             cur.rec_count[i] = 0u;
             cur.nfull[i] = 0u;
             cur.nsparse[i] = 0u;

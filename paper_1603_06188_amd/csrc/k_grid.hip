@@ -84,9 +84,7 @@ __device__ __forceinline__ void grid_update_body(const BinLists &cur, const Slab
     constexpr int GE = REGS * NCOR <= 32 ? NCOR : (REGS * NCOR / 2 <= 32 ? NCOR / 2 : NCOR / 4);
     const int lane = lane_id();
     const int64_t G = g.d.G;
-    __shared__ uint32_t wave_bits[4];
     const uint32_t nrec = cur.rpre[kBuckets];
-    uint32_t bits = 0u;  // wave maximum so far of the bounds below
     const WaveWalk ww = wave_walk(blk, nblk, nrec);
     int lc[3] = {0, 0, 0};
     local_coords<DIM>(lane, lc);
@@ -204,31 +202,23 @@ __device__ __forceinline__ void grid_update_body(const BinLists &cur, const Slab
             const bool live = valid && mm[0] > T(0) && !sticky;
             const T inv_m = live ? T(1) / mm[0] : T(0);
             const int64_t node = tau * 64 + lane;
-            float vabs = 0.f;
+            uint32_t bits[4] = {0u, 0u, 0u, 0u};
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
                 // the node tile's reference added back last
                 const T vt = live ? (mm[1 + a] * inv_m + prm.dt * prm.g[a]) + own[a] : T(0);
                 g.vt[a * G + node] = vt;
-                // binary32 value not below |vt| (NaN propagates as the largest bits)
+                // the tile's bound of |vt|: binary32 values not below it, which
+                // order like their bit patterns (NaN above all)
                 const T va = vt < T(0) ? -vt : vt;
                 float f = (float)va;
                 if ((T)f < va) f = __uint_as_float(__float_as_uint(f) + 1u);  // next binary32 up
-                vabs = (f > vabs || f != f) ? f : vabs;
+                bits[a] = __float_as_uint(f) & 0x7FFFFFFFu;
             }
-            // non-negative binary32 values order like their bit patterns
-            const uint32_t mine = __float_as_uint(vabs);
-            bits = mine > bits ? mine : bits;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) bits[a] = wave_max_last(bits[a]);
+            if (lane == 63) ((uint4 *)g.vmax)[tau] = uint4{bits[0], bits[1], bits[2], bits[3]};
         }
-    }
-    // one atomic per block, blocks spread over the slots
-    bits = wave_max_u32(bits);
-    if (lane == 0) wave_bits[threadIdx.x >> 6] = bits;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t m = wave_bits[0];
-        for (int k = 1; k < (int)(blockDim.x >> 6); ++k) m = wave_bits[k] > m ? wave_bits[k] : m;
-        if (m != 0u) atomicMax(g.vmax + (blk % (uint32_t)kVmaxSlots), m);
     }
 }
 
@@ -246,9 +236,9 @@ __global__ __launch_bounds__(256) void k_grid_update_batch(const SceneDesc<T> *d
         const SceneDesc<T> &d = *b.d;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const Slabs<T> slabs = d.slabs;
-        const GridState<T> g = d.g;
-        const StepParams<T> prm = d.prm;
+        const Slabs<T> slabs = scalar_struct(d.slabs);
+        const GridState<T> g = scalar_struct(d.g);
+        const StepParams<T> prm = scalar_struct(d.prm);
         grid_update_body<T, DIM, DEG, COMP>(b.cur, slabs, g, prm, b.blk, b.nblk);
     });
 }

@@ -270,7 +270,7 @@ void launch_keep_affine(const Parts<T> &P, int transfer, hipStream_t st) {
 // One wavefront: b = max of src[0..n) (binary64; NaN propagates), then
 //   dt = b > 0 ? min(cap, nu_dx / b) : cap      (a NaN bound gives cap: the
 // flags of the transfers report a non-finite state), state[0] = dt,
-// state[1] += dt, and the kVmaxSlots bound slots are zeroed for the next
+// state[1] += dt, and the kCflSlots bound slots are zeroed for the next
 // transfer to particles (src may be those slots: each lane reads its
 // entries before it clears them).
 __global__ __launch_bounds__(64) void k_adapt_dt(const double *src, int n, unsigned long long *slots, double cap,
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(64) void k_adapt_dt(const double *src, int n, unsig
         const double y = __shfl_xor(b, o, 64);
         b = y > b || y != y ? y : b;
     }
-    for (int i = lane; i < kVmaxSlots; i += 64) slots[i] = 0ull;
+    for (int i = lane; i < kCflSlots; i += 64) slots[i] = 0ull;
     if (lane == 0) {
         double dt = cap;
         if (b > 0.0) {

@@ -20,14 +20,11 @@
 
 namespace apic {
 
-// The first block clears what the following passes of the step raise or fill.
-template <typename T>
-__device__ __forceinline__ void p2g_clear(const BinLists &nxt, const GridState<T> &g, uint32_t blk) {
+// The first block empties the lists of the layout that the following transfer
+// to particles builds.
+__device__ __forceinline__ void p2g_clear(const BinLists &nxt, uint32_t blk) {
     if (blk != 0) return;
-    // the grid update that follows raises these bounds of max |vt|, and
-    // the layout the following G2P builds starts from empty lists
     for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
-        g.vmax[i] = 0u;
         nxt.rec_count[i] = 0u;
         nxt.nfull[i] = 0u;
         nxt.nsparse[i] = 0u;
@@ -303,7 +300,7 @@ __device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur
     const int comp = wv & 3, c0 = (wv >> 2) * CZ;  // its plane and z-slices
     int lcoord[3] = {0, 0, 0};
     local_coords<3>(lane, lcoord);
-    p2g_clear(nxt, g, blk);
+    p2g_clear(nxt, blk);
     const TileWalk walk = tile_walk(cur);
     T *terms = (T *)lds, *mine = terms + wv * LEVEL + lane * L::LANE;
     U *hi = (U *)lds + comp * LP, *lo = (U *)lds + (NC + comp) * LP;
@@ -421,7 +418,7 @@ __device__ __forceinline__ void p2g_body(const Parts<T> &P, const BinLists &cur,
     const int lane = lane_id();
     int lcoord[3] = {0, 0, 0};
     local_coords<DIM>(lane, lcoord);
-    p2g_clear(nxt, g, blk);
+    p2g_clear(nxt, blk);
     const TileWalk walk = tile_walk(cur);
     for (uint32_t r = blk * 4 + (threadIdx.x >> 6); r < walk.nrec; r += nblk * 4) {
         uint32_t start, cnt, maxc, kstart;
@@ -514,11 +511,11 @@ __global__ __launch_bounds__(p2g_threads(DIM, DEG, sizeof(T))) __attribute__((am
         const SceneDesc<T> &d = *b.d;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const Parts<T> P = scalar_parts(d.bufs[b.sp.src]);
-        const TileTables tab = d.tab[b.sp.cur];
-        const Slabs<T> slabs = d.slabs;
-        const GridState<T> g = d.g;
-        const StepParams<T> prm = d.prm;
+        const Parts<T> P = scalar_struct(d.bufs[b.sp.src]);
+        const TileTables tab = scalar_struct(d.tab[b.sp.cur]);
+        const Slabs<T> slabs = scalar_struct(d.slabs);
+        const GridState<T> g = scalar_struct(d.g);
+        const StepParams<T> prm = scalar_struct(d.prm);
         p2g_any<T, DIM, DEG, COMP, false>(P, b.cur, b.nxt, tab, slabs, g, prm, b.blk, b.nblk);
     });
 }

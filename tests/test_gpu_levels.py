@@ -4,11 +4,14 @@ groups of four or eight, tiles whose busiest key holds more than 32 particles
 are stored key by key, and keys of one tile may hold from none to all of them.
 One step against the oracle at the bars of the parity tests (binary64 1e-12,
 binary32 1e-5 relative per field)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
+import oracle
 from paper_1603_06188_amd import scenes
-from tests.test_gpu_parity import TOL, compare_step
+from tests.test_gpu_parity import TOL, compare_step, rel
 
 pytestmark = pytest.mark.gpu
 
@@ -45,3 +48,55 @@ def test_levels(dim, degree, precision, compensated, counts):
     s = _scene(dim, degree, precision, counts, seed=len(counts) + 10 * dim + degree)
     ds = _b().DeviceScene(s, compensated=compensated)
     compare_step(s, ds, TOL[precision], label=f"{dim}d deg{degree} {precision} {counts}")
+
+
+@pytest.mark.parametrize("dim,degree", [(3, 2), (3, 3), (2, 2)])
+@pytest.mark.parametrize("crowd", [24, 60])
+def test_movers_of_crowded_tiles(dim, degree, crowd):
+    """Chained steps of a cloud with about `crowd` particles per key whose
+    particles change key by the tenth every step: marks of many levels (24) and
+    tiles stored key by key that their particles enter and leave (60), against
+    the oracle in binary64 (1e-11 over the steps)."""
+    b = _b()
+    cells, steps, width = 16, 4, 3.0 if dim == 3 else 5.0
+    n = int(crowd * width ** dim)
+    s = scenes.random_particles(n, dim=dim, cells=cells, degree=degree, seed=crowd + dim + degree, model=0,
+                                vel_sigma=0.3, b_sigma=0.002)
+    rng = np.random.default_rng(crowd)
+    x = (5.3 + width * rng.random((n, dim))) / cells
+    s = dataclasses.replace(s.with_state(x=x, v=s.v + np.array([1.5, 1.0, -0.7])[:dim]), dt=1e-2)
+    ds = b.DeviceScene(s)
+    ds.step(steps)
+    got = ds.state()
+    g = oracle.Grid(s.dim, s.degree, s.cells, s.dx)
+    x, v, B, F = s.x, s.v, s.B, s.F
+    shift = 0.5 if degree == 2 else 0.0
+    moved = 0
+    for _ in range(steps):
+        r = oracle.step(g, x, v, B, F, s.m, s.V, s.model, s.mu, s.lam, s.dt, s.gravity, s.band, transfer=s.transfer)
+        moved += int(np.count_nonzero((np.floor(r["x_new"] / s.dx - shift) != np.floor(x / s.dx - shift)).any(axis=1)))
+        x, v, B, F = r["x_new"], r["v_new"], r["B_new"], r["F_new"]
+    assert moved > n // 10 and ds.flags() == 0
+    assert float(np.abs(got["x"] - x).max() / s.dx) <= 1e-11
+    for key, ref in (("v", v), ("B", B), ("F", F)):
+        assert rel(got[key], ref) <= 1e-11, (key, rel(got[key], ref))
+
+
+def test_wavefronts_per_tile_give_the_same_bits():
+    """A scene below the sizes at which the key pass and the transfer to
+    particles take one wavefront per tile, and the same scene in a batch above
+    them: the same bits."""
+    b = _b()
+    hosts = []
+    for k in range(3):
+        s = scenes.cube3d(seed=20 + k, cells=72, precision="fp32", steps=1)
+        rng = np.random.default_rng(k)
+        hosts.append(dataclasses.replace(s.with_state(v=s.v + rng.normal(0.0, 2.0, size=s.v.shape)), dt=1e-3))
+    assert hosts[0].n < (1 << 19) and sum(h.n for h in hosts) >= (1 << 20)
+    alone = b.DeviceScene(hosts[1], compensated=True)
+    alone.step(3)
+    batch = b.SceneBatch([b.DeviceScene(h, compensated=True) for h in hosts])
+    batch.step(3)
+    ga, gb = alone.state(), batch.scenes[1].state()
+    for key in ("cell", "off", "v", "B", "F", "m"):
+        assert np.array_equal(ga[key], gb[key]), key
