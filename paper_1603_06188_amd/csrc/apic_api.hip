@@ -537,31 +537,28 @@ struct OpArgs {
 };
 
 // Bins the particles of `src` (at their current positions) into list
-// parity `nxt` and writes them, in the new order, to `dst`.
+// parity `nxt` and writes them, in the new order, to `dst`; through a copy in
+// `via` when dst is src.
 template <typename T, int DIM, int DEG, bool ABS = false>
-void bin_static(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> &dst, int nxt, hipStream_t st) {
+void bin_static(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> &dst, const Parts<T> *via, int nxt,
+                hipStream_t st) {
     begin_build(v, ss, nxt, st);
-    launch_bin_reset(v.lists[nxt], st);
-    launch_bin_keys_static<T, DIM, DEG, ABS>(src, v.L.d, v.lists[nxt], v.sc, v.g.flags, v.g.inv_dx, st);
-    launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, st);
-    launch_bin_finalize(v.lists[nxt], v.L.rc, st);
-    launch_bin_scatter_copy<T, DIM>(src, dst, v.lists[nxt], v.tab[nxt], v.sc, st);
+    launch_bin_keys_static<T, DIM, DEG, ABS>(src, via, v.L.d, v.lists[nxt], v.sc, v.g.flags, v.g.inv_dx, st);
+    launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, true, st);
+    launch_bin_finalize(v.lists[nxt], v.lists[1 - nxt], v.L.rc, st);
+    launch_bin_gather<T, DIM>(via ? *via : src, dst, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, st);
 }
 
-// One G2P from `src` (layout `cur`) into `dst` (layout 1 - cur).  The
-// counters of the new layout were zeroed by the preceding P2G; `reset`
-// zeroes them again (calls outside a whole step).
+// One G2P from `src` (layout `cur`) into `dst` (layout 1 - cur).
 template <typename T, int DIM, int DEG, bool ABS = false>
-void g2p_rebin(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> &dst, int cur, bool reset,
-               hipStream_t st) {
+void g2p_rebin(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> &dst, int cur, hipStream_t st) {
     const int nxt = 1 - cur;
     begin_build(v, ss, nxt, st);
     timed(APIC_PHASE_BIN, st, [&] {
-        if (reset) launch_bin_reset(v.lists[nxt], st);
         launch_bin_keys_moved<T, DIM, DEG, ABS>(src, v.lists[cur], v.tab[cur], v.g, v.prm, v.lists[nxt], v.sc,
                                                 v.L.rc, st);
-        launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, st);
-        launch_bin_finalize(v.lists[nxt], v.L.rc, st);
+        launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, false, st);
+        launch_bin_finalize(v.lists[nxt], v.lists[1 - nxt], v.L.rc, st);
     });
     timed(APIC_PHASE_G2P, st, [&] {
         launch_g2p<T, DIM, DEG, ABS>(src, dst, v.lists[cur], v.tab[cur], v.lists[nxt], v.tab[nxt], v.sc, v.g, v.prm,
@@ -585,8 +582,8 @@ void g2p2g_rebin(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T>
     timed(APIC_PHASE_BIN, st, [&] {
         launch_bin_keys_moved<T, DIM, DEG>(src, v.lists[cur], v.tab[cur], v.g, v.prm, v.lists[nxt], v.sc, v.L.rc,
                                            st);
-        launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, st);
-        launch_bin_finalize(v.lists[nxt], v.L.rc, st);
+        launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, false, st);
+        launch_bin_finalize(v.lists[nxt], v.lists[1 - nxt], v.L.rc, st);
     });
     if constexpr (fused_step<T, DIM, DEG>()) {
         timed(APIC_PHASE_G2P, st, [&] {
@@ -607,8 +604,7 @@ apic_status run(Op op, const apic_scene *s, int64_t cap, hipStream_t st, const O
     switch (op) {
         case Op::Sort: {
             const int nxt = 1 - ss.cur;
-            bin_static<T, DIM, DEG, ABS>(v, ss, v.user, v.shadow, nxt, st);
-            launch_copy_state<T, DIM>(v.shadow, v.user, st);
+            bin_static<T, DIM, DEG, ABS>(v, ss, v.user, v.user, &v.shadow, nxt, st);
             ss.cur = nxt;
             ss.binned = true;
             if (ss.grid_meta == nxt) ss.grid_meta = -1;
@@ -622,7 +618,7 @@ apic_status run(Op op, const apic_scene *s, int64_t cap, hipStream_t st, const O
                 v = make_view<T>(s, cap, ss);
             }
             launch_keep_affine<T, DIM>(v.user, s->prm.transfer, st);
-            launch_p2g<T, DIM, DEG, COMP, ABS>(v.user, v.lists[ss.cur], v.lists[1 - ss.cur], v.tab[ss.cur], v.slabs, v.g,
+            launch_p2g<T, DIM, DEG, COMP, ABS>(v.user, v.lists[ss.cur], v.tab[ss.cur], v.slabs, v.g,
                                           v.prm, v.L.rc, st);
             ss.grid_meta = ss.cur;
             ss.vt_valid = false;
@@ -637,7 +633,7 @@ apic_status run(Op op, const apic_scene *s, int64_t cap, hipStream_t st, const O
         case Op::G2P:
             if (!ss.vt_valid || !ss.binned || ss.grid_meta != ss.cur)
                 return fail(APIC_E_INVAL, "apic_g2p needs apic_p2g and apic_grid_update on the current particles");
-            g2p_rebin<T, DIM, DEG, ABS>(v, ss, v.user, v.shadow, ss.cur, true, st);
+            g2p_rebin<T, DIM, DEG, ABS>(v, ss, v.user, v.shadow, ss.cur, st);
             launch_copy_state<T, DIM>(v.shadow, v.user, st);
             ss.cur = 1 - ss.cur;
             ss.vt_valid = false;
@@ -684,7 +680,7 @@ apic_status run_steps(apic_scene *s, int64_t cap, int32_t n_steps, int32_t sort_
     Parts<T> bufs[2] = {v.user, v.shadow};
     int where = 0;
     if (!ss.binned) {
-        timed(APIC_PHASE_SORT, st, [&] { bin_static<T, DIM, DEG, ABS>(v, ss, v.user, v.shadow, 1 - ss.cur, st); });
+        timed(APIC_PHASE_SORT, st, [&] { bin_static<T, DIM, DEG, ABS>(v, ss, v.user, v.shadow, nullptr, 1 - ss.cur, st); });
         ss.cur = 1 - ss.cur;
         where = 1;
     }
@@ -706,7 +702,7 @@ apic_status run_steps(apic_scene *s, int64_t cap, int32_t n_steps, int32_t sort_
     for (int32_t k = 0; k < n_steps; ++k) {
         if (sort_every > 0 && k > 0 && k % sort_every == 0) {
             timed(APIC_PHASE_SORT, st,
-                  [&] { bin_static<T, DIM, DEG, ABS>(v, ss, bufs[where], bufs[1 - where], 1 - ss.cur, st); });
+                  [&] { bin_static<T, DIM, DEG, ABS>(v, ss, bufs[where], bufs[1 - where], nullptr, 1 - ss.cur, st); });
             ss.cur = 1 - ss.cur;
             where = 1 - where;
             slabs_ready = false;
@@ -721,7 +717,7 @@ apic_status run_steps(apic_scene *s, int64_t cap, int32_t n_steps, int32_t sort_
         }
         if (!slabs_ready) {
             timed(APIC_PHASE_P2G, st, [&] {
-                launch_p2g<T, DIM, DEG, COMP, ABS>(bufs[where], v.lists[ss.cur], v.lists[1 - ss.cur], v.tab[ss.cur],
+                launch_p2g<T, DIM, DEG, COMP, ABS>(bufs[where], v.lists[ss.cur], v.tab[ss.cur],
                                               v.slabs, v.g, v.prm, v.L.rc, st);
             });
         }
@@ -735,7 +731,7 @@ apic_status run_steps(apic_scene *s, int64_t cap, int32_t n_steps, int32_t sort_
         if (fuse)
             g2p2g_rebin<T, DIM, DEG, COMP>(v, ss, bufs[where], bufs[1 - where], ss.cur, st);
         else
-            g2p_rebin<T, DIM, DEG, ABS>(v, ss, bufs[where], bufs[1 - where], ss.cur, false, st);
+            g2p_rebin<T, DIM, DEG, ABS>(v, ss, bufs[where], bufs[1 - where], ss.cur, st);
         slabs_ready = fuse;
         ss.cur = 1 - ss.cur;
         where = 1 - where;
@@ -1006,7 +1002,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         View<T> v = make_view<T>(&scenes[i], cap, ss);
         int where = 0;
         if (!ss.binned) {
-            timed(APIC_PHASE_SORT, st, [&] { bin_static<T, DIM, DEG>(v, ss, v.user, v.shadow, 1 - ss.cur, st); });
+            timed(APIC_PHASE_SORT, st, [&] { bin_static<T, DIM, DEG>(v, ss, v.user, v.shadow, nullptr, 1 - ss.cur, st); });
             ss.cur = 1 - ss.cur;
             ss.binned = true;
             where = 1;

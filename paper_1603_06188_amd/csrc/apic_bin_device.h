@@ -38,6 +38,54 @@ __device__ __forceinline__ uint32_t block_bucket_prefix(const uint32_t *v, uint3
     return total;
 }
 
+// The same for three tables at once (their loads, scans and barriers shared).
+__device__ __forceinline__ void block_bucket_prefix3(const uint32_t *a, const uint32_t *b, const uint32_t *c,
+                                                     uint32_t *pa, uint32_t *pb, uint32_t *pc, uint32_t *part,
+                                                     uint32_t &ta, uint32_t &tb, uint32_t &tc) {
+    const int tid = (int)threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const uint32_t *v[3] = {a, b, c};
+    uint32_t *pre[3] = {pa, pb, pc};
+    uint4 q[3];
+    uint32_t own[3], inc[3], total[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        q[k] = ((const uint4 *)v[k])[tid];
+        own[k] = inc[k] = q[k].x + q[k].y + q[k].z + q[k].w;
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            const uint32_t y = __shfl_up(inc[k], o, 64);
+            if (lane >= o) inc[k] += y;
+        }
+    if (lane == 63) {
+#pragma unroll
+        for (int k = 0; k < 3; ++k) part[4 * k + w] = inc[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        uint32_t before = 0;
+        total[k] = 0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t p = part[4 * k + i];
+            before += i < w ? p : 0u;
+            total[k] += p;
+        }
+        const uint32_t e = before + inc[k] - own[k];
+        pre[k][4 * tid + 0] = e;
+        pre[k][4 * tid + 1] = e + q[k].x;
+        pre[k][4 * tid + 2] = e + q[k].x + q[k].y;
+        pre[k][4 * tid + 3] = e + q[k].x + q[k].y + q[k].z;
+    }
+    __syncthreads();
+    ta = total[0];
+    tb = total[1];
+    tc = total[2];
+}
+
 // Bucket of list index r (r below the table's total): the last bucket whose
 // exclusive prefix is <= r (it holds r).  Wave-wide, r wave-uniform.
 __device__ __forceinline__ uint32_t bucket_find(const uint32_t *pre, uint32_t r) {
@@ -212,6 +260,60 @@ __device__ __forceinline__ void rank_movers(uint32_t *head, uint32_t n, const Bi
         for (uint32_t b = h; b; b = sc.next[b - 1]) r += sc.pord[b - 1] < oa ? 1u : 0u;
         sc.prank[a - 1] = r;
     }
+}
+
+// A particle's values of all planes: loaded all at once, then stored (a load
+// after a store to another plane could not be moved above it, so every plane
+// would be a round trip of its own).
+template <typename T, int DIM>
+struct ParticleState {
+    uint32_t cell;
+    int32_t id;
+    T m, off[DIM], v[DIM], B[DIM * DIM], F[DIM * DIM];
+};
+template <typename T, int DIM>
+__device__ __forceinline__ void load_particle(const Parts<T> &src, uint32_t p, bool ids, ParticleState<T, DIM> &x) {
+    const int64_t s = src.s;
+    const uint32_t pb = p * (uint32_t)sizeof(T);
+    x.cell = *scalar_plane(src.cell, p * 4u);
+    x.id = ids ? *scalar_plane(src.id, p * 4u) : 0;
+    x.m = *scalar_plane(src.m, pb);
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        x.off[a] = *scalar_plane(src.off + a * s, pb);
+        x.v[a] = *scalar_plane(src.v + a * s, pb);
+    }
+#pragma unroll
+    for (int k = 0; k < DIM * DIM; ++k) {
+        x.B[k] = *scalar_plane(src.B + k * s, pb);
+        x.F[k] = *scalar_plane(src.F + k * s, pb);
+    }
+}
+template <typename T, int DIM>
+__device__ __forceinline__ void store_particle(const Parts<T> &dst, uint32_t q, bool ids,
+                                               const ParticleState<T, DIM> &x) {
+    const int64_t s = dst.s;
+    const uint32_t qb = q * (uint32_t)sizeof(T);
+    *scalar_plane(dst.cell, q * 4u) = x.cell;
+    if (ids) *scalar_plane(dst.id, q * 4u) = x.id;
+    *scalar_plane(dst.m, qb) = x.m;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        *scalar_plane(dst.off + a * s, qb) = x.off[a];
+        *scalar_plane(dst.v + a * s, qb) = x.v[a];
+    }
+#pragma unroll
+    for (int k = 0; k < DIM * DIM; ++k) {
+        *scalar_plane(dst.B + k * s, qb) = x.B[k];
+        *scalar_plane(dst.F + k * s, qb) = x.F[k];
+    }
+}
+template <typename T, int DIM>
+__device__ __forceinline__ void copy_particle(const Parts<T> &src, const Parts<T> &dst, uint32_t p, uint32_t q,
+                                              bool ids) {
+    ParticleState<T, DIM> x;
+    load_particle<T, DIM>(src, p, ids, x);
+    store_particle<T, DIM>(dst, q, ids, x);
 }
 
 // One scene's view of step k of a batched launch: its descriptor, the lists

@@ -42,37 +42,37 @@ template <typename T, int DIM>
 void launch_copy_state(const Parts<T> &src, const Parts<T> &dst, hipStream_t st);
 
 // --- binning (apic_sort and the re-binning inside apic_g2p) ----------------
-// Zeroes the counters of the lists a layout is about to be built in.
-void launch_bin_reset(const BinLists &nxt, hipStream_t st);
-
-// Keys of particles at their current positions (apic_sort).
+// Keys of particles at their current positions (apic_sort); `to`: the particles
+// are copied there as well (null: not).
 template <typename T, int DIM, int DEG, bool ABS = false>
-void launch_bin_keys_static(const Parts<T> &P, const GridDims &d, const BinLists &nxt, const BinScratch &sc,
-                            uint32_t *flags, T inv_dx, hipStream_t st);
+void launch_bin_keys_static(const Parts<T> &P, const Parts<T> *to, const GridDims &d, const BinLists &nxt,
+                            const BinScratch &sc, uint32_t *flags, T inv_dx, hipStream_t st);
 
 // Per listed tile of `nxt`: key counts and prefix sums, the tile's place in
 // its bucket, its record index, level tables and the node tiles of the
 // next grid update.
 template <int DIM>
 void launch_bin_records(const GridDims &d, const BinLists &nxt, const TileTables &tab, const BinScratch &sc,
-                        int64_t max_records, hipStream_t st);
+                        int64_t max_records, bool from_scratch, hipStream_t st);
 
-// Prefix tables (records and particle bases per bucket) of a finished layout.
-void launch_bin_finalize(const BinLists &nxt, int64_t max_records, hipStream_t st);
+// Prefix tables (records and particle bases per bucket) of a finished layout; the
+// counters of the other parity are zeroed for the build after it (a workspace
+// starts with those of both zero).
+void launch_bin_finalize(const BinLists &nxt, const BinLists &other, int64_t max_records, hipStream_t st);
 template <typename T>
 void launch_bin_finalize_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, int blocks,
                                hipStream_t st);
 
-// Moves every particle to its binned position (apic_sort).
+// Moves every particle from src to its binned position in dst (apic_sort).
 template <typename T, int DIM>
-void launch_bin_scatter_copy(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const TileTables &tab,
-                             const BinScratch &sc, hipStream_t st);
+void launch_bin_gather(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const TileTables &tab,
+                       const BinScratch &sc, int64_t max_records, hipStream_t st);
 
 // --- transfers ----------------------------------------------------------------
 // P2G over the layout `cur`; also zeroes the counters of `nxt` and the
 // bounds of max |vt| for the grid update and re-binning that follow.
 template <typename T, int DIM, int DEG, bool COMP, bool ABS = false>
-void launch_p2g(const Parts<T> &P, const BinLists &cur, const BinLists &nxt, const TileTables &tab,
+void launch_p2g(const Parts<T> &P, const BinLists &cur, const TileTables &tab,
                 const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm, int64_t max_records,
                 hipStream_t st);
 

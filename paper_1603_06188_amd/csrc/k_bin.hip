@@ -13,52 +13,53 @@ static inline int blocks_for(int64_t work, int threads, int cap) {
     return (int)b;
 }
 
-// --- counters of a layout about to be built ---------------------------------------
-__global__ void k_bin_reset(BinLists nxt) {
-    for (int t = (int)threadIdx.x; t < kBuckets; t += (int)blockDim.x) {
-        nxt.rec_count[t] = 0u;
-        nxt.nfull[t] = 0u;
-        nxt.nsparse[t] = 0u;
-        nxt.tot[t] = 0u;
-    }
-    if (threadIdx.x < kCtrCount) nxt.ctr[threadIdx.x] = 0u;
-}
-
-void launch_bin_reset(const BinLists &nxt, hipStream_t st) {
-    hipLaunchKernelGGL(k_bin_reset, dim3(1), dim3(256), 0, st, nxt);
-}
-
-// --- keys of particles at their current position (apic_sort); every particle
-// counts as a mover, so ranks come from the per-key counters ---------------------
-template <typename T, int DIM, int DEG, bool ABS>
-__global__ __launch_bounds__(256) void k_bin_keys_static(Parts<T> P, GridDims d, BinLists nxt, BinScratch sc,
-                                                         uint32_t *flags, T inv_dx) {
+// --- keys of particles at their current position (apic_sort): each takes a
+// provisional rank in its key from the key's counter, the order the device runs
+// its atomics in; the gather pass orders a key's particles by their index.
+// COPY: the particles are also copied to `to` (where the gather reads them when
+// it writes over `P`), while the counters' round trips are under way ---------------
+template <typename T, int DIM, int DEG, bool ABS, bool COPY>
+__global__ __launch_bounds__(256) void k_bin_keys_static(Parts<T> P, Parts<T> to, GridDims d, BinLists nxt,
+                                                         BinScratch sc, uint32_t *flags, T inv_dx) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const bool active = p < P.n;
     uint32_t key = kDeadKey;
+    ParticleState<T, DIM> state;
     if (active) {
         int ci[3] = {0, 0, 0};
         T x[DIM], off[DIM];
 #pragma unroll
         for (int a = 0; a < DIM; ++a) x[a] = P.off[a * P.s + p];
-        particle_cells<T, DIM, ABS>(ABS ? 0u : P.cell[p], x, inv_dx, ci, off);
+        const uint32_t cell = ABS ? 0u : P.cell[p];
+        if constexpr (COPY) load_particle<T, DIM>(P, (uint32_t)p, P.id != nullptr, state);
+        particle_cells<T, DIM, ABS>(cell, x, inv_dx, ci, off);
         bool finite;
         key = key_of<T, DIM, DEG>(ci, off, d, finite);
         if (key == kDeadKey) atomicOr(flags, finite ? FLAG_OUT_OF_DOMAIN : FLAG_NONFINITE);
     }
-    const uint32_t rank = bin_take_slot(key, active, (uint32_t)p, (uint64_t)p, nxt, sc);
+    uint32_t rank = 0u;
+    if (active) rank = atomicAdd(key == kDeadKey ? nxt.ctr + kCtrDead : sc.key_count + key, 1u);
+    if (first_lane_of_value(key >> 6, active && key != kDeadKey)) list_tile(key >> 6, nxt);
     if (active) {
+        if constexpr (COPY) store_particle<T, DIM>(to, (uint32_t)p, P.id != nullptr, state);
         sc.pkey[p] = key;
         sc.prank[p] = rank;
     }
 }
 
 template <typename T, int DIM, int DEG, bool ABS>
-void launch_bin_keys_static(const Parts<T> &P, const GridDims &d, const BinLists &nxt, const BinScratch &sc,
-                            uint32_t *flags, T inv_dx, hipStream_t st) {
+void launch_bin_keys_static(const Parts<T> &P, const Parts<T> *to, const GridDims &d, const BinLists &nxt,
+                            const BinScratch &sc, uint32_t *flags, T inv_dx, hipStream_t st) {
     if (P.n == 0) return;
-    hipLaunchKernelGGL((k_bin_keys_static<T, DIM, DEG, ABS>), dim3((unsigned)((P.n + 255) / 256)), dim3(256), 0, st,
-                       P, d, nxt, sc, flags, inv_dx);
+    Parts<T> s2 = P, d2 = to ? *to : P;
+    if (!s2.id || !d2.id) s2.id = d2.id = nullptr;
+    const dim3 blocks((unsigned)((P.n + 255) / 256));
+    if (to)
+        hipLaunchKernelGGL((k_bin_keys_static<T, DIM, DEG, ABS, true>), blocks, dim3(256), 0, st, s2, d2, d, nxt, sc,
+                           flags, inv_dx);
+    else
+        hipLaunchKernelGGL((k_bin_keys_static<T, DIM, DEG, ABS, false>), blocks, dim3(256), 0, st, s2, d2, d, nxt, sc,
+                           flags, inv_dx);
 }
 
 // --- per listed tile: counts, prefix sums, tile offset, level table ------------------
@@ -74,7 +75,7 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t x, uint32_t &total) 
     return inc - x;
 }
 
-template <int DIM>
+template <int DIM, bool STATIC = false>
 __device__ __forceinline__ void records_body(const BinLists &nxt, const TileTables &tab, const BinScratch &sc,
                                              const GridDims &d, uint32_t blk, uint32_t nblk) {
     __shared__ uint32_t rpre[kBuckets + 4];
@@ -88,7 +89,7 @@ __device__ __forceinline__ void records_body(const BinLists &nxt, const TileTabl
         const uint32_t c = mov + sc.scount[key];
         sc.key_count[key] = 0u;
         sc.scount[key] = 0u;
-        if (mov) rank_movers(sc.head + key, mov, sc);
+        if (!STATIC && mov) rank_movers(sc.head + key, mov, sc);
         uint32_t total;
         const uint32_t kp = wave_excl_scan(c, total);
         const uint32_t mx = wave_max_u32(c);
@@ -125,9 +126,10 @@ __device__ __forceinline__ void records_body(const BinLists &nxt, const TileTabl
     }
 }
 
-template <int DIM>
+// STATIC: a build from scratch, whose particles are on no mover lists.
+template <int DIM, bool STATIC>
 __global__ __launch_bounds__(256) void k_bin_records(BinLists nxt, TileTables tab, BinScratch sc, GridDims d) {
-    records_body<DIM>(nxt, tab, sc, d, blockIdx.x, gridDim.x);
+    records_body<DIM, STATIC>(nxt, tab, sc, d, blockIdx.x, gridDim.x);
 }
 
 template <typename T, int DIM, bool QUEUE>
@@ -163,22 +165,10 @@ __global__ __launch_bounds__(256) void k_copy_back_batch(const SceneDesc<T> *des
                                                          int k) {
     const BatchStep<T> b = batch_step<T>(descs, start, n, k, blockIdx.x);
     if (b.sp.src != 1) return;
-    const Parts<T> &src = b.d->bufs[1], &dst = b.d->bufs[0];
-    for (int64_t j = (int64_t)b.blk * blockDim.x + threadIdx.x; j < src.n; j += (int64_t)b.nblk * blockDim.x) {
-        dst.cell[j] = src.cell[j];
-        dst.m[j] = src.m[j];
-        if (src.id && dst.id) dst.id[j] = src.id[j];
-#pragma unroll
-        for (int a = 0; a < DIM; ++a) {
-            dst.off[a * dst.s + j] = src.off[a * src.s + j];
-            dst.v[a * dst.s + j] = src.v[a * src.s + j];
-        }
-#pragma unroll
-        for (int q = 0; q < DIM * DIM; ++q) {
-            dst.B[q * dst.s + j] = src.B[q * src.s + j];
-            dst.F[q * dst.s + j] = src.F[q * src.s + j];
-        }
-    }
+    const Parts<T> src = scalar_struct(b.d->bufs[1]), dst = scalar_struct(b.d->bufs[0]);
+    const bool ids = src.id != nullptr && dst.id != nullptr;
+    for (int64_t j = (int64_t)b.blk * blockDim.x + threadIdx.x; j < src.n; j += (int64_t)b.nblk * blockDim.x)
+        copy_particle<T, DIM>(src, dst, (uint32_t)j, (uint32_t)j, ids);
 }
 
 template <typename T, int DIM>
@@ -206,17 +196,23 @@ __device__ __forceinline__ uint32_t bucket_search(const uint32_t *pre, uint32_t 
     return lo;
 }
 
-__device__ __forceinline__ void finalize_body(const BinLists &nxt, uint32_t blk, uint32_t nblk) {
+// The counters of the other parity's build are not needed once the layout that
+// followed it is finished: they are zeroed here, for the build after this one.
+__device__ __forceinline__ void finalize_body(const BinLists &nxt, const BinLists &other, uint32_t blk, uint32_t nblk) {
     __shared__ uint32_t rpre[kBuckets + 1], fpre[kBuckets + 1], bpre[kBuckets + 1], part[12];
-    const uint32_t nrec = block_bucket_prefix(nxt.rec_count, rpre, part);
-    const uint32_t nfull = block_bucket_prefix(nxt.nfull, fpre, part + 4);
+    uint32_t nrec, nfull, live;
+    block_bucket_prefix3(nxt.rec_count, nxt.nfull, nxt.tot, rpre, fpre, bpre, part, nrec, nfull, live);
     if (threadIdx.x == 0) rpre[kBuckets] = nrec;
     if (blk == 0) {
-        const uint32_t live = block_bucket_prefix(nxt.tot, bpre, part + 8);
         for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
             nxt.rpre[i] = rpre[i];
             nxt.bpre[i] = bpre[i];
+            other.rec_count[i] = 0u;
+            other.nfull[i] = 0u;
+            other.nsparse[i] = 0u;
+            other.tot[i] = 0u;
         }
+        if (threadIdx.x < kCtrCount) other.ctr[threadIdx.x] = 0u;
         if (threadIdx.x == 0) {
             nxt.rpre[kBuckets] = nrec;
             nxt.bpre[kBuckets] = live;
@@ -233,17 +229,19 @@ __device__ __forceinline__ void finalize_body(const BinLists &nxt, uint32_t blk,
     }
 }
 
-__global__ __launch_bounds__(256) void k_bin_finalize(BinLists nxt) { finalize_body(nxt, blockIdx.x, gridDim.x); }
+__global__ __launch_bounds__(256) void k_bin_finalize(BinLists nxt, BinLists other) {
+    finalize_body(nxt, other, blockIdx.x, gridDim.x);
+}
 
-void launch_bin_finalize(const BinLists &nxt, int64_t max_records, hipStream_t st) {
-    hipLaunchKernelGGL(k_bin_finalize, dim3(blocks_for(max_records, 256, 128)), dim3(256), 0, st, nxt);
+void launch_bin_finalize(const BinLists &nxt, const BinLists &other, int64_t max_records, hipStream_t st) {
+    hipLaunchKernelGGL(k_bin_finalize, dim3(blocks_for(max_records, 256, 128)), dim3(256), 0, st, nxt, other);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_bin_finalize_batch(const SceneDesc<T> *descs, const int32_t *start, int n,
                                                             int k) {
     const BatchStep<T> b = batch_step<T>(descs, start, n, k, blockIdx.x);
-    finalize_body(b.nxt, b.blk, b.nblk);
+    finalize_body(b.nxt, b.cur, b.blk, b.nblk);
 }
 
 template <typename T>
@@ -257,51 +255,95 @@ template void launch_bin_finalize_batch<double>(const SceneDesc<double> *, const
 
 template <int DIM>
 void launch_bin_records(const GridDims &d, const BinLists &nxt, const TileTables &tab, const BinScratch &sc,
-                        int64_t max_records, hipStream_t st) {
-    hipLaunchKernelGGL((k_bin_records<DIM>), dim3(blocks_for(max_records, 4, 2048)), dim3(256), 0, st, nxt, tab, sc,
-                       d);
+                        int64_t max_records, bool from_scratch, hipStream_t st) {
+    const dim3 blocks(blocks_for(max_records, 4, 2048));
+    if (from_scratch)
+        hipLaunchKernelGGL((k_bin_records<DIM, true>), blocks, dim3(256), 0, st, nxt, tab, sc, d);
+    else
+        hipLaunchKernelGGL((k_bin_records<DIM, false>), blocks, dim3(256), 0, st, nxt, tab, sc, d);
 }
 
 // --- moves every particle to its binned position (apic_sort) ------------------------
-template <typename T, int DIM>
-__global__ __launch_bounds__(256) void k_bin_scatter_copy(Parts<T> src, Parts<T> dst, BinLists nxt, TileTables tab,
-                                                          BinScratch sc) {
+// First every key's particles are listed (key after key, in provisional order;
+// the dead after all), then a block per tile puts each key's list in order in
+// LDS and gathers the tile's particles plane by plane: whole-line writes and one
+// scattered read per value, where moving each particle from its old place wrote
+// parts of lines that several XCDs' caches held (2.1M binary32 particles in
+// lexicographic order: 805 us, the two passes now 18 and 216; 4,096 of them: 17
+// us, now 3 and 12, where launches and round trips bound both).
+__global__ __launch_bounds__(256) void k_bin_place(int64_t n, BinLists nxt, TileTables tab, BinScratch sc) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= src.n) return;
-    const uint32_t live = nxt.bpre[kBuckets];
-    const uint32_t key = sc.pkey[p];
-    const uint32_t rank = sc.prank[p];
-    const int64_t q = bin_destination(key, rank, tab, bucket_base_of(key, nxt.bpre), live);
-    dst.cell[q] = src.cell[p];
-    dst.m[q] = src.m[p];
-    if (src.id) dst.id[q] = src.id[p];
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        dst.off[a * dst.s + q] = src.off[a * src.s + p];
-        dst.v[a * dst.s + q] = src.v[a * src.s + p];
-    }
-#pragma unroll
-    for (int k = 0; k < DIM * DIM; ++k) {
-        dst.B[k * dst.s + q] = src.B[k * src.s + p];
-        dst.F[k * dst.s + q] = src.F[k * src.s + p];
+    if (p >= n) return;
+    const uint32_t key = sc.pkey[p], rank = sc.prank[p];
+    uint32_t at = nxt.bpre[kBuckets];
+    if (key != kDeadKey) at = nxt.bpre[bucket_of(key >> 6)] + tab.off[key >> 6] + tab.kprefix[key];
+    sc.next[at + rank] = (uint32_t)p;
+}
+
+template <typename T, int DIM>
+__global__ __launch_bounds__(256) void k_bin_gather(Parts<T> src, Parts<T> dst, BinLists nxt, TileTables tab,
+                                                    BinScratch sc) {
+    __shared__ uint32_t listed[64 * kMaxLevels], order[64 * kMaxLevels];
+    __shared__ uint32_t lvl_off[kMaxLevels];
+    __shared__ uint64_t lvl_mask[kMaxLevels];
+    const int lane = lane_id(), wv = (int)(threadIdx.x >> 6);
+    const TileWalk walk = tile_walk(nxt);
+    const uint32_t *src_of = sc.next;
+    const bool ids = src.id != nullptr;
+    const uint32_t dead = (uint32_t)((src.n - (int64_t)walk.live + 255) / 256);
+    for (uint32_t r = blockIdx.x; r < walk.nrec + dead; r += gridDim.x) {
+        if (r >= walk.nrec) {
+            const uint32_t q = walk.live + (r - walk.nrec) * 256u + threadIdx.x;
+            if ((int64_t)q < src.n) copy_particle<T, DIM>(src, dst, src_of[q], q, ids);
+            continue;
+        }
+        uint32_t start, cnt, maxc, kstart;
+        const uint32_t t = tile_of_record(walk, r, nxt, tab, start, cnt, maxc, kstart);
+        const uint32_t total = tab.tcount[t], kp = tab.kprefix[(int64_t)t * 64 + lane];
+        if (maxc > (uint32_t)kMaxLevels) {
+            // stored key by key: a particle's place is its rank in its key
+            for (uint32_t j = (uint32_t)wv; j < cnt; j += 4u) {
+                const uint32_t p = src_of[kstart + j];
+                uint32_t rank = 0;
+                for (uint32_t i = 0; i < cnt; ++i) rank += src_of[kstart + i] < p ? 1u : 0u;
+                copy_particle<T, DIM>(src, dst, p, kstart + rank, ids);
+            }
+            continue;
+        }
+        for (uint32_t i = threadIdx.x; i < total; i += 256u) listed[i] = src_of[start + i];
+        if (wv == 0 && lane < kMaxLevels) {
+            lvl_off[lane] = tab.lvl_off[(int64_t)t * kMaxLevels + lane];
+            lvl_mask[lane] = tab.lvl_mask[(int64_t)t * kMaxLevels + lane];
+        }
+        __syncthreads();
+        for (uint32_t j = (uint32_t)wv; j < cnt; j += 4u) {
+            const uint32_t p = listed[kp + j];
+            uint32_t rank = 0;
+            for (uint32_t i = 0; i < cnt; ++i) rank += listed[kp + i] < p ? 1u : 0u;
+            order[lvl_off[rank] + (uint32_t)popc64(lvl_mask[rank] & lanes_below(lane))] = p;
+        }
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < total; i += 256u) copy_particle<T, DIM>(src, dst, order[i], start + i, ids);
+        __syncthreads();
     }
 }
 
 template <typename T, int DIM>
-void launch_bin_scatter_copy(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const TileTables &tab,
-                             const BinScratch &sc, hipStream_t st) {
+void launch_bin_gather(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const TileTables &tab,
+                       const BinScratch &sc, int64_t max_records, hipStream_t st) {
     if (src.n == 0) return;
     Parts<T> s2 = src, d2 = dst;
     if (!src.id || !dst.id) s2.id = d2.id = nullptr;
-    hipLaunchKernelGGL((k_bin_scatter_copy<T, DIM>), dim3((unsigned)((src.n + 255) / 256)), dim3(256), 0, st, s2, d2,
-                       nxt, tab, sc);
+    hipLaunchKernelGGL(k_bin_place, dim3((unsigned)((src.n + 255) / 256)), dim3(256), 0, st, src.n, nxt, tab, sc);
+    hipLaunchKernelGGL((k_bin_gather<T, DIM>), dim3(blocks_for(max_records + (src.n + 255) / 256, 1, 8192)), dim3(256),
+                       0, st, s2, d2, nxt, tab, sc);
 }
 
 // --- instantiations ---------------------------------------------------------------------
 template void launch_bin_records<2>(const GridDims &, const BinLists &, const TileTables &, const BinScratch &,
-                                    int64_t, hipStream_t);
+                                    int64_t, bool, hipStream_t);
 template void launch_bin_records<3>(const GridDims &, const BinLists &, const TileTables &, const BinScratch &,
-                                    int64_t, hipStream_t);
+                                    int64_t, bool, hipStream_t);
 
 #define APIC_BIN_INST(T, DIM)                                                                                    \
     template void launch_bin_records_batch<T, DIM>(const SceneDesc<T> *, const int32_t *, int, int,                   \
@@ -309,25 +351,25 @@ template void launch_bin_records<3>(const GridDims &, const BinLists &, const Ti
                                                    hipStream_t);                                                  \
     template void launch_copy_back_batch<T, DIM>(const SceneDesc<T> *, const int32_t *, int, int, int,            \
                                                  hipStream_t);                                                    \
-    template void launch_bin_scatter_copy<T, DIM>(const Parts<T> &, const Parts<T> &, const BinLists &,           \
-                                                  const TileTables &, const BinScratch &, hipStream_t);           \
-    template void launch_bin_keys_static<T, DIM, 1, false>(const Parts<T> &, const GridDims &, const BinLists &,  \
+    template void launch_bin_gather<T, DIM>(const Parts<T> &, const Parts<T> &, const BinLists &,                 \
+                                            const TileTables &, const BinScratch &, int64_t, hipStream_t);        \
+    template void launch_bin_keys_static<T, DIM, 1, false>(const Parts<T> &, const Parts<T> *, const GridDims &, const BinLists &,  \
                                                            const BinScratch &, uint32_t *, T, hipStream_t);      \
-    template void launch_bin_keys_static<T, DIM, 2, false>(const Parts<T> &, const GridDims &, const BinLists &,  \
+    template void launch_bin_keys_static<T, DIM, 2, false>(const Parts<T> &, const Parts<T> *, const GridDims &, const BinLists &,  \
                                                            const BinScratch &, uint32_t *, T, hipStream_t);      \
-    template void launch_bin_keys_static<T, DIM, 3, false>(const Parts<T> &, const GridDims &, const BinLists &,  \
+    template void launch_bin_keys_static<T, DIM, 3, false>(const Parts<T> &, const Parts<T> *, const GridDims &, const BinLists &,  \
                                                            const BinScratch &, uint32_t *, T, hipStream_t);
 APIC_BIN_INST(float, 2)
 APIC_BIN_INST(float, 3)
 APIC_BIN_INST(double, 2)
 APIC_BIN_INST(double, 3)
-template void launch_bin_keys_static<float, 2, 2, true>(const Parts<float> &, const GridDims &, const BinLists &,
+template void launch_bin_keys_static<float, 2, 2, true>(const Parts<float> &, const Parts<float> *, const GridDims &, const BinLists &,
                                                         const BinScratch &, uint32_t *, float, hipStream_t);
-template void launch_bin_keys_static<float, 2, 3, true>(const Parts<float> &, const GridDims &, const BinLists &,
+template void launch_bin_keys_static<float, 2, 3, true>(const Parts<float> &, const Parts<float> *, const GridDims &, const BinLists &,
                                                         const BinScratch &, uint32_t *, float, hipStream_t);
-template void launch_bin_keys_static<float, 3, 2, true>(const Parts<float> &, const GridDims &, const BinLists &,
+template void launch_bin_keys_static<float, 3, 2, true>(const Parts<float> &, const Parts<float> *, const GridDims &, const BinLists &,
                                                         const BinScratch &, uint32_t *, float, hipStream_t);
-template void launch_bin_keys_static<float, 3, 3, true>(const Parts<float> &, const GridDims &, const BinLists &,
+template void launch_bin_keys_static<float, 3, 3, true>(const Parts<float> &, const Parts<float> *, const GridDims &, const BinLists &,
                                                         const BinScratch &, uint32_t *, float, hipStream_t);
 
 }  // namespace apic

@@ -231,18 +231,6 @@ __device__ __forceinline__ void p2g_movers_body(const Parts<T> &P, const BinList
     const int lane = lane_id();
     int lcoord[3] = {0, 0, 0};
     local_coords<3>(lane, lcoord);
-    if (blk == 0) {
-        // the next grid update raises these bounds of max |vt|, and the
-        // layout the next step builds (the one just read) starts from empty
-        // lists
-        for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
-            cur.rec_count[i] = 0u;
-            cur.nfull[i] = 0u;
-            cur.nsparse[i] = 0u;
-            cur.tot[i] = 0u;
-        }
-        if (threadIdx.x < kCtrCount) cur.ctr[threadIdx.x] = 0u;
-    }
     const TileWalk walk = tile_walk(nxt);
     for (uint32_t r = blk * 4 + (threadIdx.x >> 6); r < walk.nrec; r += nblk * 4) {
         uint32_t start, cnt, maxc, kstart;

@@ -1,4 +1,5 @@
 // Fills, state copies, binary64 particle totals and position conversion.
+#include "apic_bin_device.h"
 #include "apic_kernels.h"
 
 namespace apic {
@@ -30,19 +31,7 @@ template <typename T, int DIM>
 __global__ __launch_bounds__(256) void k_copy_state(Parts<T> src, Parts<T> dst) {
     const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (j >= src.n) return;
-    dst.cell[j] = src.cell[j];
-    dst.m[j] = src.m[j];
-    if (src.id) dst.id[j] = src.id[j];
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        dst.off[a * dst.s + j] = src.off[a * src.s + j];
-        dst.v[a * dst.s + j] = src.v[a * src.s + j];
-    }
-#pragma unroll
-    for (int k = 0; k < DIM * DIM; ++k) {
-        dst.B[k * dst.s + j] = src.B[k * src.s + j];
-        dst.F[k * dst.s + j] = src.F[k * src.s + j];
-    }
+    copy_particle<T, DIM>(src, dst, (uint32_t)j, (uint32_t)j, src.id != nullptr);
 }
 
 template <typename T, int DIM>

@@ -20,19 +20,6 @@
 
 namespace apic {
 
-// The first block empties the lists of the layout that the following transfer
-// to particles builds.
-__device__ __forceinline__ void p2g_clear(const BinLists &nxt, uint32_t blk) {
-    if (blk != 0) return;
-    for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
-        nxt.rec_count[i] = 0u;
-        nxt.nfull[i] = 0u;
-        nxt.nsparse[i] = 0u;
-        nxt.tot[i] = 0u;
-    }
-    if (threadIdx.x < kCtrCount) nxt.ctr[threadIdx.x] = 0u;
-}
-
 // --- 3D, quadratic and cubic: one block of wavefronts per listed tile ---------------------
 // Lane = key in every wavefront.  Levels are taken several at a time: each
 // wavefront forms the terms of every key's particle of one level (stress,
@@ -281,9 +268,8 @@ struct PlaneSums {
 };
 
 template <typename T, int DEG, bool COMP, bool ABS>
-__device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur, const BinLists &nxt,
-                                          const TileTables &tab, const Slabs<T> &slabs, const GridState<T> &g,
-                                          const StepParams<T> &prm_in, uint32_t blk, uint32_t nblk) {
+__device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur, const TileTables &tab,
+                                          const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm_in, uint32_t blk, uint32_t nblk) {
     const StepParams<T> prm = with_step_dt(prm_in);
     using Gm = Geo<3, DEG>;
     using SL = SlabLds<3, DEG>;
@@ -300,7 +286,6 @@ __device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur
     const int comp = wv & 3, c0 = (wv >> 2) * CZ;  // its plane and z-slices
     int lcoord[3] = {0, 0, 0};
     local_coords<3>(lane, lcoord);
-    p2g_clear(nxt, blk);
     const TileWalk walk = tile_walk(cur);
     T *terms = (T *)lds, *mine = terms + wv * LEVEL + lane * L::LANE;
     U *hi = (U *)lds + comp * LP, *lo = (U *)lds + (NC + comp) * LP;
@@ -403,9 +388,8 @@ __device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur
 }
 
 template <typename T, int DIM, int DEG, bool COMP, bool ABS = false>
-__device__ __forceinline__ void p2g_body(const Parts<T> &P, const BinLists &cur, const BinLists &nxt,
-                                         const TileTables &tab, const Slabs<T> &slabs, const GridState<T> &g,
-                                         const StepParams<T> &prm_in, uint32_t blk, uint32_t nblk) {
+__device__ __forceinline__ void p2g_body(const Parts<T> &P, const BinLists &cur, const TileTables &tab,
+                                         const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm_in, uint32_t blk, uint32_t nblk) {
     const StepParams<T> prm = with_step_dt(prm_in);
     using Gm = Geo<DIM, DEG>;
     using SL = SlabLds<DIM, DEG>;
@@ -418,7 +402,6 @@ __device__ __forceinline__ void p2g_body(const Parts<T> &P, const BinLists &cur,
     const int lane = lane_id();
     int lcoord[3] = {0, 0, 0};
     local_coords<DIM>(lane, lcoord);
-    p2g_clear(nxt, blk);
     const TileWalk walk = tile_walk(cur);
     for (uint32_t r = blk * 4 + (threadIdx.x >> 6); r < walk.nrec; r += nblk * 4) {
         uint32_t start, cnt, maxc, kstart;
@@ -475,13 +458,12 @@ __device__ __forceinline__ void p2g_body(const Parts<T> &P, const BinLists &cur,
 }
 
 template <typename T, int DIM, int DEG, bool COMP, bool ABS>
-__device__ __forceinline__ void p2g_any(const Parts<T> &P, const BinLists &cur, const BinLists &nxt,
-                                        const TileTables &tab, const Slabs<T> &slabs, const GridState<T> &g,
-                                        const StepParams<T> &prm, uint32_t blk, uint32_t nblk) {
+__device__ __forceinline__ void p2g_any(const Parts<T> &P, const BinLists &cur, const TileTables &tab,
+                                        const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm, uint32_t blk, uint32_t nblk) {
     if constexpr (p2g_block_per_tile(DIM, DEG))
-        p2g_tile3<T, DEG, COMP, ABS>(P, cur, nxt, tab, slabs, g, prm, blk, nblk);
+        p2g_tile3<T, DEG, COMP, ABS>(P, cur, tab, slabs, g, prm, blk, nblk);
     else
-        p2g_body<T, DIM, DEG, COMP, ABS>(P, cur, nxt, tab, slabs, g, prm, blk, nblk);
+        p2g_body<T, DIM, DEG, COMP, ABS>(P, cur, tab, slabs, g, prm, blk, nblk);
 }
 
 // Threads of a block.
@@ -499,8 +481,8 @@ constexpr int p2g_min_waves() {
 
 template <typename T, int DIM, int DEG, bool COMP, bool ABS>
 __global__ __launch_bounds__(p2g_threads(DIM, DEG, sizeof(T))) __attribute__((amdgpu_waves_per_eu(p2g_min_waves<T, DIM, DEG>()))) void k_p2g(
-    Parts<T> P, BinLists cur, BinLists nxt, TileTables tab, Slabs<T> slabs, GridState<T> g, StepParams<T> prm) {
-    p2g_any<T, DIM, DEG, COMP, ABS>(P, cur, nxt, tab, slabs, g, prm, blockIdx.x, gridDim.x);
+    Parts<T> P, BinLists cur, TileTables tab, Slabs<T> slabs, GridState<T> g, StepParams<T> prm) {
+    p2g_any<T, DIM, DEG, COMP, ABS>(P, cur, tab, slabs, g, prm, blockIdx.x, gridDim.x);
 }
 
 template <typename T, int DIM, int DEG, bool COMP, bool QUEUE>
@@ -516,7 +498,7 @@ __global__ __launch_bounds__(p2g_threads(DIM, DEG, sizeof(T))) __attribute__((am
         const Slabs<T> slabs = scalar_struct(d.slabs);
         const GridState<T> g = scalar_struct(d.g);
         const StepParams<T> prm = scalar_struct(d.prm);
-        p2g_any<T, DIM, DEG, COMP, false>(P, b.cur, b.nxt, tab, slabs, g, prm, b.blk, b.nblk);
+        p2g_any<T, DIM, DEG, COMP, false>(P, b.cur, tab, slabs, g, prm, b.blk, b.nblk);
     });
 }
 
@@ -532,13 +514,13 @@ void launch_p2g_batch(const SceneDesc<T> *descs, const int32_t *start, int n, in
 }
 
 template <typename T, int DIM, int DEG, bool COMP, bool ABS>
-void launch_p2g(const Parts<T> &P, const BinLists &cur, const BinLists &nxt, const TileTables &tab,
-                const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm, int64_t max_records,
+void launch_p2g(const Parts<T> &P, const BinLists &cur, const TileTables &tab, const Slabs<T> &slabs,
+                 const GridState<T> &g, const StepParams<T> &prm, int64_t max_records,
                 hipStream_t st) {
     int64_t blocks = p2g_block_per_tile(DIM, DEG) ? max_records : (max_records + 3) / 4;
     if (blocks < 1) blocks = 1;
     if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL((k_p2g<T, DIM, DEG, COMP, ABS>), dim3((unsigned)blocks), dim3(p2g_threads(DIM, DEG, sizeof(T))), 0, st, P, cur, nxt, tab,
+    hipLaunchKernelGGL((k_p2g<T, DIM, DEG, COMP, ABS>), dim3((unsigned)blocks), dim3(p2g_threads(DIM, DEG, sizeof(T))), 0, st, P, cur, tab,
                        slabs, g, prm);
 }
 
@@ -549,10 +531,10 @@ void launch_p2g(const Parts<T> &P, const BinLists &cur, const BinLists &nxt, con
     template void launch_p2g_batch<T, DIM, DEG, true>(const SceneDesc<T> *, const int32_t *, int, int,                \
                                                       const BatchQueue &, int,                                        \
                                                       hipStream_t);                                               \
-    template void launch_p2g<T, DIM, DEG, false, false>(const Parts<T> &, const BinLists &, const BinLists &,    \
+    template void launch_p2g<T, DIM, DEG, false, false>(const Parts<T> &, const BinLists &,    \
                                                         const TileTables &, const Slabs<T> &, const GridState<T> &, \
                                                         const StepParams<T> &, int64_t, hipStream_t);            \
-    template void launch_p2g<T, DIM, DEG, true, false>(const Parts<T> &, const BinLists &, const BinLists &,     \
+    template void launch_p2g<T, DIM, DEG, true, false>(const Parts<T> &, const BinLists &,     \
                                                        const TileTables &, const Slabs<T> &, const GridState<T> &, \
                                                        const StepParams<T> &, int64_t, hipStream_t);
 APIC_P2G_INST(float, 2, 1)
@@ -571,10 +553,10 @@ APIC_P2G_INST(double, 3, 3)
 // absolute binary32 positions: binary32, quadratic and cubic
 #define APIC_P2G_ABS_INST(DIM, DEG)                                                                                \
     template void launch_p2g<float, DIM, DEG, false, true>(const Parts<float> &, const BinLists &,              \
-                                                           const BinLists &, const TileTables &,                 \
+                                                           const TileTables &,                 \
                                                            const Slabs<float> &, const GridState<float> &,       \
                                                            const StepParams<float> &, int64_t, hipStream_t);     \
-    template void launch_p2g<float, DIM, DEG, true, true>(const Parts<float> &, const BinLists &, const BinLists &, \
+    template void launch_p2g<float, DIM, DEG, true, true>(const Parts<float> &, const BinLists &, \
                                                           const TileTables &, const Slabs<float> &,              \
                                                           const GridState<float> &, const StepParams<float> &,   \
                                                           int64_t, hipStream_t);
