@@ -273,39 +273,41 @@ struct ParticleState {
 };
 template <typename T, int DIM>
 __device__ __forceinline__ void load_particle(const Parts<T> &src, uint32_t p, bool ids, ParticleState<T, DIM> &x) {
-    const int64_t s = src.s;
-    const uint32_t pb = p * (uint32_t)sizeof(T);
-    x.cell = *scalar_plane(src.cell, p * 4u);
     x.id = ids ? *scalar_plane(src.id, p * 4u) : 0;
+    const int64_t step = plane_step<T>(src.s);
+    const uint32_t pb = lane_offset(p * (uint32_t)sizeof(T));
+    x.cell = *scalar_plane(src.cell, sizeof(T) == 4 ? pb : p * 4u);
     x.m = *scalar_plane(src.m, pb);
+    PlaneRun<T> off(src.off, step), v(src.v, step), B(src.B, step), F(src.F, step);
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        x.off[a] = *scalar_plane(src.off + a * s, pb);
-        x.v[a] = *scalar_plane(src.v + a * s, pb);
+        x.off[a] = *off.next(pb);
+        x.v[a] = *v.next(pb);
     }
 #pragma unroll
     for (int k = 0; k < DIM * DIM; ++k) {
-        x.B[k] = *scalar_plane(src.B + k * s, pb);
-        x.F[k] = *scalar_plane(src.F + k * s, pb);
+        x.B[k] = *B.next(pb);
+        x.F[k] = *F.next(pb);
     }
 }
 template <typename T, int DIM>
 __device__ __forceinline__ void store_particle(const Parts<T> &dst, uint32_t q, bool ids,
                                                const ParticleState<T, DIM> &x) {
-    const int64_t s = dst.s;
-    const uint32_t qb = q * (uint32_t)sizeof(T);
-    *scalar_plane(dst.cell, q * 4u) = x.cell;
     if (ids) *scalar_plane(dst.id, q * 4u) = x.id;
+    const int64_t step = plane_step<T>(dst.s);
+    const uint32_t qb = lane_offset(q * (uint32_t)sizeof(T));
+    *scalar_plane(dst.cell, sizeof(T) == 4 ? qb : q * 4u) = x.cell;
     *scalar_plane(dst.m, qb) = x.m;
+    PlaneRun<T> off(dst.off, step), v(dst.v, step), B(dst.B, step), F(dst.F, step);
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        *scalar_plane(dst.off + a * s, qb) = x.off[a];
-        *scalar_plane(dst.v + a * s, qb) = x.v[a];
+        *off.next(qb) = x.off[a];
+        *v.next(qb) = x.v[a];
     }
 #pragma unroll
     for (int k = 0; k < DIM * DIM; ++k) {
-        *scalar_plane(dst.B + k * s, qb) = x.B[k];
-        *scalar_plane(dst.F + k * s, qb) = x.F[k];
+        *B.next(qb) = x.B[k];
+        *F.next(qb) = x.F[k];
     }
 }
 template <typename T, int DIM>
@@ -356,11 +358,11 @@ __device__ __forceinline__ BatchStep<T> batch_step(const SceneDesc<T> *descs, co
     // with it every pointer of its table entry
     const int s = __builtin_amdgcn_readfirstlane(scene_of_block(start, n, item));
     b.d = descs + s;
-    const uint32_t gen0[2] = {b.d->lists[0].gen, b.d->lists[1].gen};
-    b.sp = scalar_struct(step_parity(b.d->cur0, b.d->where0, gen0, k));
-    b.cur = scalar_struct(b.d->lists[b.sp.cur]);
+    const uint32_t gen0[2] = {table_struct(b.d->lists[0].gen), table_struct(b.d->lists[1].gen)};
+    b.sp = scalar_struct(step_parity(table_struct(b.d->cur0), table_struct(b.d->where0), gen0, k));
+    b.cur = table_struct(b.d->lists[b.sp.cur]);
     b.cur.gen = b.sp.gen_cur;
-    b.nxt = scalar_struct(b.d->lists[b.sp.nxt]);
+    b.nxt = table_struct(b.d->lists[b.sp.nxt]);
     b.nxt.gen = b.sp.gen_nxt;
     const uint32_t first = (uint32_t)__builtin_amdgcn_readfirstlane(start[s]);
     b.blk = item - first;

@@ -613,9 +613,7 @@ __device__ __forceinline__ T &plane_at(T *plane, uint32_t boff) {
     return *(T *)((char *)plane + boff);
 }
 
-// A struct read from a scene table, held in scalar registers (the same for the
-// whole block): loaded by vector loads, its pointers would take two vector
-// registers each.
+// A struct that is the same for the whole wavefront, held in scalar registers.
 template <typename S>
 __device__ __forceinline__ S scalar_struct(const S &s) {
     static_assert(sizeof(S) % 4 == 0, "whole words");
@@ -628,12 +626,70 @@ __device__ __forceinline__ S scalar_struct(const S &s) {
     return __builtin_bit_cast(S, x);
 }
 
+template <typename T>
+using GlobalPtr = T __attribute__((address_space(1))) *;
+
+// The pointers of a struct marked as pointers to device memory.  The compiler
+// knows that of a kernel's arguments; a pointer read from a table could point
+// into LDS as well, and its accesses would count as both (a wait for one then
+// waits for the other; key pass of 512 bodies 524 -> 409 us, transfer to
+// particles of 24 bodies 28.8 -> 26.1).
+template <typename... T>
+__device__ __forceinline__ void in_device_memory(T *&...p) {
+    ((p = (T *)(GlobalPtr<T>)(uintptr_t)p), ...);
+}
+__device__ __forceinline__ void in_device_memory(int32_t &) {}
+__device__ __forceinline__ void in_device_memory(uint32_t &) {}
+__device__ __forceinline__ void in_device_memory(GridDims &) {}
+template <typename T>
+__device__ __forceinline__ void in_device_memory(Parts<T> &x) {
+    in_device_memory(x.cell, x.off, x.v, x.B, x.F, x.m, x.id);
+}
+__device__ __forceinline__ void in_device_memory(BinLists &x) {
+    in_device_memory(x.tile_gen, x.slot, x.rec_count, x.nfull, x.nsparse, x.rec_list, x.tot, x.rpre, x.rec_tile, x.bpre,
+                     x.ctr);
+}
+__device__ __forceinline__ void in_device_memory(TileTables &x) {
+    in_device_memory(x.kcount, x.kmov, x.kprefix, x.maxc, x.tcount, x.off, x.lvl_off, x.lvl_mask);
+}
+__device__ __forceinline__ void in_device_memory(BinScratch &x) {
+    in_device_memory(x.key_count, x.scount, x.head, x.pkey, x.prank, x.next, x.pord);
+}
+template <typename T>
+__device__ __forceinline__ void in_device_memory(Slabs<T> &x) {
+    in_device_memory(x.v);
+}
+template <typename T>
+__device__ __forceinline__ void in_device_memory(GridState<T> &x) {
+    in_device_memory(x.vt, x.uref, x.flags, x.vmax, x.cfl);
+}
+template <typename T>
+__device__ __forceinline__ void in_device_memory(StepParams<T> &x) {
+    in_device_memory(x.dt_dev);
+}
+
+// A struct of a scene table at an address that is the same for the whole
+// wavefront: no kernel that reads a table writes it, so its words come by scalar
+// loads straight into scalar registers.
+template <typename S>
+__device__ __forceinline__ S table_struct(const S &s) {
+    static_assert(sizeof(S) % 4 == 0, "whole words");
+    struct Words {
+        int w[sizeof(S) / 4];
+    };
+    const int __attribute__((address_space(4))) *at = (const int __attribute__((address_space(4))) *)(uintptr_t)&s;
+    Words x;
+#pragma unroll
+    for (size_t i = 0; i < sizeof(S) / 4; ++i) x.w[i] = at[i];
+    S v = __builtin_bit_cast(S, x);
+    in_device_memory(v);
+    return v;
+}
+
 // Element at byte offset `boff` of a plane whose base is held in scalar
 // registers: the planes of a particle are then addressed by one 32-bit lane
 // offset beside scalar bases.  (Left alone, the compiler adds the plane stride
 // to a 64-bit lane address, a vector add per plane.)
-template <typename T>
-using GlobalPtr = T __attribute__((address_space(1))) *;
 template <typename T>
 __device__ __forceinline__ GlobalPtr<T> scalar_plane(T *plane, uint32_t boff) {
     GlobalPtr<char> p = (GlobalPtr<char>)plane;
@@ -641,6 +697,43 @@ __device__ __forceinline__ GlobalPtr<T> scalar_plane(T *plane, uint32_t boff) {
     asm("" : "+s"(p));  // (the host compiler knows no scalar register)
 #endif
     return (GlobalPtr<T>)(p + boff);
+}
+
+// The planes of an array one after another, each base found from the last by a
+// scalar add.  The stride is made opaque where the walk starts (plane_step), so
+// that the bases are not all found before the loop around it: the 25 planes a
+// particle is written to do not fit the scalar registers beside those it is read
+// from, and the spilled ones cost a vector instruction per half.
+template <typename T>
+struct PlaneRun {
+    GlobalPtr<char> p;
+    int64_t step;
+    __device__ __forceinline__ PlaneRun(T *first, int64_t step_) : p((GlobalPtr<char>)first), step(step_) {}
+    __device__ __forceinline__ GlobalPtr<T> next(uint32_t boff) {
+#ifdef __HIP_DEVICE_COMPILE__
+        asm("" : "+s"(p));
+#endif
+        const GlobalPtr<T> q = (GlobalPtr<T>)(p + boff);
+        p += step;
+        return q;
+    }
+};
+template <typename T>
+__device__ __forceinline__ int64_t plane_step(int64_t s) {
+    int64_t b = s * (int64_t)sizeof(T);
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+s"(b));
+#endif
+    return b;
+}
+// A lane's byte offset made opaque in the block of code that uses it: its
+// extension to 64 bits is then seen beside each access, which takes the 32-bit
+// register and the scalar base as they are.
+__device__ __forceinline__ uint32_t lane_offset(uint32_t boff) {
+#ifdef __HIP_DEVICE_COMPILE__
+    asm volatile("" : "+v"(boff));
+#endif
+    return boff;
 }
 
 // Exact error of a + b (Knuth two-sum).

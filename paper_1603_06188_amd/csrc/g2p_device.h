@@ -263,12 +263,12 @@ __device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> 
     }
 }
 
-// Occupancy target: binary32 quadratic 3D fits 128 registers (4 waves per
-// SIMD); binary64 cubic 3D runs at 2 (256 registers, a few spilled) rather
-// than the compiler's 1; other variants are left to the compiler.
+// Occupancy target: binary32 3D quadratic and cubic fit 128 registers (4 waves
+// per SIMD), 2D 80 (6); binary64 cubic 3D runs at 2 (256 registers) rather than
+// the compiler's 1; other variants are left to the compiler.
 template <typename T, int DIM, int DEG>
 constexpr int g2p_min_waves() {
-    if (sizeof(T) == 4 && DEG == 2) return 4;
+    if (sizeof(T) == 4 && DEG >= 2) return DIM == 2 ? 6 : 4;
     return (sizeof(T) == 8 && DIM == 3 && DEG == 3) ? 2 : 1;
 }
 
@@ -282,15 +282,16 @@ struct G2PRaw {
 
 template <typename T, int DIM, bool ABS = false>
 __device__ __forceinline__ void g2p_load(const Parts<T> &src, uint32_t p, G2PRaw<T, DIM> &r) {
-    const int64_t ss = src.s;
-    const uint32_t pb = p * (uint32_t)sizeof(T);
-    r.cell = ABS ? 0u : *scalar_plane(src.cell, p * 4u);
-    r.m = *scalar_plane(src.m, pb);
     r.id = src.id ? *scalar_plane(src.id, p * 4u) : 0;
+    const int64_t step = plane_step<T>(src.s);
+    const uint32_t pb = lane_offset(p * (uint32_t)sizeof(T));
+    r.cell = ABS ? 0u : *scalar_plane(src.cell, sizeof(T) == 4 ? pb : p * 4u);
+    r.m = *scalar_plane(src.m, pb);
+    PlaneRun<T> off(src.off, step), F(src.F, step);
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) r.off[a] = *scalar_plane(src.off + a * ss, pb);
+    for (int a = 0; a < DIM; ++a) r.off[a] = *off.next(pb);
 #pragma unroll
-    for (int k = 0; k < DIM * DIM; ++k) r.F[k] = *scalar_plane(src.F + k * ss, pb);
+    for (int k = 0; k < DIM * DIM; ++k) r.F[k] = *F.next(pb);
 }
 
 // Writes a particle's new state at q of dst (position planes: on, or the
@@ -298,20 +299,21 @@ __device__ __forceinline__ void g2p_load(const Parts<T> &src, uint32_t p, G2PRaw
 template <typename T, int DIM>
 __device__ __forceinline__ void g2p_store(const Parts<T> &dst, uint32_t q, uint32_t cell, const G2PRaw<T, DIM> &raw,
                                           bool ids, const T *x, const T *vn, const T *Bs, const T *Fn) {
-    const int64_t ds = dst.s;
-    const uint32_t qb = q * (uint32_t)sizeof(T);
-    *scalar_plane(dst.cell, q * 4u) = cell;
-    *scalar_plane(dst.m, qb) = raw.m;
     if (ids) *scalar_plane(dst.id, q * 4u) = raw.id;
+    const int64_t step = plane_step<T>(dst.s);
+    const uint32_t qb = lane_offset(q * (uint32_t)sizeof(T));
+    *scalar_plane(dst.cell, sizeof(T) == 4 ? qb : q * 4u) = cell;
+    *scalar_plane(dst.m, qb) = raw.m;
+    PlaneRun<T> off(dst.off, step), v(dst.v, step), B(dst.B, step), F(dst.F, step);
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        *scalar_plane(dst.off + a * ds, qb) = x[a];
-        *scalar_plane(dst.v + a * ds, qb) = vn[a];
+        *off.next(qb) = x[a];
+        *v.next(qb) = vn[a];
     }
 #pragma unroll
     for (int k = 0; k < DIM * DIM; ++k) {
-        *scalar_plane(dst.B + k * ds, qb) = Bs[k];
-        *scalar_plane(dst.F + k * ds, qb) = Fn[k];
+        *B.next(qb) = Bs[k];
+        *F.next(qb) = Fn[k];
     }
 }
 
@@ -336,8 +338,8 @@ __device__ __forceinline__ void g2p_update(const G2PRaw<T, DIM> &raw, const T *r
     for (int a = 0; a < DIM; ++a) lk[a] = axis_w_fixed<T, DEG>(ci[a], off[a], wf[a]) - origin[a];
     // One sweep over the support nodes (c, b, a) from LDS: the
     // axis-pair sums Tx_k(a) = sum_{b,c} wy wz vt_k (in the
-    // sequence of pass 1), Ty_k(b) = sum_{a,c} wx wz vt_k and
-    // Tz_k(c) = sum_{a,b} wx wy vt_k, from which
+    // sequence of pass 1), and with the row sums X_k = sum_a wx vt_k
+    // Ty_k(b) = sum_c wz X_k and Tz_k(c) = sum_b wy X_k, from which
     //   v_k = sum_a wx Tx_k(a),
     //   B_k0 = sum_a wx rx Tx_k(a), grad v_k0 = sum_a dwx Tx_k(a),
     // and likewise along y and z.
@@ -357,18 +359,21 @@ __device__ __forceinline__ void g2p_update(const G2PRaw<T, DIM> &raw, const T *r
 #pragma unroll
             for (int b = 0; b < K; ++b) {
                 const T wyz = DIM == 3 ? wf[1][b] * wf[2][c] : wf[1][b];
+                T row[DIM];
 #pragma unroll
                 for (int a = 0; a < K; ++a) {
-                    const T wxz = DIM == 3 ? wf[0][a] * wf[2][c] : wf[0][a];
-                    const T wxy = DIM == 3 ? wf[0][a] * wf[1][b] : T(0);
                     const int idx = R::at(lk[0] + a, lk[1] + b, DIM == 3 ? lk[2] + c : 0);
 #pragma unroll
                     for (int k = 0; k < DIM; ++k) {
                         const T x = reg[k * R::SIZE + idx] - cref[k];
                         Tx[k][a] = fma_t(wyz, x, Tx[k][a]);
-                        Ty[k][b] = fma_t(wxz, x, Ty[k][b]);
-                        if constexpr (DIM == 3) Tz[k][c] = fma_t(wxy, x, Tz[k][c]);
+                        row[k] = a == 0 ? wf[0][0] * x : fma_t(wf[0][a], x, row[k]);
                     }
+                }
+#pragma unroll
+                for (int k = 0; k < DIM; ++k) {
+                    Ty[k][b] = DIM == 3 ? fma_t(wf[2][c], row[k], Ty[k][b]) : row[k];
+                    if constexpr (DIM == 3) Tz[k][c] = fma_t(wf[1][b], row[k], Tz[k][c]);
                 }
                 // the sums are formed here, row by row, not sunk to
                 // their later use (which would keep every LDS value
@@ -432,23 +437,9 @@ __device__ __forceinline__ void g2p_update(const G2PRaw<T, DIM> &raw, const T *r
 template <typename T, int DIM>
 __device__ __forceinline__ void carry_dead(const Parts<T> &src, const Parts<T> &dst, const BinScratch &sc,
                                            uint32_t live, uint32_t live_nxt, uint32_t c) {
-    const int64_t ss = src.s, ds = dst.s;
     const int64_t p = (int64_t)live + (int64_t)c * 64 + lane_id();
     if (p >= src.n) return;
-    const int64_t q = (int64_t)live_nxt + sc.prank[p];
-    dst.cell[q] = src.cell[p];
-    dst.m[q] = src.m[p];
-    if (src.id) dst.id[q] = src.id[p];
-#pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        dst.off[a * ds + q] = src.off[a * ss + p];
-        dst.v[a * ds + q] = src.v[a * ss + p];
-    }
-#pragma unroll
-    for (int k = 0; k < DIM * DIM; ++k) {
-        dst.B[k * ds + q] = src.B[k * ss + p];
-        dst.F[k * ds + q] = src.F[k * ss + p];
-    }
+    copy_particle<T, DIM>(src, dst, (uint32_t)p, live_nxt + sc.prank[p], src.id != nullptr);
 }
 
 // New velocity from the grid velocities staged in LDS (base node at lk

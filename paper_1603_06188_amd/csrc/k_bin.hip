@@ -140,9 +140,9 @@ __global__ __launch_bounds__(256) void k_bin_records_batch(const SceneDesc<T> *d
         const SceneDesc<T> &d = *b.d;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const TileTables tab = scalar_struct(d.tab[b.sp.nxt]);
-        const BinScratch sc = scalar_struct(d.sc);
-        const GridDims dims = scalar_struct(d.g.d);
+        const TileTables tab = table_struct(d.tab[b.sp.nxt]);
+        const BinScratch sc = table_struct(d.sc);
+        const GridDims dims = table_struct(d.g.d);
         records_body<DIM>(b.nxt, tab, sc, dims, b.blk, b.nblk);
     });
 }
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void k_copy_back_batch(const SceneDesc<T> *des
                                                          int k) {
     const BatchStep<T> b = batch_step<T>(descs, start, n, k, blockIdx.x);
     if (b.sp.src != 1) return;
-    const Parts<T> src = scalar_struct(b.d->bufs[1]), dst = scalar_struct(b.d->bufs[0]);
+    const Parts<T> src = table_struct(b.d->bufs[1]), dst = table_struct(b.d->bufs[0]);
     const bool ids = src.id != nullptr && dst.id != nullptr;
     for (int64_t j = (int64_t)b.blk * blockDim.x + threadIdx.x; j < src.n; j += (int64_t)b.nblk * blockDim.x)
         copy_particle<T, DIM>(src, dst, (uint32_t)j, (uint32_t)j, ids);

@@ -255,11 +255,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
         const SceneDesc<T> &d = *b.d;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const Parts<T> P = scalar_struct(d.bufs[b.sp.src]);
-        const TileTables ctab = scalar_struct(d.tab[b.sp.cur]);
-        const GridState<T> g = scalar_struct(d.g);
-        const StepParams<T> prm = scalar_struct(d.prm);
-        const BinScratch sc = scalar_struct(d.sc);
+        const Parts<T> P = table_struct(d.bufs[b.sp.src]);
+        const TileTables ctab = table_struct(d.tab[b.sp.cur]);
+        const GridState<T> g = table_struct(d.g);
+        const StepParams<T> prm = table_struct(d.prm);
+        const BinScratch sc = table_struct(d.sc);
         keys_body<T, DIM, DEG, false, WPT>(P, b.cur, ctab, g, prm, b.nxt, sc, b.blk, b.nblk);
     });
 }
@@ -299,7 +299,11 @@ void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTab
 // stayers.  At full size it runs at the copy rate of its own traffic (2.1M
 // particles: 427 MB in 91 us, 96 before its stayers took their ranks from the
 // marks: no counter, no test of the key, and the tile's level tables from LDS
-// instead of two dependent loads per particle).
+// instead of two dependent loads per particle).  Below it, vector issue counts:
+// with the plane addresses by scalar adds and row sums in the sweep a chunk is
+// 670 vector instructions, not 920 (quadratic), and four wavefronts fit a SIMD
+// in the cubic too (binary32 quadratic 512,000 particles 29.8 -> 26.1 us, cubic
+// 9.0M 724 -> 659, binary64 quadratic 512,000 47 -> 42.5).
 // ADAPT: the step's dt comes from the device and the CFL bound of the
 // written state is folded into g.cfl (adaptive steps); a separate
 // instantiation, so that fixed steps carry none of it.
@@ -424,7 +428,7 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
 }
 
 template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int WPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADAPT ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADAPT && DIM == 3 ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p(
     Parts<T> src, Parts<T> dst, BinLists cur, TileTables ctab, BinLists nxt, TileTables ntab, BinScratch sc,
     GridState<T> g, StepParams<T> prm) {
     g2p_body<T, DIM, DEG, ADAPT, ABS, WPT>(src, dst, cur, ctab, nxt, ntab, sc, g, prm, blockIdx.x, gridDim.x);
@@ -436,14 +440,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
     batch_items<QUEUE>(q, [&](uint32_t it) {
         const BatchStep<T> b = batch_step<T>(descs, start, n, k, it);
         const SceneDesc<T> &d = *b.d;
-        Parts<T> src = scalar_struct(d.bufs[b.sp.src]), dst = scalar_struct(d.bufs[b.sp.src ^ 1]);
+        Parts<T> src = table_struct(d.bufs[b.sp.src]), dst = table_struct(d.bufs[b.sp.src ^ 1]);
         if (!src.id || !dst.id) src.id = dst.id = nullptr;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const TileTables ctab = scalar_struct(d.tab[b.sp.cur]), ntab = scalar_struct(d.tab[b.sp.nxt]);
-        const BinScratch sc = scalar_struct(d.sc);
-        const GridState<T> g = scalar_struct(d.g);
-        const StepParams<T> prm = scalar_struct(d.prm);
+        const TileTables ctab = table_struct(d.tab[b.sp.cur]), ntab = table_struct(d.tab[b.sp.nxt]);
+        const BinScratch sc = table_struct(d.sc);
+        const GridState<T> g = table_struct(d.g);
+        const StepParams<T> prm = table_struct(d.prm);
         g2p_body<T, DIM, DEG, ADAPT, false, WPT>(src, dst, b.cur, ctab, b.nxt, ntab, sc, g, prm, b.blk, b.nblk);
     });
 }

@@ -236,9 +236,9 @@ __global__ __launch_bounds__(256) void k_grid_update_batch(const SceneDesc<T> *d
         const SceneDesc<T> &d = *b.d;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const Slabs<T> slabs = scalar_struct(d.slabs);
-        const GridState<T> g = scalar_struct(d.g);
-        const StepParams<T> prm = scalar_struct(d.prm);
+        const Slabs<T> slabs = table_struct(d.slabs);
+        const GridState<T> g = table_struct(d.g);
+        const StepParams<T> prm = table_struct(d.prm);
         grid_update_body<T, DIM, DEG, COMP>(b.cur, slabs, g, prm, b.blk, b.nblk);
     });
 }

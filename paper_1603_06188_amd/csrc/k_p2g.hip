@@ -37,7 +37,8 @@ namespace apic {
 // binary32 cubic 9.0M 784 -> 594 (0.70 of the time VALU issue), binary32
 // quadratic 238,328 particles 21 -> 17, 4,096 particles 21 -> 12, 2,097,152
 // particles 86 -> 84 (VALU issue 48 us; a tile's chain of loads, barriers and
-// flush rounds is 17 us with four blocks on a CU).
+// flush rounds is 17 us with four blocks on a CU), 80 since the plane addresses
+// are scalar adds.
 // Binary32 adds by 4x4x1 matrix products (rows: slices, columns: a of one b, 16
 // keys a product) need the terms spread over the lanes again: twice the LDS
 // traffic, which then bounds the pass (cubic 670 us, quadratic 100).  The next
@@ -493,11 +494,11 @@ __global__ __launch_bounds__(p2g_threads(DIM, DEG, sizeof(T))) __attribute__((am
         const SceneDesc<T> &d = *b.d;
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
-        const Parts<T> P = scalar_struct(d.bufs[b.sp.src]);
-        const TileTables tab = scalar_struct(d.tab[b.sp.cur]);
-        const Slabs<T> slabs = scalar_struct(d.slabs);
-        const GridState<T> g = scalar_struct(d.g);
-        const StepParams<T> prm = scalar_struct(d.prm);
+        const Parts<T> P = table_struct(d.bufs[b.sp.src]);
+        const TileTables tab = table_struct(d.tab[b.sp.cur]);
+        const Slabs<T> slabs = table_struct(d.slabs);
+        const GridState<T> g = table_struct(d.g);
+        const StepParams<T> prm = table_struct(d.prm);
         p2g_any<T, DIM, DEG, COMP, false>(P, b.cur, tab, slabs, g, prm, b.blk, b.nblk);
     });
 }

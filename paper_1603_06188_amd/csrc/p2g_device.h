@@ -28,19 +28,20 @@ struct P2GRaw {
 // ABS: absolute positions in the offset planes; the cell plane is not read.
 template <typename T, int DIM, bool ABS = false>
 __device__ __forceinline__ void p2g_load(const Parts<T> &P, uint32_t q, P2GRaw<T, DIM> &r) {
-    const int64_t s = P.s;
-    const uint32_t qb = q * (uint32_t)sizeof(T);
-    r.cell = ABS ? 0u : *scalar_plane(P.cell, q * 4u);
+    const int64_t step = plane_step<T>(P.s);
+    const uint32_t qb = lane_offset(q * (uint32_t)sizeof(T));
+    r.cell = ABS ? 0u : *scalar_plane(P.cell, sizeof(T) == 4 ? qb : q * 4u);
     r.m = *scalar_plane(P.m, qb);
+    PlaneRun<T> off(P.off, step), v(P.v, step), B(P.B, step), F(P.F, step);
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        r.off[a] = *scalar_plane(P.off + a * s, qb);
-        r.v[a] = *scalar_plane(P.v + a * s, qb);
+        r.off[a] = *off.next(qb);
+        r.v[a] = *v.next(qb);
     }
 #pragma unroll
     for (int k = 0; k < DIM * DIM; ++k) {
-        r.B[k] = *scalar_plane(P.B + k * s, qb);
-        r.F[k] = *scalar_plane(P.F + k * s, qb);
+        r.B[k] = *B.next(qb);
+        r.F[k] = *F.next(qb);
     }
 }
 
