@@ -586,22 +586,24 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t blk, uint32_t nblk) {
     return c * q + (c < rem ? c : rem) + blk / kXcds;
 }
 
-// A walk over `items` work items, one per wavefront of 256-thread blocks.
+// A walk over `items` work items, one per PER wavefronts of 256-thread blocks.
 // Launches are sized for the capacity, so only the first
-// min(nblk, ceil(items / 4)) blocks take part, renumbered by xcd_block among
-// themselves; `first` is this wave's first item (items when it has none).
+// min(nblk, ceil(items / (4 / PER))) blocks take part, renumbered by xcd_block
+// among themselves; `first` is this wave's first item (items when it has none).
 // When the items outnumber the waves the walk is strided and left in
 // hardware order, which spreads the extra items over all XCDs.
 struct WaveWalk {
     uint32_t first, stride;
 };
+template <int PER>
 __device__ __forceinline__ WaveWalk wave_walk(uint32_t blk, uint32_t nblk, uint32_t items) {
-    const uint32_t need = (uint32_t)(((uint64_t)items + 3u) / 4u);
+    constexpr uint32_t IPB = 4 / PER;  // items of a block
+    const uint32_t need = (uint32_t)(((uint64_t)items + IPB - 1u) / IPB);
     const uint32_t nb = need < nblk ? need : nblk;
     WaveWalk w;
-    w.stride = nb * 4u;
+    w.stride = nb * IPB;
     const uint32_t lb = need <= nblk ? xcd_block(blk, nb) : blk;
-    w.first = blk < nb ? lb * 4u + (uint32_t)(threadIdx.x >> 6) : items;
+    w.first = blk < nb ? lb * IPB + (uint32_t)(threadIdx.x >> 6) / (uint32_t)PER : items;
     return w;
 }
 

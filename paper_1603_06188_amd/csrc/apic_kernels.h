@@ -31,6 +31,26 @@ constexpr int g2p_waves(int64_t n) {
     return g2p_waves_choice<T, DIM, DEG>() && n >= ((int64_t)1 << 20) ? 1 : 4;
 }
 
+//   grid update (a tile at an edge of the body updates up to 2^dim node tiles,
+//   one after another by one wavefront): 227k binary32 quadratic 6.2 with four
+//   against 11.7, 2.1M 20.1 against 21.2, 2D 12k 3.5 against 4.5; cubic 9.0M 81
+//   against 62, 19M in 512 bodies 296 against 231, 2D 1.19M 7.7 against 6.8.
+template <int DIM>
+constexpr int grid_waves(int64_t n) {
+    return n >= ((int64_t)1 << (DIM == 3 ? 22 : 20)) ? 1 : 4;
+}
+// Runs f with the wavefronts per tile as a compile-time constant.
+template <bool CHOICE, typename F>
+inline void with_tile_waves(int waves, F &&f) {
+    if constexpr (CHOICE) {
+        if (waves == 1) {
+            f(std::integral_constant<int, 1>{});
+            return;
+        }
+    }
+    f(std::integral_constant<int, 4>{});
+}
+
 // The transfer to grid takes a block per tile (else a wavefront).
 constexpr bool p2g_block_per_tile(int dim, int deg) { return dim == 3 && deg >= 2; }
 
@@ -78,7 +98,7 @@ void launch_p2g(const Parts<T> &P, const BinLists &cur, const TileTables &tab,
 
 template <typename T, int DIM, int DEG, bool COMP>
 void launch_grid_update(const BinLists &cur, const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm,
-                        int64_t max_records, hipStream_t st);
+                        int64_t n, int64_t max_records, hipStream_t st);
 
 // New keys of the particles of layout `cur` after G2P (first pass of
 // apic_g2p): stayer counts per key, movers' keys and ranks, dead ranks.
@@ -118,7 +138,7 @@ void launch_p2g_batch(const SceneDesc<T> *descs, const int32_t *start, int n, in
                       hipStream_t st);
 template <typename T, int DIM, int DEG, bool COMP>
 void launch_grid_update_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
-                              int blocks, hipStream_t st);
+                              int blocks, int waves, hipStream_t st);
 template <typename T, int DIM, int DEG>
 void launch_bin_keys_moved_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
                                  int blocks, int waves, hipStream_t st);

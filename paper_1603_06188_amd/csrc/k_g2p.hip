@@ -23,18 +23,6 @@
 
 namespace apic {
 
-// Runs f with the wavefronts per tile as a compile-time constant.
-template <bool CHOICE, typename F>
-static void with_tile_waves(int waves, F &&f) {
-    if constexpr (CHOICE) {
-        if (waves == 1) {
-            f(std::integral_constant<int, 1>{});
-            return;
-        }
-    }
-    f(std::integral_constant<int, 4>{});
-}
-
 // Waves per SIMD asked for: a wavefront per tile holds the offsets of eight
 // chunks (binary32: three).
 template <typename T, int WPT>
