@@ -240,8 +240,8 @@ struct MidSorted {
     double *F;              // dim*dim planes
     double *m;
     double *mv;             // dim planes: m v
-    double *M;              // dim*dim + 1 planes: m (k / dx) B for the transfer to grid, then F_hat^{-T} and
-                            // mu - lambda ln J of the last force pass
+    double *M;              // dim*dim + 1 planes: m (k / dx) B for the transfer to grid, then of the last
+                            // force pass F_hat^{-T} (3D: F_hat^{-T} F^T) and mu - lambda ln J
     uint32_t *id;           // particle ids (the caller's, else the particle's index); null: not kept
     int64_t n;              // plane stride
     double dx;

@@ -29,6 +29,7 @@
 // in the solve's order (ids move with them), those outside the grid last.
 #include <hip/hip_ext.h>
 
+#include "apic_bin_device.h"
 #include "apic_kernels.h"
 
 namespace apic {
@@ -100,17 +101,17 @@ __device__ __forceinline__ void local_coords(int l, int *lc) {
 // Sum over the block's threads of a[b * K + k] for b < n (each thread its
 // stride of b in order, then a fixed tree); every thread returns the total.
 __device__ __forceinline__ double block_total(const double *a, int64_t n, int K, int k) {
-    __shared__ double red[kMidBlock];
+    __shared__ double red[kMidBlock / 64];
     double s = 0.0;
     for (int64_t b = threadIdx.x; b < n; b += kMidBlock) s += a[b * K + k];
-    red[threadIdx.x] = s;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
     __syncthreads();
-    for (int w = kMidBlock / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-        __syncthreads();
-    }
-    const double t = red[0];
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
     __syncthreads();
+    double t = red[0];
+#pragma unroll
+    for (int w = 1; w < kMidBlock / 64; ++w) t += red[w];
     return t;
 }
 
@@ -274,6 +275,12 @@ __device__ __forceinline__ void mat_mul(const double *A, const double *B, double
         }
 }
 
+// Index of (r, c) in the upper triangle of a symmetric matrix.
+template <int DIM>
+__host__ __device__ constexpr int sym(int r, int c) {
+    return r <= c ? r * DIM - r * (r + 1) / 2 + c : c * DIM - c * (c + 1) / 2 + r;
+}
+
 // det A and A^{-T}.
 template <int DIM>
 __device__ __forceinline__ double det_inv_t(const double *A, double *IT) {
@@ -352,31 +359,36 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_fill_u32(uint32_t *a, int64_t
     if (i < n) a[i] = 0u;
 }
 
-// Key = slot of the particle's base node; particles whose support leaves the
-// grid take no part in the step and get the key `nodes`, after every node.
+// Key = slot of the particle's base node, and the particle's rank in the order its
+// key's counter ran; particles whose support leaves the grid take no part in the
+// step and get the key `nodes`, after every node.
 template <int DIM, int DEG>
-__global__ __launch_bounds__(kMidBlock) void k_mid_keys(Parts<double> P, MidGrid g, uint32_t *key, uint32_t *count,
-                                                        uint32_t *flags) {
+__global__ __launch_bounds__(kMidBlock) void k_mid_keys(Parts<double> P, MidGrid g, uint32_t *key, uint32_t *rank,
+                                                        uint32_t *count, uint32_t *flags) {
     const int64_t p = gtid();
     if (p >= P.n) return;
     Axis<double, DEG> ax[DIM];
     if (!particle_axes<DIM, DEG>(P, p, g, ax)) {
         key[p] = (uint32_t)g.nodes;  // the bucket after every node: particles that take no part
-        atomicAdd(&count[g.nodes], 1u);
+        rank[p] = atomicAdd(&count[g.nodes], 1u);
         atomicOr(flags, (uint32_t)APIC_FLAG_OUT_OF_DOMAIN);
         return;
     }
     const int64_t k = node_slot<DIM>(g, ax[0].base, ax[1].base, DIM == 3 ? ax[DIM - 1].base : 0);
     key[p] = (uint32_t)k;
-    atomicAdd(&count[k], 1u);
+    rank[p] = atomicAdd(&count[k], 1u);
 }
 
 // Exclusive prefix sum of count[0, n) into start[0, n], start[n] = total:
 // blocks of 1024 entries (scan1), the block totals in one block (scan2),
-// then the block offsets added (scan3).
+// then the block offsets added (scan3).  blockIdx.y: several arrays, one after
+// another.
 __global__ __launch_bounds__(kMidBlock) void k_mid_scan1(const uint32_t *count, int64_t n, uint32_t *start,
                                                          uint32_t *bsum) {
     __shared__ uint32_t sh[kMidBlock];
+    count += (int64_t)blockIdx.y * n;
+    start += (int64_t)blockIdx.y * (n + 1);
+    bsum += blockIdx.y * gridDim.x;
     const int tid = threadIdx.x;
     const int64_t base = (int64_t)blockIdx.x * 1024 + tid * 4;
     uint32_t v[4], tsum = 0;
@@ -405,6 +417,8 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_scan1(const uint32_t *count, 
 __global__ __launch_bounds__(kMidBlock) void k_mid_scan2(uint32_t *bsum, int64_t nb, uint32_t *start, int64_t n) {
     __shared__ uint32_t sh[kMidBlock];
     __shared__ uint32_t carry;
+    start += (int64_t)blockIdx.y * (n + 1);
+    bsum += (int64_t)blockIdx.y * nb;
     const int tid = threadIdx.x;
     if (tid == 0) carry = 0u;
     __syncthreads();
@@ -429,18 +443,19 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_scan2(uint32_t *bsum, int64_t
 }
 
 __global__ __launch_bounds__(kMidBlock) void k_mid_scan3(uint32_t *start, int64_t n, const uint32_t *bsum) {
+    start += (int64_t)blockIdx.y * (n + 1);
+    bsum += (int64_t)blockIdx.y * ((n + 1023) / 1024);
     const int64_t i = gtid();
     if (i < n) start[i] += bsum[i >> 10];
 }
 
 // perm[position] = particle; the positions of one key in any order (the
 // level-major copy orders them).
-__global__ __launch_bounds__(kMidBlock) void k_mid_place(int64_t n, const uint32_t *key, const uint32_t *start,
-                                                         uint32_t *cursor, uint32_t *perm) {
+__global__ __launch_bounds__(kMidBlock) void k_mid_place(int64_t n, const uint32_t *key, const uint32_t *rank,
+                                                         const uint32_t *start, uint32_t *perm) {
     const int64_t p = gtid();
     if (p >= n) return;
-    const uint32_t k = key[p];
-    perm[start[k] + atomicAdd(&cursor[k], 1u)] = (uint32_t)p;
+    perm[start[key[p]] + rank[p]] = (uint32_t)p;
 }
 
 // Tile lists: klist = tiles holding particles, nlist = tiles t with a tile
@@ -657,15 +672,8 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_sort_dead(Parts<double> P, Mi
 //               -V (dP/dF(F_hat) : dF) F^T grad w / dx                       (Sec. 4.2)
 enum { TILE_P2G = 0, TILE_FORCE = 1, TILE_APPLY = 2 };
 
-// Waves per SIMD the register allocation of a tile kernel aims at (1: no
-// target).
 template <int DIM, int DEG, int MODE>
-constexpr int tile_waves() {
-    return MODE == TILE_APPLY && DIM == 3 && DEG == 2 ? 3 : 1;
-}
-
-template <int DIM, int DEG, int MODE>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(tile_waves<DIM, DEG, MODE>()))) void k_mid_tile(
+__global__ __launch_bounds__(64) void k_mid_tile(
     MidSorted S, MidGrid g, MidTiles tl, MidMaterial mat, const double *va, const double *vb, double ca, double cb,
     double *epart, uint32_t *flags, const MidCg *cg) {
     constexpr int R = region_nodes<DIM, DEG>(), RE = region_edge<DIM, DEG>(), E = tile_edge<DIM>();
@@ -858,6 +866,257 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(tile_waves<D
     }
 }
 
+// The same elastic terms in 3D: a block of four wavefronts per key tile that deal
+// its levels, each adding into an LDS region of its own.  A wavefront's first
+// particles are loaded before the region is staged, and its next ones when the
+// matrix of the current ones is formed, so that they arrive while its terms are
+// added.  Neither memory nor a unit bounds it alone: 884,736 particles take 50.7 us
+// (54.2 with one wavefront per tile that loaded each level when it came to it), of
+// which binary64 issue is 23, LDS 25 and the 166 MB read 33 at the copy rate.  The
+// support's sums in registers, a plane per wavefront, with the matrices handed over
+// in LDS: 59 us (the weights again in each); two or three wavefronts per SIMD, one
+// or two per tile: 51.6 to 53.7; four per SIMD spill: 63.
+constexpr int kMidParts = 4;
+
+// What the elastic terms read of a particle.
+template <bool DIFF>
+struct MidRaw {
+    double off[3], F[9], W[9], cT, m;
+};
+template <bool DIFF>
+__device__ __forceinline__ void mid_load(const MidSorted &S, int64_t first, uint32_t place, MidRaw<DIFF> &r) {
+    const int64_t step = plane_step<double>(S.n);
+    const uint32_t pb = lane_offset(place * 8u);
+    PlaneRun<double> offs(S.off + first, step), Fs(S.F + first, step), Ms(S.M + first, step);
+#pragma unroll
+    for (int a = 0; a < 3; ++a) r.off[a] = *offs.next(pb);
+#pragma unroll
+    for (int k = 0; k < 9; ++k) r.F[k] = *Fs.next(pb);
+    if constexpr (DIFF) {
+#pragma unroll
+        for (int k = 0; k < 9; ++k) r.W[k] = *Ms.next(pb);
+        r.cT = *Ms.next(pb);
+    }
+    r.m = *scalar_plane(S.m + first, pb);
+}
+
+template <int DEG, int MODE>
+__global__ __launch_bounds__(64 * kMidParts) __attribute__((amdgpu_waves_per_eu(3))) void k_mid_tile3(
+    MidSorted S, MidGrid g, MidTiles tl, MidMaterial mat, const double *va, const double *vb, double ca, double cb,
+    double *epart, uint32_t *flags, const MidCg *cg) {
+    constexpr int R = region_nodes<3, DEG>(), RE = region_edge<3, DEG>(), WPT = kMidParts, NT = 64 * WPT;
+    constexpr int D2 = 9;
+    __shared__ double stage[3 * R];
+    __shared__ double sums[WPT][3 * R];  // each wavefront's own
+    __shared__ double esum[WPT];
+    if constexpr (MODE == TILE_APPLY) {
+        if (cg->done) return;
+    }
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t part = (uint32_t)__builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t t = tl.klist[blockIdx.x];
+    // the lane's key: its particles, and the base node's place in the region
+    const int key = lane_key<3, DEG>(lane);
+    const uint32_t k0 = S.start[t * 64 + key], cnt = S.start[t * 64 + key + 1] - k0;
+    int64_t first = (int64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)S.start[t * 64]);
+    const uint32_t maxc = (uint32_t)__builtin_amdgcn_readlane((int)wave_max_last(cnt), 63);
+    const uint64_t below = (1ull << lane) - 1ull;
+    uint32_t lv = 0;  // level that starts at position `first`
+    MidRaw<MODE == TILE_APPLY> raw;
+    auto load_level = [&](uint32_t q) {
+        for (; lv < q; ++lv) first += popc64(ballot(cnt > lv));
+        const uint64_t bal = ballot(cnt > q);
+        if (cnt > q) mid_load(S, first, (uint32_t)popc64(bal & below), raw);
+    };
+    load_level(part);
+    int tc[3];
+    tile_coords<3>(g, t, tc);
+    for (int k = tid; k < R; k += NT) {
+        const int x = 4 * tc[0] + k % RE, y = 4 * tc[1] + (k / RE) % RE, z = 4 * tc[2] + k / (RE * RE);
+        const bool in = x < g.N[0] && y < g.N[1] && z < g.N[2];
+        const int64_t i = in ? node_slot<3>(g, x, y, z) : 0;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            double u = 0.0;
+            if (in) {
+                u = ca * va[a * g.nodes + i];
+                if (vb) u += cb * vb[a * g.nodes + i];
+            }
+            stage[a * R + k] = u;
+        }
+    }
+    for (int k = tid; k < WPT * 3 * R; k += NT) (&sums[0][0])[k] = 0.0;
+    int kc[3];
+    local_coords<3>(key, kc);
+    const int at0 = kc[0] + RE * (kc[1] + RE * kc[2]);
+    const double inv_dx = wave_uniform(1.0 / g.dx), inv_rho0 = wave_uniform(1.0 / mat.rho0);
+    double energy = 0.0;
+    double *acc = sums[part];
+    __syncthreads();
+    for (uint32_t q = part; q < maxc; q += WPT) {
+        Axis<double, DEG> ax[3];
+        double M[D2];
+        bool ok = cnt > q;
+        const uint64_t ballot_at = ballot(ok);
+        if (ok) {
+            // F, and for the differential F F^T (its upper triangle), W = F_hat^{-T}
+            // F^T and mu - lambda ln J of the force pass (an inverted F_hat was
+            // rejected by the line search: its element is not kept)
+            double G[D2], F[D2], H[6], W[D2];
+            const double cT = raw.cT, V = raw.m * inv_rho0;
+#pragma unroll
+            for (int a = 0; a < 3; ++a) axis_weights<double, DEG>(0, raw.off[a], ax[a]);
+#pragma unroll
+            for (int k = 0; k < D2; ++k) {
+                F[k] = raw.F[k];
+                W[k] = raw.W[k];
+                G[k] = 0.0;
+            }
+            if constexpr (MODE == TILE_APPLY) {
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int c = r; c < 3; ++c) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) sum += F[r * 3 + k] * F[c * 3 + k];
+                        H[sym<3>(r, c)] = sum;
+                    }
+            }
+            // G = sum_i u_i grad w^T over the staged node values (cell units),
+            // per row: the x sums of w u and dw u, then the row's y, z factors
+            for_rows<3, DEG>(ax, [&](int j, int k, double c0, double c1, double c2, double, double) {
+                const int r0 = at0 + RE * (j + RE * k);
+                double sw[3], sdw[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    sw[a] = 0.0;
+                    sdw[a] = 0.0;
+                }
+#pragma unroll
+                for (int i = 0; i <= DEG; ++i)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) {
+                        const double u = stage[a * R + r0 + i];
+                        sw[a] += ax[0].w[i] * u;
+                        sdw[a] += ax[0].dw[i] * u;
+                    }
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    G[a * 3] += sdw[a] * c0;
+                    G[a * 3 + 1] += sw[a] * c1;
+                    G[a * 3 + 2] += sw[a] * c2;
+                }
+            });
+            // M = -V P F^T / dx; node i receives M grad w = dw_x (M e_x) c0 + w_x (M_y c1 + M_z c2)
+            const double cm = -V * inv_dx;
+            if constexpr (MODE == TILE_FORCE) {
+                double Fh[D2], IT[D2], Pk[D2];
+#pragma unroll
+                for (int k = 0; k < D2; ++k) G[k] *= inv_dx;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) G[a * 3 + a] += 1.0;
+                mat_mul<3>(G, F, Fh);
+                const double J = det_inv_t<3>(Fh, IT);
+                ok = J > 0.0;
+                if (!ok) {
+                    atomicOr(flags, (uint32_t)APIC_FLAG_INVERTED);
+                    energy = INFINITY;
+                } else {
+                    const int64_t step = plane_step<double>(S.n);
+                    const uint32_t ob = lane_offset((uint32_t)popc64(ballot_at & below) * 8u);
+                    PlaneRun<double> Ms(S.M + first, step);
+                    const double lnJ = log(J);
+                    double tr = 0.0;
+#pragma unroll
+                    for (int k = 0; k < D2; ++k) {
+                        tr += Fh[k] * Fh[k];
+                        Pk[k] = mat.mu * (Fh[k] - IT[k]) + mat.lambda * lnJ * IT[k];
+                    }
+                    energy += V * (0.5 * mat.mu * (tr - 3) - mat.mu * lnJ + 0.5 * mat.lambda * lnJ * lnJ);
+                    // kept for the differential: W and mu - lambda ln J
+#pragma unroll
+                    for (int r = 0; r < 3; ++r)
+#pragma unroll
+                        for (int c = 0; c < 3; ++c) {
+                            double sum = 0.0, w = 0.0;
+#pragma unroll
+                            for (int k = 0; k < 3; ++k) {
+                                sum += Pk[r * 3 + k] * F[c * 3 + k];
+                                w += IT[r * 3 + k] * F[c * 3 + k];
+                            }
+                            M[r * 3 + c] = cm * sum;
+                            *Ms.next(ob) = w;
+                        }
+                    *Ms.next(ob) = mat.mu - mat.lambda * lnJ;
+                }
+            } else {
+                // with A = sum_i p_i grad w^T:  dF = A F,  F_hat^{-T} dF^T F_hat^{-T} F^T = W A^T W,
+                // tr(F_hat^{-1} dF) = W : A, so that
+                // dP F^T = mu A F F^T + (mu - lambda ln J) W A^T W + lambda (W : A) W
+                double T1[D2], tr = 0.0;
+#pragma unroll
+                for (int k = 0; k < D2; ++k) tr += W[k] * G[k];
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        double sum = 0.0;
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) sum += G[k * 3 + r] * W[k * 3 + c];
+                        T1[r * 3 + c] = cT * sum;
+                    }
+#pragma unroll
+                for (int r = 0; r < 3; ++r)
+#pragma unroll
+                    for (int c = 0; c < 3; ++c) {
+                        double ah = 0.0, sum = mat.lambda * tr * W[r * 3 + c];
+#pragma unroll
+                        for (int k = 0; k < 3; ++k) {
+                            ah += G[r * 3 + k] * H[sym<3>(k, c)];
+                            sum += W[r * 3 + k] * T1[k * 3 + c];
+                        }
+                        M[r * 3 + c] = cm * inv_dx * (mat.mu * ah + sum);
+                    }
+            }
+        }
+        if (q + WPT < maxc) load_level(q + WPT);
+        if (ok) {
+            for_rows<3, DEG>(ax, [&](int j, int k, double c0, double c1, double c2, double, double) {
+                const int r0 = at0 + RE * (j + RE * k);
+                double A[3], Bv[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    A[a] = M[a * 3] * c0;
+                    Bv[a] = M[a * 3 + 1] * c1 + M[a * 3 + 2] * c2;
+                }
+#pragma unroll
+                for (int i = 0; i <= DEG; ++i)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a) atomicAdd(&acc[a * R + r0 + i], ax[0].dw[i] * A[a] + ax[0].w[i] * Bv[a]);
+            });
+        }
+    }
+    if constexpr (MODE == TILE_FORCE) {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) energy += __shfl_xor(energy, o, 64);
+        if (lane == 0) esum[part] = energy;
+    }
+    __syncthreads();
+    double *sl = tl.slab + (int64_t)blockIdx.x * 3 * R;
+    for (int k = tid; k < 3 * R; k += NT) {
+        double sum = sums[0][k];
+#pragma unroll
+        for (int w = 1; w < WPT; ++w) sum += sums[w][k];
+        sl[k] = sum;
+    }
+    if (MODE == TILE_FORCE && tid == 0) {
+        double sum = esum[0];
+        for (int w = 1; w < WPT; ++w) sum += esum[w];
+        epart[blockIdx.x] = sum;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Node passes, one wavefront per listed node tile
 // ---------------------------------------------------------------------------
@@ -881,14 +1140,17 @@ __device__ __forceinline__ bool node_at(const MidGrid &g, const MidTiles &tl, No
 }
 
 // Sum of the COUT region sums that cover the node, over the key tiles
-// tc - d, d in {0, 1}^dim, in that order.
+// tc - d, d in {0, 1}^dim, in that order.  The records of all of them are looked
+// up first, then the values of all are loaded, then they are added: two round
+// trips, where one key tile after another took two each.
 template <int DIM, int DEG, int COUT>
 __device__ __forceinline__ void slab_sum(const MidGrid &g, const MidTiles &tl, const NodeAt &n, double *out) {
     constexpr int R = region_nodes<DIM, DEG>(), RE = region_edge<DIM, DEG>(), E = tile_edge<DIM>();
+    constexpr int ND = 1 << DIM;
+    int32_t rec[ND];
+    int64_t at[ND];
 #pragma unroll
-    for (int c = 0; c < COUT; ++c) out[c] = 0.0;
-#pragma unroll
-    for (int d = 0; d < (1 << DIM); ++d) {
+    for (int d = 0; d < ND; ++d) {
         const int dd[3] = {d & 1, (d >> 1) & 1, DIM == 3 ? d >> 2 : 0};
         int T[3], rc[3];
         bool ok = true;
@@ -898,14 +1160,25 @@ __device__ __forceinline__ void slab_sum(const MidGrid &g, const MidTiles &tl, c
             rc[a] = n.lc[a] + E * dd[a];
             ok = ok && T[a] >= 0 && (a >= DIM || rc[a] < RE);
         }
-        if (!ok) continue;
-        const int32_t s = tl.slot[tile_index<DIM>(g, T)];
-        if (s < 0) continue;
-        const int ri = DIM == 3 ? rc[0] + RE * (rc[1] + RE * rc[2]) : rc[0] + RE * rc[1];
-        const double *sl = tl.slab + (int64_t)s * COUT * R + ri;
-#pragma unroll
-        for (int c = 0; c < COUT; ++c) out[c] += sl[c * R];
+        const int32_t s = tl.slot[ok ? tile_index<DIM>(g, T) : 0];
+        rec[d] = ok ? s : -1;
+        at[d] = DIM == 3 ? rc[0] + RE * (rc[1] + RE * rc[2]) : rc[0] + RE * rc[1];
     }
+    double v[ND][COUT];
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+        if (rec[d] >= 0) {
+            const double *sl = tl.slab + (int64_t)rec[d] * COUT * R + at[d];
+#pragma unroll
+            for (int c = 0; c < COUT; ++c) v[d][c] = sl[c * R];
+        }
+#pragma unroll
+    for (int c = 0; c < COUT; ++c) out[c] = 0.0;
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+        if (rec[d] >= 0)
+#pragma unroll
+            for (int c = 0; c < COUT; ++c) out[c] += v[d][c];
 }
 
 // mf_i = m_i and v_i = (m v)_i / m_i on free nodes (mass, outside the sticky
@@ -970,21 +1243,23 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_node_apply(MidGrid g, MidTile
     double acc[1] = {0.0};
     NodeAt n;
     if (node_at<DIM>(g, tl, n)) {
-        double df[DIM];
+        const double m = mf[n.i];
+        double df[DIM], p[DIM];
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) p[a] = pv[a * g.nodes + n.i];
         if constexpr (ELASTIC)
             slab_sum<DIM, DEG, DIM>(g, tl, n, df);
         else
 #pragma unroll
             for (int a = 0; a < DIM; ++a) df[a] = 0.0;
-        const double m = mf[n.i];
         const double cc = 0.25 * dt * dt;
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
             const int64_t k = a * g.nodes + n.i;
             double sa = 0.0;
             if (m > 0.0) {
-                sa = pv[k] - cc * df[a] / m;
-                acc[0] += m * pv[k] * sa;
+                sa = p[a] - cc * df[a] / m;
+                acc[0] += m * p[a] * sa;
             }
             s[k] = sa;
         }
@@ -1026,9 +1301,22 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_cg_step(MidGrid g, MidTiles t
                                                            double *rc, const double *part_ps, int64_t nps,
                                                            double *part, MidCg *cg, int it) {
     if (cg->done) return;
-    const double ps = block_total(part_ps, nps, 1, 0);
+    // the node's values are loaded while the partials are summed
     NodeAt n;
     const bool have = node_at<DIM>(g, tl, n);
+    double p[DIM], sa[DIM], da[DIM], ra[DIM], m = 0.0;
+    if (have) {
+        m = mf[n.i];
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            const int64_t k = a * g.nodes + n.i;
+            p[a] = pv[k];
+            sa[a] = s[k];
+            da[a] = delta[k];
+            ra[a] = rc[k];
+        }
+    }
+    const double ps = block_total(part_ps, nps, 1, 0);
     const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
     if (!(ps > 0.0)) {
         if (it == 0 && have)
@@ -1043,14 +1331,13 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_cg_step(MidGrid g, MidTiles t
     const double alpha = cg->gamma[it & 1] / ps;
     double acc[1] = {0.0};
     if (have) {
-        const double m = mf[n.i];
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
             const int64_t k = a * g.nodes + n.i;
-            delta[k] += alpha * pv[k];
-            const double ra = rc[k] - alpha * s[k];
-            rc[k] = ra;
-            acc[0] += m * ra * ra;
+            delta[k] = da[a] + alpha * p[a];
+            ra[a] -= alpha * sa[a];
+            rc[k] = ra[a];
+            acc[0] += m * ra[a] * ra[a];
         }
     }
     block_partials<1>(acc, part);
@@ -1073,6 +1360,16 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_cg_dir(MidGrid g, MidTiles tl
         if (lead) cg->done = 1;
         return;
     }
+    NodeAt n;
+    const bool have = node_at<DIM>(g, tl, n);
+    double ra[DIM], p[DIM];
+    if (have) {
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            ra[a] = rc[a * g.nodes + n.i];
+            p[a] = pv[a * g.nodes + n.i];
+        }
+    }
     const double kappa = block_total(part, nblk, 1, 0);
     const double beta = kappa / cg->gamma[it & 1];
     const bool stop = kappa <= cg->tol2 * cg->gamma0 || (uint32_t)it + 1u >= cg->max_iters;
@@ -1080,14 +1377,9 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_cg_dir(MidGrid g, MidTiles tl
         cg->gamma[(it + 1) & 1] = kappa;
         if (stop) cg->done = 1;
     }
-    if (stop) return;
-    NodeAt n;
-    if (!node_at<DIM>(g, tl, n)) return;
+    if (stop || !have) return;
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        const int64_t k = a * g.nodes + n.i;
-        pv[k] = rc[k] + beta * pv[k];
-    }
+    for (int a = 0; a < DIM; ++a) pv[a * g.nodes + n.i] = ra[a] + beta * p[a];
 }
 
 // Scalars from the block partials of the node pass before it (one block; the
@@ -1354,26 +1646,22 @@ void launch_mid_sort(const Parts<double> &P, const MidGrid &g, const MidSorted &
     // buckets: one per node slot, then one for the particles that take no part
     const int64_t nbk = g.nodes + 1;
     k_mid_fill_u32<<<blocks_for(nbk), kMidBlock, 0, st>>>(count, nbk);
-    k_mid_fill_u32<<<blocks_for(nbk), kMidBlock, 0, st>>>(cursor, nbk);
-    if (P.n > 0) k_mid_keys<DIM, DEG><<<blocks_for(P.n), kMidBlock, 0, st>>>(P, g, key, count, flags);
+    uint32_t *rank = S.cell;  // written with the particles' cells only after the placement
+    if (P.n > 0) k_mid_keys<DIM, DEG><<<blocks_for(P.n), kMidBlock, 0, st>>>(P, g, key, rank, count, flags);
     const int64_t nb = mid_scan_blocks(nbk);
     uint32_t *start = const_cast<uint32_t *>(S.start);
     k_mid_scan1<<<(unsigned)nb, kMidBlock, 0, st>>>(count, nbk, start, bsum);
     k_mid_scan2<<<1, kMidBlock, 0, st>>>(bsum, nb, start, nbk);
     k_mid_scan3<<<blocks_for(nbk), kMidBlock, 0, st>>>(start, nbk, bsum);
-    if (P.n > 0) k_mid_place<<<blocks_for(P.n), kMidBlock, 0, st>>>(P.n, key, S.start, cursor, S.perm);
-    // count and cursor are free again: tile flags and their prefix sums
+    if (P.n > 0) k_mid_place<<<blocks_for(P.n), kMidBlock, 0, st>>>(P.n, key, rank, S.start, S.perm);
+    // count is free again (cursor is not used before): tile flags and their prefix sums
     uint32_t *kf = count, *nf = count + g.tiles, *hf = count + 2 * g.tiles;
     uint32_t *ks = cursor, *ns = cursor + g.tiles + 1, *hs = cursor + 2 * (g.tiles + 1);
     const int64_t tb = mid_scan_blocks(g.tiles);
     k_mid_tile_flags<DIM><<<blocks_for(g.tiles), kMidBlock, 0, st>>>(g, S.start, kf, nf, hf);
-    for (int q = 0; q < 3; ++q) {
-        const uint32_t *f = q == 0 ? kf : (q == 1 ? nf : hf);
-        uint32_t *sc = q == 0 ? ks : (q == 1 ? ns : hs);
-        k_mid_scan1<<<(unsigned)tb, kMidBlock, 0, st>>>(f, g.tiles, sc, bsum);
-        k_mid_scan2<<<1, kMidBlock, 0, st>>>(bsum, tb, sc, g.tiles);
-        k_mid_scan3<<<blocks_for(g.tiles), kMidBlock, 0, st>>>(sc, g.tiles, bsum);
-    }
+    k_mid_scan1<<<dim3((unsigned)tb, 3), kMidBlock, 0, st>>>(kf, g.tiles, ks, bsum);
+    k_mid_scan2<<<dim3(1, 3), kMidBlock, 0, st>>>(bsum, tb, ks, g.tiles);
+    k_mid_scan3<<<dim3(blocks_for(g.tiles), 3), kMidBlock, 0, st>>>(ks, g.tiles, bsum);
     k_mid_tile_place<<<blocks_for(g.tiles), kMidBlock, 0, st>>>(g.tiles, kf, nf, hf, ks, ns, hs, tl, counts);
 }
 
@@ -1397,8 +1685,12 @@ void launch_mid_force_tiles(const MidSorted &S, const MidGrid &g, const MidTiles
                             const double *gv, const double *dv, double dt, double *epart, uint32_t *flags,
                             hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     if (tl.nk == 0) return;
-    hipExtLaunchKernelGGL(k_mid_tile<DIM, DEG, TILE_FORCE>, dim3((unsigned)tl.nk), dim3(64), 0, st, ev0, ev1, 0, S, g,
-                          tl, mat, gv, dv, 0.5 * dt, 0.25 * dt, epart, flags, (const MidCg *)nullptr);
+    if constexpr (DIM == 3)
+        hipExtLaunchKernelGGL((k_mid_tile3<DEG, TILE_FORCE>), dim3((unsigned)tl.nk), dim3(64 * kMidParts), 0,
+                              st, ev0, ev1, 0, S, g, tl, mat, gv, dv, 0.5 * dt, 0.25 * dt, epart, flags, (const MidCg *)nullptr);
+    else
+        hipExtLaunchKernelGGL((k_mid_tile<DIM, DEG, TILE_FORCE>), dim3((unsigned)tl.nk), dim3(64), 0, st, ev0, ev1, 0,
+                              S, g, tl, mat, gv, dv, 0.5 * dt, 0.25 * dt, epart, flags, (const MidCg *)nullptr);
 }
 
 template <int DIM, int DEG>
@@ -1419,9 +1711,14 @@ template <int DIM, int DEG>
 void launch_mid_apply_tiles(const MidSorted &S, const MidGrid &g, const MidTiles &tl, const MidMaterial &mat,
                             const double *pv, MidCg *cg, hipStream_t st, hipEvent_t ev0, hipEvent_t ev1) {
     if (tl.nk == 0) return;
-    hipExtLaunchKernelGGL(k_mid_tile<DIM, DEG, TILE_APPLY>, dim3((unsigned)tl.nk), dim3(64), 0, st, ev0, ev1, 0, S, g,
-                          tl, mat, pv, (const double *)nullptr, 1.0, 0.0, (double *)nullptr, (uint32_t *)nullptr,
-                          (const MidCg *)cg);
+    if constexpr (DIM == 3)
+        hipExtLaunchKernelGGL((k_mid_tile3<DEG, TILE_APPLY>), dim3((unsigned)tl.nk), dim3(64 * kMidParts), 0, st, ev0,
+                              ev1, 0, S, g, tl, mat, pv, (const double *)nullptr, 1.0, 0.0, (double *)nullptr,
+                              (uint32_t *)nullptr, (const MidCg *)cg);
+    else
+        hipExtLaunchKernelGGL((k_mid_tile<DIM, DEG, TILE_APPLY>), dim3((unsigned)tl.nk), dim3(64), 0, st, ev0, ev1, 0,
+                              S, g, tl, mat, pv, (const double *)nullptr, 1.0, 0.0, (double *)nullptr,
+                              (uint32_t *)nullptr, (const MidCg *)cg);
 }
 
 template <int DIM, int DEG>
