@@ -553,16 +553,17 @@ void bin_static(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> 
 template <typename T, int DIM, int DEG, bool ABS = false>
 void g2p_rebin(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> &dst, int cur, hipStream_t st) {
     const int nxt = 1 - cur;
+    const bool finish = g2p_finishes<T, DIM, DEG>(src.n);
     begin_build(v, ss, nxt, st);
     timed(APIC_PHASE_BIN, st, [&] {
         launch_bin_keys_moved<T, DIM, DEG, ABS>(src, v.lists[cur], v.tab[cur], v.g, v.prm, v.lists[nxt], v.sc,
                                                 v.L.rc, st);
         launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, false, st);
-        launch_bin_finalize(v.lists[nxt], v.lists[1 - nxt], v.L.rc, st);
+        if (!finish) launch_bin_finalize(v.lists[nxt], v.lists[1 - nxt], v.L.rc, st);
     });
     timed(APIC_PHASE_G2P, st, [&] {
         launch_g2p<T, DIM, DEG, ABS>(src, dst, v.lists[cur], v.tab[cur], v.lists[nxt], v.tab[nxt], v.sc, v.g, v.prm,
-                                     v.L.rc, st);
+                                     v.L.rc, finish, st);
     });
 }
 
@@ -986,6 +987,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
     int64_t all = 0;
     for (int32_t i = 0; i < n; ++i) all += scenes[i].p.n;
     const int nwaves = grid_waves<DIM>(all), kwaves = key_waves(all), gwaves = g2p_waves<T, DIM, DEG>(all);
+    const bool finish = g2p_finishes<T, DIM, DEG>(all);
     for (int32_t i = 0; i < n; ++i) {
         int64_t cap = 0;
         (void)check_scene(&scenes[i], &cap);
@@ -1122,11 +1124,11 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
                 launch_bin_keys_moved_batch<T, DIM, DEG>(dd, start_of(BK_KEYS), n, k, qk, nk, kwaves, s);
                 const BatchQueue qr = queue_of(BK_RECORDS, nr);
                 launch_bin_records_batch<T, DIM>(dd, start_of(BK_RECORDS), n, k, qr, nr, s);
-                launch_bin_finalize_batch<T>(dd, start_of(BK_FINAL), n, k, total[BK_FINAL], s);
+                if (!finish) launch_bin_finalize_batch<T>(dd, start_of(BK_FINAL), n, k, total[BK_FINAL], s);
             });
             q = queue_of(BK_G2P, nb);
             timed(APIC_PHASE_G2P, s,
-                  [&] { launch_g2p_batch<T, DIM, DEG>(dd, start_of(BK_G2P), n, k, q, nb, adaptive, gwaves, s); });
+                  [&] { launch_g2p_batch<T, DIM, DEG>(dd, start_of(BK_G2P), n, k, q, nb, adaptive, gwaves, finish, s); });
         }
         launch_copy_back_batch<T, DIM>(dd, start_of(BK_COPY), n, n_steps, total[BK_COPY], s);
     };
@@ -1157,7 +1159,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         key_put(key, DIM * 100 + DEG * 10 + (COMP ? 1 : 0));
         key_put(key, (int)adaptive);
         key_put(key, qblocks);
-        key_put(key, (nwaves * 8 + kwaves) * 8 + gwaves);
+        key_put(key, ((nwaves * 8 + kwaves) * 8 + gwaves) * 2 + (finish ? 1 : 0));
         key.append((const char *)starts.data(), starts.size() * 4);
         auto it = g_graphs.find(key);
         if (it == g_graphs.end()) {

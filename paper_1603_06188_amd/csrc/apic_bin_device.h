@@ -318,6 +318,69 @@ __device__ __forceinline__ void copy_particle(const Parts<T> &src, const Parts<T
     store_particle<T, DIM>(dst, q, ids, x);
 }
 
+// Prefix tables of a layout whose records are counted: per bucket its first record
+// number, first full tile and first particle, found by each block that asks.
+struct BucketTables {
+    uint32_t rpre[kBuckets + 1], fpre[kBuckets + 1], bpre[kBuckets + 1], part[12];
+    uint32_t nfull;
+};
+__device__ __forceinline__ void bucket_tables(const BinLists &nxt, BucketTables &tb) {
+    uint32_t nrec, nfull, live;
+    block_bucket_prefix3(nxt.rec_count, nxt.nfull, nxt.tot, tb.rpre, tb.fpre, tb.bpre, tb.part, nrec, nfull, live);
+    if (threadIdx.x == 0) {
+        tb.rpre[kBuckets] = nrec;
+        tb.bpre[kBuckets] = live;
+        tb.nfull = nfull;
+    }
+    __syncthreads();
+}
+
+// Last bucket whose exclusive prefix is <= i (pre[kBuckets] = total > i).
+__device__ __forceinline__ uint32_t bucket_search(const uint32_t *pre, uint32_t i) {
+    uint32_t lo = 0, hi = kBuckets;
+    while (hi - lo > 1u) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (pre[mid] <= i)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
+
+// Stores them and numbers the records (block `blk` of `nblk` its share of them):
+// the tiles of at least kFullTile particles first, in bucket order and then by
+// their rank in the bucket, then the others the same way, so that every tile walk
+// takes the short tiles last.
+// The counters of the other parity's build are not needed once the layout that
+// followed it is finished: they are zeroed here, for the build after this one.
+__device__ __forceinline__ void finish_layout(const BinLists &nxt, const BinLists &other, const BucketTables &tb,
+                                              uint32_t blk, uint32_t nblk) {
+    if (blk == 0) {
+        for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
+            other.rec_count[i] = 0u;
+            other.nfull[i] = 0u;
+            other.nsparse[i] = 0u;
+            other.tot[i] = 0u;
+        }
+        for (int i = (int)threadIdx.x; i <= kBuckets; i += (int)blockDim.x) {
+            nxt.rpre[i] = tb.rpre[i];
+            nxt.bpre[i] = tb.bpre[i];
+        }
+        if (threadIdx.x < kCtrCount) other.ctr[threadIdx.x] = 0u;
+    }
+    const uint32_t nrec = tb.rpre[kBuckets];
+    for (uint32_t i = blk * blockDim.x + threadIdx.x; i < nrec; i += nblk * blockDim.x) {
+        const uint32_t b = bucket_search(tb.rpre, i);
+        const uint32_t t = nxt.rec_list[(int64_t)b * nxt.rcap + (i - tb.rpre[b])];
+        const uint32_t v = nxt.slot[t];
+        const uint32_t rec =
+            (v & 0x80000000u) ? tb.nfull + (tb.rpre[b] - tb.fpre[b]) + (v & 0x7FFFFFFFu) : tb.fpre[b] + v;
+        nxt.slot[t] = rec;
+        nxt.rec_tile[rec] = t;
+    }
+}
+
 // One scene's view of step k of a batched launch: its descriptor, the lists
 // being read and built (with their generations) and its share of blocks.
 template <typename T>

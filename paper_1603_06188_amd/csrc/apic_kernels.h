@@ -51,6 +51,16 @@ inline void with_tile_waves(int waves, F &&f) {
     f(std::integral_constant<int, 4>{});
 }
 
+// The transfer to particles finds the bucket tables and numbers the records itself
+// in small scenes, instead of a launch for that before it: its blocks start later by
+// the scan (12k particles 8.6 -> 10.1 us, 4,096 12.7 -> 13.8, 227k 18.9 -> 21.5, 24
+// bodies of 0.2M 26.1 -> 29.4, against 4.1 to 5.0 and the gap between two launches;
+// 512,000 26.1 -> 30.9, binary64 42.5 -> 52.4: no longer worth it).
+template <typename T, int DIM, int DEG>
+constexpr bool g2p_finishes(int64_t n) {
+    return n > 0 && n < ((int64_t)1 << 18) && g2p_waves<T, DIM, DEG>(n) == 4;
+}
+
 // The transfer to grid takes a block per tile (else a wavefront).
 constexpr bool p2g_block_per_tile(int dim, int deg) { return dim == 3 && deg >= 2; }
 
@@ -111,7 +121,7 @@ void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTab
 template <typename T, int DIM, int DEG, bool ABS = false>
 void launch_g2p(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur, const TileTables &ctab,
                 const BinLists &nxt, const TileTables &ntab, const BinScratch &sc, const GridState<T> &g,
-                const StepParams<T> &prm, int64_t max_records, hipStream_t st);
+                const StepParams<T> &prm, int64_t max_records, bool finish, hipStream_t st);
 
 // G2P fused with the next step's P2G (binary32 quadratic 3D): writes each
 // particle to its place in layout `nxt` and the slabs of `nxt` with the
@@ -147,7 +157,7 @@ void launch_bin_records_batch(const SceneDesc<T> *descs, const int32_t *start, i
                               int blocks, hipStream_t st);
 template <typename T, int DIM, int DEG>
 void launch_g2p_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q, int blocks,
-                      bool adapt, int waves, hipStream_t st);
+                      bool adapt, int waves, bool finish, hipStream_t st);
 // Adaptive batched steps: before each step, every scene's dt from its bound
 // slots (first: the slots cleared and raised by a pass over the particles
 // each scene starts the call with; blocks as the copy-back table).

@@ -178,59 +178,11 @@ void launch_copy_back_batch(const SceneDesc<T> *descs, const int32_t *start, int
 }
 
 // --- prefix tables and record numbers of a finished layout --------------------------
-// Every block forms the bucket prefixes in LDS (block 0 also stores them).
-// Record numbers: the tiles of at least kFullTile particles first, in bucket
-// order and then by their rank in the bucket, then the others the same way,
-// so that every tile walk takes the short tiles last.
-
-// Last bucket whose exclusive prefix is <= i (pre[kBuckets] = total > i).
-__device__ __forceinline__ uint32_t bucket_search(const uint32_t *pre, uint32_t i) {
-    uint32_t lo = 0, hi = kBuckets;
-    while (hi - lo > 1u) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (pre[mid] <= i)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
-}
-
-// The counters of the other parity's build are not needed once the layout that
-// followed it is finished: they are zeroed here, for the build after this one.
-__device__ __forceinline__ void finalize_body(const BinLists &nxt, const BinLists &other, uint32_t blk, uint32_t nblk) {
-    __shared__ uint32_t rpre[kBuckets + 1], fpre[kBuckets + 1], bpre[kBuckets + 1], part[12];
-    uint32_t nrec, nfull, live;
-    block_bucket_prefix3(nxt.rec_count, nxt.nfull, nxt.tot, rpre, fpre, bpre, part, nrec, nfull, live);
-    if (threadIdx.x == 0) rpre[kBuckets] = nrec;
-    if (blk == 0) {
-        for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
-            nxt.rpre[i] = rpre[i];
-            nxt.bpre[i] = bpre[i];
-            other.rec_count[i] = 0u;
-            other.nfull[i] = 0u;
-            other.nsparse[i] = 0u;
-            other.tot[i] = 0u;
-        }
-        if (threadIdx.x < kCtrCount) other.ctr[threadIdx.x] = 0u;
-        if (threadIdx.x == 0) {
-            nxt.rpre[kBuckets] = nrec;
-            nxt.bpre[kBuckets] = live;
-        }
-    }
-    __syncthreads();
-    for (uint32_t i = blk * blockDim.x + threadIdx.x; i < nrec; i += nblk * blockDim.x) {
-        const uint32_t b = bucket_search(rpre, i);
-        const uint32_t t = nxt.rec_list[(int64_t)b * nxt.rcap + (i - rpre[b])];
-        const uint32_t v = nxt.slot[t];
-        const uint32_t rec = (v & 0x80000000u) ? nfull + (rpre[b] - fpre[b]) + (v & 0x7FFFFFFFu) : fpre[b] + v;
-        nxt.slot[t] = rec;
-        nxt.rec_tile[rec] = t;
-    }
-}
-
+// (bucket_tables, finish_layout)
 __global__ __launch_bounds__(256) void k_bin_finalize(BinLists nxt, BinLists other) {
-    finalize_body(nxt, other, blockIdx.x, gridDim.x);
+    __shared__ BucketTables tables;
+    bucket_tables(nxt, tables);
+    finish_layout(nxt, other, tables, blockIdx.x, gridDim.x);
 }
 
 void launch_bin_finalize(const BinLists &nxt, const BinLists &other, int64_t max_records, hipStream_t st) {
@@ -241,7 +193,9 @@ template <typename T>
 __global__ __launch_bounds__(256) void k_bin_finalize_batch(const SceneDesc<T> *descs, const int32_t *start, int n,
                                                             int k) {
     const BatchStep<T> b = batch_step<T>(descs, start, n, k, blockIdx.x);
-    finalize_body(b.nxt, b.cur, b.blk, b.nblk);
+    __shared__ BucketTables tables;
+    bucket_tables(b.nxt, tables);
+    finish_layout(b.nxt, b.cur, tables, b.blk, b.nblk);
 }
 
 template <typename T>

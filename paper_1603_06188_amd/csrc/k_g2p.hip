@@ -295,7 +295,9 @@ void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTab
 // ADAPT: the step's dt comes from the device and the CFL bound of the
 // written state is folded into g.cfl (adaptive steps); a separate
 // instantiation, so that fixed steps carry none of it.
-template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int WPT>
+// FINISH: the new layout's bucket tables are found here, and its records numbered
+// (g2p_finishes).
+template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int WPT, bool FINISH>
 __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur,
                                          const TileTables &ctab, const BinLists &nxt, const TileTables &ntab,
                                          const BinScratch &sc, const GridState<T> &g, const StepParams<T> &prm_in,
@@ -314,8 +316,20 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
     uint32_t *gone = lds_gone[tl], *nlo = lds_nlo[tl];
     uint64_t *nmask = lds_nmask[tl];
     const TileWalk walk = tile_walk(cur);
-    const uint32_t *bases = nxt.bpre;
-    const uint32_t live_nxt = nxt.bpre[kBuckets];
+    __shared__ std::conditional_t<FINISH, BucketTables, int> lds_tables;
+    if constexpr (FINISH) {
+        bucket_tables(nxt, lds_tables);
+        // from the last block on: those of a launch sized for the capacity have no
+        // tile, and the records end with the short ones
+        finish_layout(nxt, cur, lds_tables, nblk - 1u - blk, nblk);
+    }
+    const auto base_at = [&](uint32_t b) {
+        if constexpr (FINISH)
+            return lds_tables.bpre[b];
+        else
+            return nxt.bpre[b];
+    };
+    const uint32_t live_nxt = base_at(kBuckets);
     const T dt_inv_dx = prm.dt * g.inv_dx, gs = prm.dt * g.inv_dx;
     const uint32_t dead = dead_chunks(src.n, walk.live);
     const uint32_t items = walk.nrec + (dead + WPT - 1) / WPT;
@@ -330,7 +344,7 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
         const uint32_t t = cur.rec_tile[r];
         const uint32_t start = walk.bbase[bucket_of(t)] + ctab.off[t], total = ctab.tcount[t], maxc = ctab.maxc[t];
         const uint32_t cnt = ctab.kcount[(int64_t)t * 64 + lane];
-        const uint32_t nbase = bases[bucket_of(t)] + ntab.off[t];  // the tile's place in the new layout
+        const uint32_t nbase = base_at(bucket_of(t)) + ntab.off[t];  // the tile's place in the new layout
         const bool busy = maxc > (uint32_t)kMaxLevels, nbusy = ntab.maxc[t] > (uint32_t)kMaxLevels;
         int origin[3] = {0, 0, 0};
         tile_origin<DIM>(t, g.d.TN, origin);
@@ -396,7 +410,8 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
                 } else {
                     const uint32_t dkey = sc.pkey[p];
                     const uint32_t drank = sc.prank[p] + (dkey == kDeadKey ? 0u : ntab.kcount[dkey] - ntab.kmov[dkey]);
-                    q = bin_destination(dkey, drank, ntab, bucket_base_of(dkey, bases), live_nxt);
+                    const uint32_t dbase = dkey == kDeadKey ? 0u : base_at(bucket_of(dkey >> 6));
+                    q = bin_destination(dkey, drank, ntab, dbase, live_nxt);
                 }
                 // keep the packed index representable; a particle that left
                 // the grid is in the dead region and is not transferred again
@@ -415,14 +430,14 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
     (void)cmax;
 }
 
-template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int WPT>
+template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int WPT, bool FINISH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADAPT && DIM == 3 ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p(
     Parts<T> src, Parts<T> dst, BinLists cur, TileTables ctab, BinLists nxt, TileTables ntab, BinScratch sc,
     GridState<T> g, StepParams<T> prm) {
-    g2p_body<T, DIM, DEG, ADAPT, ABS, WPT>(src, dst, cur, ctab, nxt, ntab, sc, g, prm, blockIdx.x, gridDim.x);
+    g2p_body<T, DIM, DEG, ADAPT, ABS, WPT, FINISH>(src, dst, cur, ctab, nxt, ntab, sc, g, prm, blockIdx.x, gridDim.x);
 }
 
-template <typename T, int DIM, int DEG, bool ADAPT, bool QUEUE, int WPT>
+template <typename T, int DIM, int DEG, bool ADAPT, bool QUEUE, int WPT, bool FINISH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p_batch(
     const SceneDesc<T> *descs, const int32_t *start, int n, int k, BatchQueue q) {
     batch_items<QUEUE>(q, [&](uint32_t it) {
@@ -436,24 +451,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
         const BinScratch sc = table_struct(d.sc);
         const GridState<T> g = table_struct(d.g);
         const StepParams<T> prm = table_struct(d.prm);
-        g2p_body<T, DIM, DEG, ADAPT, false, WPT>(src, dst, b.cur, ctab, b.nxt, ntab, sc, g, prm, b.blk, b.nblk);
+        g2p_body<T, DIM, DEG, ADAPT, false, WPT, FINISH>(src, dst, b.cur, ctab, b.nxt, ntab, sc, g, prm, b.blk,
+                                                        b.nblk);
     });
+}
+
+// Runs f with the wavefronts per tile and FINISH as compile-time constants.
+template <typename T, int DIM, int DEG, typename F>
+static void with_g2p_variant(int waves, bool finish, F &&f) {
+    if (finish)
+        f(std::integral_constant<int, 4>{}, std::true_type{});
+    else
+        with_tile_waves<g2p_waves_choice<T, DIM, DEG>()>(waves, [&](auto w) { f(w, std::false_type{}); });
 }
 
 template <typename T, int DIM, int DEG>
 void launch_g2p_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q, int blocks,
-                      bool adapt, int waves, hipStream_t st) {
+                      bool adapt, int waves, bool finish, hipStream_t st) {
     const dim3 grid((unsigned)blocks), block(256);
-    with_tile_waves<g2p_waves_choice<T, DIM, DEG>()>(waves, [&](auto w) {
+    with_g2p_variant<T, DIM, DEG>(waves, finish, [&](auto w, auto f) {
         constexpr int WPT = decltype(w)::value;
+        constexpr bool FINISH = decltype(f)::value;
         if (adapt && q.ctr)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, true, WPT>), grid, block, 0, st, descs, start, n, k, q);
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, true, WPT, FINISH>), grid, block, 0, st, descs, start, n,
+                               k, q);
         else if (adapt)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, false, WPT>), grid, block, 0, st, descs, start, n, k, q);
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, false, WPT, FINISH>), grid, block, 0, st, descs, start,
+                               n, k, q);
         else if (q.ctr)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, true, WPT>), grid, block, 0, st, descs, start, n, k, q);
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, true, WPT, FINISH>), grid, block, 0, st, descs, start,
+                               n, k, q);
         else
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, false, WPT>), grid, block, 0, st, descs, start, n, k, q);
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, false, WPT, FINISH>), grid, block, 0, st, descs, start,
+                               n, k, q);
     });
 }
 
@@ -528,23 +558,24 @@ void launch_adapt_dt_batch(const SceneDesc<T> *descs, const int32_t *copy_start,
 template <typename T, int DIM, int DEG, bool ABS>
 void launch_g2p(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur, const TileTables &ctab,
                 const BinLists &nxt, const TileTables &ntab, const BinScratch &sc, const GridState<T> &g,
-                const StepParams<T> &prm, int64_t max_records, hipStream_t st) {
+                const StepParams<T> &prm, int64_t max_records, bool finish, hipStream_t st) {
     if (src.n == 0) return;
     Parts<T> s2 = src, d2 = dst;
     if (!src.id || !dst.id) s2.id = d2.id = nullptr;
-    with_tile_waves<g2p_waves_choice<T, DIM, DEG>()>(g2p_waves<T, DIM, DEG>(src.n), [&](auto w) {
+    with_g2p_variant<T, DIM, DEG>(g2p_waves<T, DIM, DEG>(src.n), finish, [&](auto w, auto f) {
         constexpr int WPT = decltype(w)::value;
+        constexpr bool FINISH = decltype(f)::value;
         const int64_t items = max_records + (src.n + 64 * WPT - 1) / (64 * WPT), tpb = 4 / WPT;
         const dim3 blocks((unsigned)std::min<int64_t>(std::max<int64_t>((items + tpb - 1) / tpb, 1), 4096));
         if constexpr (!ABS) {
             if (g.cfl) {
-                hipLaunchKernelGGL((k_g2p<T, DIM, DEG, true, false, WPT>), blocks, dim3(256), 0, st, s2, d2, cur, ctab,
-                                   nxt, ntab, sc, g, prm);
+                hipLaunchKernelGGL((k_g2p<T, DIM, DEG, true, false, WPT, FINISH>), blocks, dim3(256), 0, st, s2, d2,
+                                   cur, ctab, nxt, ntab, sc, g, prm);
                 return;
             }
         }
-        hipLaunchKernelGGL((k_g2p<T, DIM, DEG, false, ABS, WPT>), blocks, dim3(256), 0, st, s2, d2, cur, ctab, nxt,
-                           ntab, sc, g, prm);
+        hipLaunchKernelGGL((k_g2p<T, DIM, DEG, false, ABS, WPT, FINISH>), blocks, dim3(256), 0, st, s2, d2, cur, ctab,
+                           nxt, ntab, sc, g, prm);
     });
 }
 
@@ -553,7 +584,7 @@ void launch_g2p(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur, c
                                                            const BatchQueue &, int, int,                              \
                                                            hipStream_t);                                          \
     template void launch_g2p_batch<T, DIM, DEG>(const SceneDesc<T> *, const int32_t *, int, int,                      \
-                                                const BatchQueue &, int, bool, int,                                   \
+                                                const BatchQueue &, int, bool, int, bool,                             \
                                                 hipStream_t);                                                     \
     template void launch_bin_keys_moved<T, DIM, DEG, false>(const Parts<T> &, const BinLists &, const TileTables &, \
                                                             const GridState<T> &, const StepParams<T> &,         \
@@ -562,7 +593,7 @@ void launch_g2p(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur, c
     template void launch_g2p<T, DIM, DEG, false>(const Parts<T> &, const Parts<T> &, const BinLists &,           \
                                                  const TileTables &, const BinLists &, const TileTables &,       \
                                                  const BinScratch &, const GridState<T> &, const StepParams<T> &, \
-                                                 int64_t, hipStream_t);
+                                                 int64_t, bool, hipStream_t);
 APIC_G2P_INST(float, 2, 1)
 APIC_G2P_INST(float, 3, 1)
 APIC_G2P_INST(double, 2, 1)
@@ -584,7 +615,7 @@ APIC_G2P_INST(double, 3, 3)
     template void launch_g2p<float, DIM, DEG, true>(const Parts<float> &, const Parts<float> &, const BinLists &, \
                                                     const TileTables &, const BinLists &, const TileTables &,    \
                                                     const BinScratch &, const GridState<float> &,                \
-                                                    const StepParams<float> &, int64_t, hipStream_t);
+                                                    const StepParams<float> &, int64_t, bool, hipStream_t);
 APIC_G2P_ABS_INST(2, 2)
 APIC_G2P_ABS_INST(2, 3)
 APIC_G2P_ABS_INST(3, 2)
