@@ -545,8 +545,7 @@ void bin_static(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> 
     begin_build(v, ss, nxt, st);
     launch_bin_keys_static<T, DIM, DEG, ABS>(src, via, v.L.d, v.lists[nxt], v.sc, v.g.flags, v.g.inv_dx, st);
     launch_bin_records<DIM>(v.L.d, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, true, st);
-    launch_bin_finalize(v.lists[nxt], v.lists[1 - nxt], v.L.rc, st);
-    launch_bin_gather<T, DIM>(via ? *via : src, dst, v.lists[nxt], v.tab[nxt], v.sc, v.L.rc, st);
+    launch_bin_gather<T, DIM>(via ? *via : src, dst, v.lists[nxt], v.lists[1 - nxt], v.tab[nxt], v.sc, v.L.rc, st);
 }
 
 // One G2P from `src` (layout `cur`) into `dst` (layout 1 - cur).

@@ -93,10 +93,11 @@ template <typename T>
 void launch_bin_finalize_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, int blocks,
                                hipStream_t st);
 
-// Moves every particle from src to its binned position in dst (apic_sort).
+// Finishes layout `nxt` and moves every particle from src to its binned position in
+// dst (apic_sort).
 template <typename T, int DIM>
-void launch_bin_gather(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const TileTables &tab,
-                       const BinScratch &sc, int64_t max_records, hipStream_t st);
+void launch_bin_gather(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const BinLists &other,
+                       const TileTables &tab, const BinScratch &sc, int64_t max_records, hipStream_t st);
 
 // --- transfers ----------------------------------------------------------------
 // P2G over the layout `cur`; also zeroes the counters of `nxt` and the

@@ -225,13 +225,25 @@ void launch_bin_records(const GridDims &d, const BinLists &nxt, const TileTables
 // parts of lines that several XCDs' caches held (2.1M binary32 particles in
 // lexicographic order: 805 us, the two passes now 18 and 216; 4,096 of them: 17
 // us, now 3 and 12, where launches and round trips bound both).
-__global__ __launch_bounds__(256) void k_bin_place(int64_t n, BinLists nxt, TileTables tab, BinScratch sc) {
+// FINISH: each block finds the bucket tables, and the layout is finished here.
+template <bool FINISH>
+__global__ __launch_bounds__(256) void k_bin_place(int64_t n, BinLists nxt, BinLists other, TileTables tab,
+                                                   BinScratch sc) {
     const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= n) return;
-    const uint32_t key = sc.pkey[p], rank = sc.prank[p];
-    uint32_t at = nxt.bpre[kBuckets];
-    if (key != kDeadKey) at = nxt.bpre[bucket_of(key >> 6)] + tab.off[key >> 6] + tab.kprefix[key];
-    sc.next[at + rank] = (uint32_t)p;
+    const uint32_t key = p < n ? sc.pkey[p] : kDeadKey, rank = p < n ? sc.prank[p] : 0u;
+    const bool dead = key == kDeadKey;
+    const uint32_t in_bucket = dead ? 0u : tab.off[key >> 6] + tab.kprefix[key];
+    const uint32_t b = dead ? (uint32_t)kBuckets : bucket_of(key >> 6);
+    uint32_t base;
+    if constexpr (FINISH) {
+        __shared__ BucketTables tables;
+        bucket_tables(nxt, tables);
+        finish_layout(nxt, other, tables, blockIdx.x, gridDim.x);
+        base = tables.bpre[b];
+    } else {
+        base = nxt.bpre[b];
+    }
+    if (p < n) sc.next[base + in_bucket + rank] = (uint32_t)p;
 }
 
 template <typename T, int DIM>
@@ -283,12 +295,21 @@ __global__ __launch_bounds__(256) void k_bin_gather(Parts<T> src, Parts<T> dst, 
 }
 
 template <typename T, int DIM>
-void launch_bin_gather(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const TileTables &tab,
-                       const BinScratch &sc, int64_t max_records, hipStream_t st) {
+void launch_bin_gather(const Parts<T> &src, const Parts<T> &dst, const BinLists &nxt, const BinLists &other,
+                       const TileTables &tab, const BinScratch &sc, int64_t max_records, hipStream_t st) {
+    // The placement finishes the layout of a small scene (its blocks wait for the
+    // scan: 37k particles 3.4 us and a finalize pass of 4.6 -> 5.8); a large one, and
+    // one without particles, has the pass.
+    const bool finish = src.n > 0 && src.n < ((int64_t)1 << 18);
+    if (!finish) launch_bin_finalize(nxt, other, max_records, st);
     if (src.n == 0) return;
     Parts<T> s2 = src, d2 = dst;
     if (!src.id || !dst.id) s2.id = d2.id = nullptr;
-    hipLaunchKernelGGL(k_bin_place, dim3((unsigned)((src.n + 255) / 256)), dim3(256), 0, st, src.n, nxt, tab, sc);
+    const dim3 blocks((unsigned)((src.n + 255) / 256));
+    if (finish)
+        hipLaunchKernelGGL(k_bin_place<true>, blocks, dim3(256), 0, st, src.n, nxt, other, tab, sc);
+    else
+        hipLaunchKernelGGL(k_bin_place<false>, blocks, dim3(256), 0, st, src.n, nxt, other, tab, sc);
     hipLaunchKernelGGL((k_bin_gather<T, DIM>), dim3(blocks_for(max_records + (src.n + 255) / 256, 1, 8192)), dim3(256),
                        0, st, s2, d2, nxt, tab, sc);
 }
@@ -305,7 +326,7 @@ template void launch_bin_records<3>(const GridDims &, const BinLists &, const Ti
                                                    hipStream_t);                                                  \
     template void launch_copy_back_batch<T, DIM>(const SceneDesc<T> *, const int32_t *, int, int, int,            \
                                                  hipStream_t);                                                    \
-    template void launch_bin_gather<T, DIM>(const Parts<T> &, const Parts<T> &, const BinLists &,                 \
+    template void launch_bin_gather<T, DIM>(const Parts<T> &, const Parts<T> &, const BinLists &, const BinLists &,                 \
                                             const TileTables &, const BinScratch &, int64_t, hipStream_t);        \
     template void launch_bin_keys_static<T, DIM, 1, false>(const Parts<T> &, const Parts<T> *, const GridDims &, const BinLists &,  \
                                                            const BinScratch &, uint32_t *, T, hipStream_t);      \
