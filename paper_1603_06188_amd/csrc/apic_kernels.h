@@ -17,8 +17,8 @@ constexpr int kDiagBlocks = 1024;
 //   key pass: 512,000 particles 13 us with four, 16 with one; 884,736: 21 and
 //   17; 2D 1.19M: 29 and 23; cubic 9.0M: 235 and 163 (153 since the bounds of
 //   |vt| are one load).
-//   transfer to particles: 884,736 binary32 quadratic 45 with four; 2,097,152:
-//   108 and 91.  The others (two or three wavefronts per SIMD by their
+//   transfer to particles: 884,736 binary32 quadratic 40 with four; 1,404,928:
+//   64 and 65; 2,097,152: 101 and 90.  The others (two or three wavefronts per SIMD by their
 //   registers, or small 2D tiles) keep four: cubic 9.0M 727 against 735, 2D
 //   1.19M 49 against 69, binary64 cubic 1.12M 167 against 178.
 constexpr int key_waves(int64_t n) { return n >= ((int64_t)1 << 19) ? 1 : 4; }

@@ -85,11 +85,14 @@ __device__ __forceinline__ void records_body(const BinLists &nxt, const TileTabl
         const uint32_t b = bucket_find(rpre, r);
         const uint32_t t = nxt.rec_list[(int64_t)b * nxt.rcap + (r - rpre[b])];
         const int64_t key = (int64_t)t * 64 + lane;
-        const uint32_t mov = sc.key_count[key];
-        const uint32_t c = mov + sc.scount[key];
+        const uint32_t mov = sc.key_count[key], stay = sc.scount[key], h = !STATIC && mov ? sc.head[key] : 0u;
+        const uint32_t c = mov + stay;
         sc.key_count[key] = 0u;
         sc.scount[key] = 0u;
-        if (!STATIC && mov) rank_movers(sc.head + key, mov, sc);
+        if (h) {
+            sc.head[key] = 0u;
+            rank_movers<DIM == 2 ? 8 : 0>(h, mov, sc);
+        }
         uint32_t total;
         const uint32_t kp = wave_excl_scan(c, total);
         const uint32_t mx = wave_max_u32(c);
