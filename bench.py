@@ -314,14 +314,14 @@ def midpoint_tiles(scene):
 
 
 MIDPOINT_TRAFFIC = os.path.join(ROOT, "profiles", "traffic_midpoint_cube128.txt")
-MIDPOINT_APPLY_KERNEL = "k_mid_tile<3, 2, 2>"
-MIDPOINT_PARTICLE_B = 188  # cell 4, offset 24, F 72, F_hat^{-T} 72, mu - lambda ln J 8, m 8
+MIDPOINT_APPLY_KERNEL = "k_mid_tile3<2, 2>"
+MIDPOINT_PARTICLE_B = 184  # offset 24, F 72, F_hat^{-T} F^T 72, mu - lambda ln J 8, m 8
 
 
 def midpoint_roofline(res):
     """Roofline of the midpoint step's dominant kernel, the particle pass of
     each CG iteration (operator application), timed live: algorithmic bytes
-    per launch = particles x 188 B + the key tiles' region slabs written
+    per launch = particles x 184 B + the key tiles' region slabs written
     (216 nodes x 3 x 8 B) + the direction p read on the listed node tiles
     (64 nodes x 3 x 8 B), over the mean launch duration; traffic from the
     committed FETCH_SIZE / WRITE_SIZE summary when it matches the sources."""
@@ -337,7 +337,7 @@ def midpoint_roofline(res):
 
         summ = profile_traffic.read_summary(MIDPOINT_TRAFFIC)
         if summ.get("source_sha256") == profile_traffic.source_hash():
-            v = summ.get("k_mid_tile_3_2_2_traffic_bytes")
+            v = summ.get("k_mid_tile3_2_2_traffic_bytes")
             traffic = float(v) if v is not None else None
     return {"bound": "hbm", "kernel": MIDPOINT_APPLY_KERNEL, "achieved": achieved, "peak": 8000.0, "unit": "GB/s",
             "frac": achieved / 8000.0, "traffic": traffic, "algorithmic_bytes": alg,

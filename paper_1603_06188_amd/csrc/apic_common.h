@@ -111,16 +111,17 @@ struct TileTables {
 // records pass walks each key's list and gives every mover its final rank:
 // the number of movers into the key that precede it in the old layout's
 // order.  The order value of a particle is (tile << 32 | index within the
-// tile) for a re-binning (tiles sit in the particle planes in the order their
-// counters ran, so absolute positions would not do) and its position for a
-// binning from scratch.
+// tile): tiles sit in the particle planes in the order their counters ran, so
+// absolute positions would not do.  (A binning from scratch takes provisional
+// ranks too, and orders a key's particles by their position as it gathers them.)
 struct BinScratch {
     uint32_t *key_count;  // [G]   movers entering each key
     uint32_t *scount;     // [G]   particles staying in each key
     uint32_t *head;       // [G]   list of the movers entering each key: first old position + 1 (0: none)
     uint32_t *pkey;       // [cap] new key of a mover (kDeadKey: dead)
     uint32_t *prank;      // [cap] rank of a mover within its key / among the dead
-    uint32_t *next;       // [cap] next mover of the same key's list, old position + 1 (0: end)
+    uint32_t *next;       // [cap] next mover of the same key's list, old position + 1 (0: end); in a sort, the
+                          // particles key after key
     uint64_t *pord;       // [cap] order value of a mover
 };
 

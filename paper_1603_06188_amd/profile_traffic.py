@@ -11,7 +11,7 @@ tell whether the kernels still match the counters.
 
 KERNELS (optional): comma-separated kernel-name prefixes to summarize instead
 of the explicit step's kernels; their keys keep the template arguments
-(k_mid_tile<3, 2, 2> -> k_mid_tile_3_2_2).
+(k_mid_tile3<2, 2> -> k_mid_tile3_2_2).
 """
 from __future__ import annotations
 
