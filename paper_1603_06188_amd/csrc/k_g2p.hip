@@ -289,7 +289,7 @@ void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTab
 // marks: no counter, no test of the key, and the tile's level tables from LDS
 // instead of two dependent loads per particle).  Below it, vector issue counts:
 // with the plane addresses by scalar adds and row sums in the sweep a chunk is
-// 670 vector instructions, not 920 (quadratic), and four wavefronts fit a SIMD
+// 760 vector instructions, not 915 (quadratic), and four wavefronts fit a SIMD
 // in the cubic too (binary32 quadratic 512,000 particles 29.8 -> 26.1 us, cubic
 // 9.0M 724 -> 659, binary64 quadratic 512,000 47 -> 42.5).
 // ADAPT: the step's dt comes from the device and the CFL bound of the
