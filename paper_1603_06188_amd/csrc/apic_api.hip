@@ -67,7 +67,7 @@ struct Layout {
     int64_t rc;     // record (slab) capacity: min(tiles, cap)
     int64_t rcap;   // list capacity per bucket: ceil(tiles / kBuckets)
     int64_t slab_stride;
-    size_t o_vt, o_uref, o_flags, o_vmax, o_cfl, o_dt, o_diag_out, o_diag_part, o_key_count, o_scount,
+    size_t o_vt, o_uref, o_flags, o_cfl, o_dt, o_diag_out, o_diag_part, o_key_count, o_scount,
         o_head;
     ListOff lists[2];
     TabOff tabs[2];
@@ -114,7 +114,6 @@ Layout make_layout(const apic_grid_desc *g, int64_t cap) {
     L.o_vt = take(dim * G * e);
     L.o_uref = take(dim * TT * e);
     L.o_flags = take(64);
-    L.o_vmax = take(TT * 16);
     L.o_cfl = take((size_t)kCflSlots * 8);
     L.o_dt = take(2 * sizeof(double));
     L.o_diag_out = take(8 * sizeof(double));
@@ -464,7 +463,7 @@ View<T> make_view(const apic_scene *s, int64_t cap, const SceneState &ss) {
     v.g.vt = (T *)(w + L.o_vt);
     v.g.uref = (T *)(w + L.o_uref);
     v.g.flags = (uint32_t *)(w + L.o_flags);
-    v.g.vmax = (float *)(w + L.o_vmax);
+    v.g.vmax = nullptr;  // by layout: tile_bounds
     v.g.cfl = nullptr;
     v.g.cfl_c = cfl_factor(s->grid);
     v.g.d = L.d;
@@ -553,6 +552,7 @@ template <typename T, int DIM, int DEG, bool ABS = false>
 void g2p_rebin(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> &dst, int cur, hipStream_t st) {
     const int nxt = 1 - cur;
     const bool finish = g2p_finishes<T, DIM, DEG>(src.n);
+    v.g.vmax = tile_bounds(v.tab[nxt].lvl_off);
     begin_build(v, ss, nxt, st);
     timed(APIC_PHASE_BIN, st, [&] {
         launch_bin_keys_moved<T, DIM, DEG, ABS>(src, v.lists[cur], v.tab[cur], v.g, v.prm, v.lists[nxt], v.sc,
@@ -578,6 +578,7 @@ constexpr bool fused_step() {
 template <typename T, int DIM, int DEG, bool COMP>
 void g2p2g_rebin(View<T> &v, SceneState &ss, const Parts<T> &src, const Parts<T> &dst, int cur, hipStream_t st) {
     const int nxt = 1 - cur;
+    v.g.vmax = tile_bounds(v.tab[nxt].lvl_off);
     begin_build(v, ss, nxt, st);
     timed(APIC_PHASE_BIN, st, [&] {
         launch_bin_keys_moved<T, DIM, DEG>(src, v.lists[cur], v.tab[cur], v.g, v.prm, v.lists[nxt], v.sc, v.L.rc,
@@ -627,6 +628,7 @@ apic_status run(Op op, const apic_scene *s, int64_t cap, hipStream_t st, const O
         case Op::GridUpdate:
             if (ss.grid_meta < 0 || ss.grid_meta != ss.cur || !ss.binned)
                 return fail(APIC_E_INVAL, "apic_grid_update needs a preceding apic_p2g on the current particles");
+            v.g.vmax = tile_bounds(v.tab[1 - ss.cur].lvl_off);
             launch_grid_update<T, DIM, DEG, COMP>(v.lists[ss.grid_meta], v.slabs, v.g, v.prm, s->p.n, v.L.rc, st);
             ss.vt_valid = true;
             break;
@@ -721,6 +723,7 @@ apic_status run_steps(apic_scene *s, int64_t cap, int32_t n_steps, int32_t sort_
                                               v.slabs, v.g, v.prm, v.L.rc, st);
             });
         }
+        v.g.vmax = tile_bounds(v.tab[1 - ss.cur].lvl_off);
         timed(APIC_PHASE_GRID_UPDATE, st, [&] {
             launch_grid_update<T, DIM, DEG, COMP>(v.lists[ss.cur], v.slabs, v.g, v.prm, s->p.n, v.L.rc, st);
         });

@@ -164,7 +164,7 @@ struct GridState {
     T *vt;              // dim planes of G nodes: updated velocity
     T *uref;            // dim planes of `tiles`: reference velocity of each listed key tile
     uint32_t *flags;
-    float *vmax;        // [tiles][4]: bound of |vt_i| over the nodes of a node tile, per axis
+    float *vmax;        // [tiles][4]: bound of |vt_i| over the nodes of a node tile, per axis (tile_bounds)
     // [kCflSlots] binary64 bits; the transfer to particles raises them to
     // max_p (|v_p| + cfl_c |B_p|_F) of the state it writes (null: it does not)
     unsigned long long *cfl;
@@ -172,6 +172,13 @@ struct GridState {
     GridDims d;
     T dx, inv_dx;
 };
+
+// Where the bounds of |vt_i| lie: in the level offsets of the layout about to be
+// built.  The grid update writes them and the key pass, the first of the build,
+// reads them; the records pass writes the offsets after it.  (Memory of their own
+// would take a workspace past the size that held the same scene without them.)
+static_assert(kMaxLevels * sizeof(uint32_t) >= 4 * sizeof(float), "a tile's bounds fit its level offsets");
+__host__ __device__ __forceinline__ float *tile_bounds(uint32_t *next_lvl_off) { return (float *)next_lvl_off; }
 
 template <typename T>
 struct StepParams {

@@ -245,7 +245,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
         // read again after every store the compiler cannot prove apart
         const Parts<T> P = table_struct(d.bufs[b.sp.src]);
         const TileTables ctab = table_struct(d.tab[b.sp.cur]);
-        const GridState<T> g = table_struct(d.g);
+        GridState<T> g = table_struct(d.g);
+        g.vmax = tile_bounds(table_struct(d.tab[b.sp.nxt].lvl_off));
         const StepParams<T> prm = table_struct(d.prm);
         const BinScratch sc = table_struct(d.sc);
         keys_body<T, DIM, DEG, false, WPT>(P, b.cur, ctab, g, prm, b.nxt, sc, b.blk, b.nblk);

@@ -239,7 +239,8 @@ __global__ __launch_bounds__(256) void k_grid_update_batch(const SceneDesc<T> *d
         // the scene's structs as values: read through the table they would be
         // read again after every store the compiler cannot prove apart
         const Slabs<T> slabs = table_struct(d.slabs);
-        const GridState<T> g = table_struct(d.g);
+        GridState<T> g = table_struct(d.g);
+        g.vmax = tile_bounds(table_struct(d.tab[b.sp.nxt].lvl_off));
         const StepParams<T> prm = table_struct(d.prm);
         grid_update_body<T, DIM, DEG, COMP, WPT>(b.cur, slabs, g, prm, b.blk, b.nblk);
     });
