@@ -629,7 +629,7 @@ apic_status run(Op op, const apic_scene *s, int64_t cap, hipStream_t st, const O
             if (ss.grid_meta < 0 || ss.grid_meta != ss.cur || !ss.binned)
                 return fail(APIC_E_INVAL, "apic_grid_update needs a preceding apic_p2g on the current particles");
             v.g.vmax = tile_bounds(v.tab[1 - ss.cur].lvl_off);
-            launch_grid_update<T, DIM, DEG, COMP>(v.lists[ss.grid_meta], v.slabs, v.g, v.prm, s->p.n, v.L.rc, st);
+            launch_grid_update<T, DIM, DEG, COMP>(v.lists[ss.grid_meta], v.slabs, v.g, v.prm, v.L.rc, st);
             ss.vt_valid = true;
             break;
         case Op::G2P:
@@ -725,7 +725,7 @@ apic_status run_steps(apic_scene *s, int64_t cap, int32_t n_steps, int32_t sort_
         }
         v.g.vmax = tile_bounds(v.tab[1 - ss.cur].lvl_off);
         timed(APIC_PHASE_GRID_UPDATE, st, [&] {
-            launch_grid_update<T, DIM, DEG, COMP>(v.lists[ss.cur], v.slabs, v.g, v.prm, s->p.n, v.L.rc, st);
+            launch_grid_update<T, DIM, DEG, COMP>(v.lists[ss.cur], v.slabs, v.g, v.prm, v.L.rc, st);
         });
         ss.grid_meta = ss.cur;
         // the last step of the call leaves the slabs of the step it made
@@ -988,7 +988,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
     double updates = 0.0;
     int64_t all = 0;
     for (int32_t i = 0; i < n; ++i) all += scenes[i].p.n;
-    const int nwaves = grid_waves<DIM>(all), kwaves = key_waves(all), gwaves = g2p_waves<T, DIM, DEG>(all);
+    const int kwaves = key_waves(all), gwaves = g2p_waves<T, DIM, DEG>(all);
     const bool finish = g2p_finishes<T, DIM, DEG>(all);
     for (int32_t i = 0; i < n; ++i) {
         int64_t cap = 0;
@@ -1045,7 +1045,9 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         // with a quarter), a quarter for a small one (24 bodies, 0.2M: 37 us
         // against 48)
         const int pb_tile = all >= ((int64_t)1 << 21) ? pb / 2 : pb / 4;
-        const int pb_p2g = p2g_block_per_tile(DIM, DEG) ? pb_tile : pb, pb_grid = nwaves == 4 ? pb_tile : pb;
+        const int pb_p2g = p2g_block_per_tile(DIM, DEG) ? pb_tile : pb;
+        // (the grid update of a batch that fills the chip takes a wavefront per tile)
+        const int pb_grid = all < ((int64_t)1 << (DIM == 3 ? 22 : 20)) ? pb_tile : pb;
         const int pb_keys = kwaves == 4 ? pb_tile : pb, pb_part = gwaves == 4 ? pb_tile : pb;
         const int share[BK_COUNT] = {share_blocks(np, pb_p2g, 4096), share_blocks(np, pb_grid, 8192),
                                      share_blocks(np, pb_keys, 4096), share_blocks(np, pb, 1024),
@@ -1119,7 +1121,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
             timed(APIC_PHASE_P2G, s, [&] { launch_p2g_batch<T, DIM, DEG, COMP>(dd, start_of(BK_P2G), n, k, q, nb, s); });
             q = queue_of(BK_GRID, nb);
             timed(APIC_PHASE_GRID_UPDATE, s,
-                  [&] { launch_grid_update_batch<T, DIM, DEG, COMP>(dd, start_of(BK_GRID), n, k, q, nb, nwaves, s); });
+                  [&] { launch_grid_update_batch<T, DIM, DEG, COMP>(dd, start_of(BK_GRID), n, k, q, nb, s); });
             timed(APIC_PHASE_BIN, s, [&] {
                 int nk = 0, nr = 0;
                 const BatchQueue qk = queue_of(BK_KEYS, nk);
@@ -1161,7 +1163,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         key_put(key, DIM * 100 + DEG * 10 + (COMP ? 1 : 0));
         key_put(key, (int)adaptive);
         key_put(key, qblocks);
-        key_put(key, ((nwaves * 8 + kwaves) * 8 + gwaves) * 2 + (finish ? 1 : 0));
+        key_put(key, (kwaves * 8 + gwaves) * 2 + (finish ? 1 : 0));
         key.append((const char *)starts.data(), starts.size() * 4);
         auto it = g_graphs.find(key);
         if (it == g_graphs.end()) {

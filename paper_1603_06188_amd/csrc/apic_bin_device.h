@@ -343,17 +343,18 @@ __device__ __forceinline__ void copy_particle(const Parts<T> &src, const Parts<T
 }
 
 // Prefix tables of a layout whose records are counted: per bucket its first record
-// number, first full tile and first particle, found by each block that asks.
+// number, first full tile and first particle (bpre, [kBuckets + 1]), found by each
+// block that asks.
 struct BucketTables {
-    uint32_t rpre[kBuckets + 1], fpre[kBuckets + 1], bpre[kBuckets + 1], part[12];
+    uint32_t rpre[kBuckets + 1], fpre[kBuckets + 1], part[12];
     uint32_t nfull;
 };
-__device__ __forceinline__ void bucket_tables(const BinLists &nxt, BucketTables &tb) {
+__device__ __forceinline__ void bucket_tables(const BinLists &nxt, BucketTables &tb, uint32_t *bpre) {
     uint32_t nrec, nfull, live;
-    block_bucket_prefix3(nxt.rec_count, nxt.nfull, nxt.tot, tb.rpre, tb.fpre, tb.bpre, tb.part, nrec, nfull, live);
+    block_bucket_prefix3(nxt.rec_count, nxt.nfull, nxt.tot, tb.rpre, tb.fpre, bpre, tb.part, nrec, nfull, live);
     if (threadIdx.x == 0) {
         tb.rpre[kBuckets] = nrec;
-        tb.bpre[kBuckets] = live;
+        bpre[kBuckets] = live;
         tb.nfull = nfull;
     }
     __syncthreads();
@@ -379,7 +380,7 @@ __device__ __forceinline__ uint32_t bucket_search(const uint32_t *pre, uint32_t 
 // The counters of the other parity's build are not needed once the layout that
 // followed it is finished: they are zeroed here, for the build after this one.
 __device__ __forceinline__ void finish_layout(const BinLists &nxt, const BinLists &other, const BucketTables &tb,
-                                              uint32_t blk, uint32_t nblk) {
+                                              const uint32_t *bpre, uint32_t blk, uint32_t nblk) {
     if (blk == 0) {
         for (int i = (int)threadIdx.x; i < kBuckets; i += (int)blockDim.x) {
             other.rec_count[i] = 0u;
@@ -389,7 +390,7 @@ __device__ __forceinline__ void finish_layout(const BinLists &nxt, const BinList
         }
         for (int i = (int)threadIdx.x; i <= kBuckets; i += (int)blockDim.x) {
             nxt.rpre[i] = tb.rpre[i];
-            nxt.bpre[i] = tb.bpre[i];
+            nxt.bpre[i] = bpre[i];
         }
         if (threadIdx.x < kCtrCount) other.ctr[threadIdx.x] = 0u;
     }

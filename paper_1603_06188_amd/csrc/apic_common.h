@@ -594,24 +594,24 @@ __device__ __forceinline__ uint32_t xcd_block(uint32_t blk, uint32_t nblk) {
     return c * q + (c < rem ? c : rem) + blk / kXcds;
 }
 
-// A walk over `items` work items, one per PER wavefronts of 256-thread blocks.
+// A walk over `items` work items, one per `per` (1 or 4) wavefronts of 256-thread blocks.
 // Launches are sized for the capacity, so only the first
-// min(nblk, ceil(items / (4 / PER))) blocks take part, renumbered by xcd_block
+// min(nblk, ceil(items / (4 / per))) blocks take part, renumbered by xcd_block
 // among themselves; `first` is this wave's first item (items when it has none).
 // When the items outnumber the waves the walk is strided and left in
 // hardware order, which spreads the extra items over all XCDs.
 struct WaveWalk {
     uint32_t first, stride;
 };
-template <int PER>
-__device__ __forceinline__ WaveWalk wave_walk(uint32_t blk, uint32_t nblk, uint32_t items) {
-    constexpr uint32_t IPB = 4 / PER;  // items of a block
-    const uint32_t need = (uint32_t)(((uint64_t)items + IPB - 1u) / IPB);
+__device__ __forceinline__ WaveWalk wave_walk(uint32_t per, uint32_t blk, uint32_t nblk, uint32_t items) {
+    const uint32_t ipb = per == 4u ? 1u : 4u;  // items of a block
+    const uint32_t need = (uint32_t)(((uint64_t)items + ipb - 1u) / ipb);
     const uint32_t nb = need < nblk ? need : nblk;
     WaveWalk w;
-    w.stride = nb * IPB;
+    w.stride = nb * ipb;
     const uint32_t lb = need <= nblk ? xcd_block(blk, nb) : blk;
-    w.first = blk < nb ? lb * IPB + (uint32_t)(threadIdx.x >> 6) / (uint32_t)PER : items;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    w.first = blk < nb ? lb * ipb + (ipb == 4u ? wave : 0u) : items;
     return w;
 }
 

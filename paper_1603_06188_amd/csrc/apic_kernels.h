@@ -7,20 +7,50 @@ namespace apic {
 
 constexpr int kDiagBlocks = 1024;
 
-// Wavefronts per tile of the key pass and of the transfer to particles of a
-// scene (or batch) of n particles.  The results are the same bits.
-// A small scene has fewer tiles than the chip has wavefront slots, and a tile's
-// chain of loads and chunks is its time: four wavefronts share it (transfer to
-// particles of 4,096 particles 34 -> 14 us, of 238,328 42 -> 21, 24 bodies 63 ->
-// 32; key pass 10 -> 8, 13.6 -> 9).  A large one pays for the tile's prologue in
-// every wavefront, and in the key pass for a round of resolving in each:
-//   key pass: 512,000 particles 13 us with four, 16 with one; 884,736: 21 and
-//   17; 2D 1.19M: 29 and 23; cubic 9.0M: 235 and 163 (153 since the bounds of
-//   |vt| are one load).
-//   transfer to particles: 884,736 binary32 quadratic 40 with four; 1,404,928:
-//   64 and 65; 2,097,152: 101 and 90.  The others (two or three wavefronts per SIMD by their
-//   registers, or small 2D tiles) keep four: cubic 9.0M 727 against 735, 2D
-//   1.19M 49 against 69, binary64 cubic 1.12M 167 against 178.
+// How many wavefronts take a tile in the key pass, the transfer to particles and
+// the grid update.  The results are the same bits.
+//
+// Key pass and transfer to particles: a tile's chain of loads and chunks is its
+// time while the chip has slots for every tile, and four wavefronts share it; with
+// more tiles each wavefront's prologue (tables, grid velocities around the tile)
+// counts, and a tile of few chunks has no work for four.  What decides is the
+// number of tiles and of particles in them, which only the device knows, so the
+// kernels for n below the lines further down hold both and choose by the layout
+// they read: a block per tile up to one and a half times the tiles that the chip
+// holds blocks for (four to a CU, binary64 3D two), or where the tiles are well
+// filled.  Transfer to particles, a block per tile against a wavefront:
+//   3D binary32 quadratic: 1,331 tiles of 94 particles 23.7 and 25.3 us, 2,197 of
+//   114 32.6 and 27.2, 17,576 of 28 109 and 63, 2,197 of 455 46.7 and 50.0;
+//   cubic: 5,832 tiles of 411 134 and 148, 17,576 of 57 168 and 110;
+//   binary64 quadratic: 729 of 171 26.0 and 29.8, 1,331 of 94 31.8 and 26.8, 2,197
+//   of 455 85 and 93;
+//   2D binary32: 1,600 of 31 16.3 and 13.2, 3,969 of 126 22.1 and 19.0; 3,969 of
+//   252 that move by a fiftieth of a cell a step 30.6 and 27.4, but the elastic
+//   disk's (about 240 to a tile, large adaptive steps) 49 and 73: a mover's loads
+//   depend on each other.
+//   Key pass and the passes after it: 17,576 of 28 113 and 89, 1,331 of 188 21.6
+//   and 25.5.
+//   In a batch the scenes share the chip, each with twice its part of the limit (a
+//   batch's scenes are of many sizes): 128 scenes of 216 tiles of 19 particles 567 us
+//   a step with a wavefront per tile and 713 with a block, 64 2D scenes of 324 tiles
+//   of 62 236 and 268, 24 bodies of 8 particles per cell 152 and 128.
+__host__ __device__ constexpr bool tiles_within(uint32_t tiles, uint32_t scenes, uint32_t limit) {
+    return (uint64_t)tiles * scenes <= (scenes > 1u ? 2u * limit : limit);
+}
+template <typename T, int DIM>
+__host__ __device__ constexpr bool block_per_tile(uint32_t tiles, uint32_t live, uint32_t scenes) {
+    return tiles_within(tiles, scenes, sizeof(T) == 8 && DIM == 3 ? 768u : 1536u) ||
+           (uint64_t)live >= (uint64_t)tiles * (DIM == 3 ? 256u : 192u);
+}
+// Above these particle counts the kernels that hold both are the slower ones even
+// where they choose well:
+//   key pass (a wavefront holds the offsets of eight chunks): 512,000 particles 13
+//   us with four, 16 with one; 884,736 21 and 17; 2D 1.19M 29 and 23; cubic 9.0M
+//   235 and 163.
+//   transfer to particles, binary32 3D quadratic and multilinear: 884,736 40 with
+//   four; 1,404,928 64 and 65; 2,097,152 101 and 90: little between them below 1.4M.  The others
+//   (two or three wavefronts per SIMD by their registers, or small 2D tiles) keep
+//   the choice at every size: cubic 9.0M 727 against 735 with one.
 constexpr int key_waves(int64_t n) { return n >= ((int64_t)1 << 19) ? 1 : 4; }
 template <typename T, int DIM, int DEG>
 constexpr bool g2p_waves_choice() {
@@ -31,13 +61,16 @@ constexpr int g2p_waves(int64_t n) {
     return g2p_waves_choice<T, DIM, DEG>() && n >= ((int64_t)1 << 20) ? 1 : 4;
 }
 
-//   grid update (a tile at an edge of the body updates up to 2^dim node tiles,
-//   one after another by one wavefront): 227k binary32 quadratic 6.2 with four
-//   against 11.7, 2.1M 20.1 against 21.2, 2D 12k 3.5 against 4.5; cubic 9.0M 81
-//   against 62, 19M in 512 bodies 296 against 231, 2D 1.19M 7.7 against 6.8.
-template <int DIM>
-constexpr int grid_waves(int64_t n) {
-    return n >= ((int64_t)1 << (DIM == 3 ? 22 : 20)) ? 1 : 4;
+// Grid update: a tile at an edge of the body updates up to 2^dim node tiles, one
+// after another by one wavefront; four share them until the chip is full of tiles,
+// later where a node's sums are many registers.  Plain binary32 3D quadratic, four
+// wavefronts against one: 1,331 tiles 9.5 and 13.9 us, 2,197 11.2 and 15.0, 4,913
+// 16.0 and 12.4, 32,768 80 and 48; compensated: the cube of 4,913 20.1 and 21.2,
+// 21,952 72 and 55; binary64 cubic: 4,913 19.6 and 18.9, 9,261 33 and 31; 2D: 1,024
+// 6.3 and 6.4, 3,969 10.0 and 9.1; 64 scenes of 64 16.5 and 10.0.
+template <typename T, int DIM, bool COMP>
+__host__ __device__ constexpr uint32_t grid_waves(uint32_t tiles, uint32_t scenes) {
+    return tiles_within(tiles, scenes, DIM == 2 ? 2048u : (sizeof(T) == 8 || COMP ? 5120u : 3072u)) ? 4u : 1u;
 }
 // Runs f with the wavefronts per tile as a compile-time constant.
 template <bool CHOICE, typename F>
@@ -109,7 +142,7 @@ void launch_p2g(const Parts<T> &P, const BinLists &cur, const TileTables &tab,
 
 template <typename T, int DIM, int DEG, bool COMP>
 void launch_grid_update(const BinLists &cur, const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm,
-                        int64_t n, int64_t max_records, hipStream_t st);
+                        int64_t max_records, hipStream_t st);
 
 // New keys of the particles of layout `cur` after G2P (first pass of
 // apic_g2p): stayer counts per key, movers' keys and ranks, dead ranks.
@@ -149,7 +182,7 @@ void launch_p2g_batch(const SceneDesc<T> *descs, const int32_t *start, int n, in
                       hipStream_t st);
 template <typename T, int DIM, int DEG, bool COMP>
 void launch_grid_update_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
-                              int blocks, int waves, hipStream_t st);
+                              int blocks, hipStream_t st);
 template <typename T, int DIM, int DEG>
 void launch_bin_keys_moved_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
                                  int blocks, int waves, hipStream_t st);

@@ -161,8 +161,10 @@ __device__ __forceinline__ int nearest_node(const T (&w)[DEG + 1]) {
 // With a margin for rounding; ABS: and for that of a coordinate of up to n
 // cells.  (Per tile and axis, not over the whole grid: the fewer particles are
 // near enough to a key boundary to be resolved.)
-template <typename T, int DIM, bool ABS>
-__device__ __forceinline__ void tile_reach(uint32_t t, const GridState<T> &g, const StepParams<T> &prm, T *reach) {
+// In two parts: the load of the bounds, to be issued before the tile's others, and
+// the reach from them, to be formed when those are under way.
+template <typename T, int DIM>
+__device__ __forceinline__ float4 load_bounds(uint32_t t, const GridState<T> &g) {
     const int lane = lane_id();
     int64_t tau = 0, mul = 1;
     bool ok = lane < (1 << DIM);
@@ -176,11 +178,16 @@ __device__ __forceinline__ void tile_reach(uint32_t t, const GridState<T> &g, co
         tau += (int64_t)c * mul;
         mul *= n;
     }
-    const float4 v4 = ok ? ((const float4 *)g.vmax)[tau] : float4{0.f, 0.f, 0.f, 0.f};
+    float4 v4{0.f, 0.f, 0.f, 0.f};
+    if (ok) v4 = ((const float4 *)g.vmax)[tau];
+    return v4;
+}
+template <typename T, int DIM, bool ABS>
+__device__ __forceinline__ void tile_reach(const float4 &v4, const GridState<T> &g, const StepParams<T> &prm, T *reach) {
     const float vm[3] = {v4.x, v4.y, v4.z};
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        uint32_t x = ok ? __float_as_uint(vm[a]) : 0u;  // bits order as the values
+        uint32_t x = __float_as_uint(vm[a]);  // bits order as the values
         // over the first 2^DIM lanes: within the pairs, the quad, its neighbour
         uint32_t y = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xf, 0xf, true);
         x = x > y ? x : y;
@@ -225,11 +232,10 @@ struct VtRegion {
     __device__ static constexpr int at(int x, int y, int z) { return x + SY * y + SZ * z; }
 };
 
-// Stages them, the corners c with c mod parts == part (the wavefronts of a block
+// Stages them, the corners c with c mod PARTS == part (the wavefronts of a block
 // share the work).
-template <typename T, int DIM>
-__device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> &g, T *reg, int part = 0,
-                                                 int parts = 1) {
+template <typename T, int DIM, int PARTS = 1>
+__device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> &g, T *reg, int part = 0) {
     using R = VtRegion<DIM>;
     constexpr int TE = DIM == 3 ? 4 : 8;
     const int lane = lane_id();
@@ -244,8 +250,8 @@ __device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> 
     }
     local_coords<DIM>(lane, lc);
 #pragma unroll
-    for (int corner = 0; corner < (1 << DIM); ++corner) {
-        if (corner % parts != part) continue;
+    for (int c0 = 0; c0 < (1 << DIM); c0 += PARTS) {
+        const int corner = c0 + (PARTS > 1 ? part : 0);
         bool ok = true;
         int64_t tau = 0, mul = 1;
         int rc[3] = {0, 0, 0};
@@ -261,6 +267,14 @@ __device__ __forceinline__ void stage_velocities(uint32_t t, const GridState<T> 
 #pragma unroll
         for (int k = 0; k < DIM; ++k) reg[k * R::SIZE + idx] = ok ? g.vt[k * G + tau * 64 + lane] : T(0);
     }
+}
+
+// All corners by one wavefront, PASSES groups of them one after another (the fewer
+// values in flight).
+template <typename T, int DIM, int PASSES>
+__device__ __forceinline__ void stage_all(uint32_t t, const GridState<T> &g, T *reg) {
+#pragma unroll 1
+    for (int h = 0; h < PASSES; ++h) stage_velocities<T, DIM, PASSES>(t, g, reg, h);
 }
 
 // Occupancy target: binary32 3D quadratic and cubic fit 128 registers (4 waves

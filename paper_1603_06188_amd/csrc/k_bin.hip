@@ -184,8 +184,9 @@ void launch_copy_back_batch(const SceneDesc<T> *descs, const int32_t *start, int
 // (bucket_tables, finish_layout)
 __global__ __launch_bounds__(256) void k_bin_finalize(BinLists nxt, BinLists other) {
     __shared__ BucketTables tables;
-    bucket_tables(nxt, tables);
-    finish_layout(nxt, other, tables, blockIdx.x, gridDim.x);
+    __shared__ uint32_t bpre[kBuckets + 1];
+    bucket_tables(nxt, tables, bpre);
+    finish_layout(nxt, other, tables, bpre, blockIdx.x, gridDim.x);
 }
 
 void launch_bin_finalize(const BinLists &nxt, const BinLists &other, int64_t max_records, hipStream_t st) {
@@ -197,8 +198,9 @@ __global__ __launch_bounds__(256) void k_bin_finalize_batch(const SceneDesc<T> *
                                                             int k) {
     const BatchStep<T> b = batch_step<T>(descs, start, n, k, blockIdx.x);
     __shared__ BucketTables tables;
-    bucket_tables(b.nxt, tables);
-    finish_layout(b.nxt, b.cur, tables, b.blk, b.nblk);
+    __shared__ uint32_t bpre[kBuckets + 1];
+    bucket_tables(b.nxt, tables, bpre);
+    finish_layout(b.nxt, b.cur, tables, bpre, b.blk, b.nblk);
 }
 
 template <typename T>
@@ -240,9 +242,10 @@ __global__ __launch_bounds__(256) void k_bin_place(int64_t n, BinLists nxt, BinL
     uint32_t base;
     if constexpr (FINISH) {
         __shared__ BucketTables tables;
-        bucket_tables(nxt, tables);
-        finish_layout(nxt, other, tables, blockIdx.x, gridDim.x);
-        base = tables.bpre[b];
+        __shared__ uint32_t bpre[kBuckets + 1];
+        bucket_tables(nxt, tables, bpre);
+        finish_layout(nxt, other, tables, bpre, blockIdx.x, gridDim.x);
+        base = bpre[b];
     } else {
         base = nxt.bpre[b];
     }

@@ -5,7 +5,8 @@
 //   F_p = (I + dt sum_i vt_i grad w_ip^T) F_p
 //   x_p = x_p + dt v_p          (cell index + offset)
 // Both passes take the listed tiles of the current layout, a wavefront or a
-// block of four per tile (key_waves, g2p_waves).
+// block of four per tile: SPLIT kernels choose by the layout (block_per_tile), the
+// others take a wavefront.
 // Pass 1 (k_bin_keys_moved) finds the particles whose key changes ("movers",
 // rare): each takes a place in its new key and is marked in a bit mask of its
 // old key's levels.  Pass 2 (k_g2p) stages the grid velocities around the tile
@@ -23,20 +24,47 @@
 
 namespace apic {
 
-// Waves per SIMD asked for: a wavefront per tile holds the offsets of eight
-// chunks (binary32: three).
-template <typename T, int WPT>
-constexpr int keys_min_waves() {
-    return WPT == 1 && sizeof(T) == 4 ? 3 : 1;
+// Tiles of a block that takes several: four, each a wavefront's; two where the grid
+// velocities around four would keep blocks off a CU (binary64 3D).
+template <typename T, int DIM, bool SPLIT>
+constexpr int keys_tiles() {
+    return SPLIT && sizeof(T) == 8 && DIM == 3 ? 2 : 4;
+}
+template <typename T, int DIM, int DEG, bool SPLIT>
+constexpr int g2p_tiles() {
+    return SPLIT && sizeof(T) == 8 && DIM == 3 && DEG == 1 ? 2 : 4;
 }
 
-// Waits for the wavefronts that work on a tile.
-template <int WPT>
-__device__ __forceinline__ void tile_sync() {
-    if constexpr (WPT == 1)
-        wave_lds_sync();
-    else
+// Waves per SIMD asked for: a wavefront per tile holds the offsets of eight
+// chunks (binary32: three).
+template <typename T, bool SPLIT>
+constexpr int keys_min_waves() {
+    return !SPLIT && sizeof(T) == 4 ? 3 : 1;
+}
+
+// Waits for the wavefronts that work on a tile (all of a block's, where there are
+// several).
+__device__ __forceinline__ void tile_sync(uint32_t wpt) {
+    if (wpt > 1u)
         __syncthreads();
+    else
+        wave_lds_sync();
+}
+
+// Work items of a pass over a layout: the tiles, a block each (`whole`) or TILES at a
+// time, 4 / TILES wavefronts each, then the chunks of dead particles four at a time.
+struct TileItems {
+    bool whole;
+    uint32_t tiles, dead, count;
+};
+template <typename T, int DIM, bool SPLIT, int TILES>
+__device__ __forceinline__ TileItems tile_items(const TileWalk &walk, int64_t n, uint32_t scenes) {
+    TileItems it;
+    it.whole = SPLIT && block_per_tile<T, DIM>(walk.nrec, walk.live, scenes);
+    it.tiles = it.whole ? walk.nrec : (walk.nrec + TILES - 1u) / TILES;
+    it.dead = dead_chunks(n, walk.live);
+    it.count = it.tiles + (it.dead + 3u) / 4u;
+    return it;
 }
 
 // --- pass 1: new keys ---------------------------------------------------------------------
@@ -99,144 +127,159 @@ __device__ __forceinline__ void resolve_near(const Parts<T> &P, const GridState<
 
 constexpr uint32_t kStayer = 0x80000000u;  // prank of a busy tile's stayer: its rank with this bit
 
-template <typename T, int DIM, int DEG, bool ABS, int WPT>
+template <typename T, int DIM, int DEG, bool ABS, bool SPLIT>
 __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur, const TileTables &ctab,
                                           const GridState<T> &g, const StepParams<T> &prm_in, const BinLists &nxt,
-                                          const BinScratch &sc, uint32_t blk, uint32_t nblk) {
+                                          const BinScratch &sc, uint32_t scenes, uint32_t blk, uint32_t nblk) {
     const StepParams<T> prm = with_step_dt(prm_in);
     using R = VtRegion<DIM>;
-    constexpr int TPB = 4 / WPT;          // tiles of a block
-    constexpr int U = kKeyChunks / WPT;   // chunks of a wavefront loaded together
-    __shared__ uint32_t lds_left[TPB][64];  // a bit per particle of a tile that is not busy
+    constexpr int U = SPLIT ? kKeyChunks / 4 : kKeyChunks;  // chunks of a wavefront loaded together
+    constexpr int TILES = keys_tiles<T, DIM, SPLIT>();
+    __shared__ uint32_t lds_left[TILES][64];  // a bit per particle of a tile that is not busy
     static_assert(kMaxLevels * 64 <= 64 * 32, "a bit for each");
     __shared__ uint32_t lds_queue[4][64 * U];
-    __shared__ T lds_vt[TPB * DIM * R::SIZE];
+    __shared__ T lds_vt[TILES * DIM * R::SIZE];
     const int lane = lane_id(), wave = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int tl = wave / WPT, wv = wave % WPT;  // tile of the block, wavefront of the tile
-    uint32_t *left = lds_left[tl], *queue = lds_queue[wave];
-    T *reg = lds_vt + tl * (DIM * R::SIZE);
+    uint32_t *queue = lds_queue[wave];
     const TileWalk walk = tile_walk(cur);
-    const uint32_t dead = dead_chunks(P.n, walk.live);
-    const uint32_t items = walk.nrec + (dead + WPT - 1) / WPT;
-    for (uint32_t r = blk * TPB + (uint32_t)tl; r < items; r += nblk * TPB) {
-        if (r >= walk.nrec) {
-            // particles that could not be binned stay in the dead region
-            const int64_t p = (int64_t)walk.live + ((int64_t)(r - walk.nrec) * WPT + wv) * 64 + lane;
-            if (p < P.n) sc.prank[p] = atomicAdd(nxt.ctr + kCtrDead, 1u);
-            continue;
-        }
-        uint32_t start, cnt, maxc, kstart;
-        const uint32_t t = tile_of_record(walk, r, cur, ctab, start, cnt, maxc, kstart);
-        const uint32_t total = ctab.tcount[t];
-        const bool busy = maxc > (uint32_t)kMaxLevels;
-        int origin[3] = {0, 0, 0};
-        tile_origin<DIM>(t, g.d.TN, origin);
-        T reach[DIM];
-        tile_reach<T, DIM, ABS>(t, g, prm, reach);
-        // the tile is claimed in the new layout now (its particles nearly all
-        // stay) and appended at the end, so the claim's round trip overlaps
-        // the tile's loads; a tile all of whose particles leave is listed
-        // empty, which every later pass takes as a tile without particles
-        uint32_t claim = nxt.gen;
-        if (wv == 0) {
-            left[lane] = 0u;
-            if (lane == 0 && total > 0u) claim = atomicExch(nxt.tile_gen + t, nxt.gen);
-            if (busy)
-                for (uint32_t j = 0; j < cnt; ++j) sc.pkey[kstart + j] = t * 64 + (uint32_t)lane;
-        }
-        bool staged = WPT > 1;  // one wavefront: grid velocities around the tile on first use
-        if (WPT > 1) stage_velocities<T, DIM>(t, g, reg, wv, WPT);
-        tile_sync<WPT>();
-        for (uint32_t c0 = 64u * (uint32_t)wv; c0 < total; c0 += 64u * kKeyChunks) {
-            T off[U][DIM];
-            // every load of the group in flight, then its chunks are classified
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t i = c0 + (uint32_t)(64 * WPT * u + lane);
-                if (i < total) {
-                    const uint32_t pb = (start + i) * (uint32_t)sizeof(T);
-#pragma unroll
-                    for (int a = 0; a < DIM; ++a) off[u][a] = *scalar_plane(P.off + a * P.s, pb);
-                }
+    const TileItems items = tile_items<T, DIM, SPLIT, TILES>(walk, P.n, scenes);
+    const auto walk_tiles = [&](auto w) {
+        // the wavefronts of a tile, which of them this one is, and the tile of the block
+        constexpr bool whole = decltype(w)::value;
+        constexpr uint32_t wpt = whole ? 4u : 4u / TILES;
+        const uint32_t wv = (uint32_t)wave & (wpt - 1u);
+        const int tl = whole ? 0 : wave / (4 / TILES);
+        uint32_t *left = lds_left[tl];
+        T *reg = lds_vt + tl * (DIM * R::SIZE);
+        for (uint32_t it = blk; it < items.count; it += nblk) {
+            if (it >= items.tiles) {
+                // particles that could not be binned stay in the dead region
+                const int64_t p = (int64_t)walk.live + ((int64_t)(it - items.tiles) * 4 + wave) * 64 + lane;
+                if (p < P.n) sc.prank[p] = atomicAdd(nxt.ctr + kCtrDead, 1u);
+                continue;
             }
-            uint32_t queued = 0;
+            const uint32_t r = whole ? it : it * TILES + (uint32_t)tl;
+            const bool have = whole || r < walk.nrec;
+            if (wpt == 1u && !have) continue;
+            uint32_t start, cnt, maxc, kstart;
+            const uint32_t t = tile_of_record(walk, have ? r : 0u, cur, ctab, start, cnt, maxc, kstart);
+            uint32_t total = ctab.tcount[t];
+            if (!have) total = cnt = maxc = 0u;  // no second tile: the wavefronts only wait for the others
+            const bool busy = maxc > (uint32_t)kMaxLevels;
+            int origin[3] = {0, 0, 0};
+            tile_origin<DIM>(t, g.d.TN, origin);
+            const float4 bounds = load_bounds<T, DIM>(t, g);
+            // the tile is claimed in the new layout now (its particles nearly all
+            // stay) and appended at the end, so the claim's round trip overlaps
+            // the tile's loads; a tile all of whose particles leave is listed
+            // empty, which every later pass takes as a tile without particles
+            uint32_t claim = nxt.gen;
+            if (wv == 0) {
+                left[lane] = 0u;
+                if (lane == 0 && total > 0u) claim = atomicExch(nxt.tile_gen + t, nxt.gen);
+                if (busy)
+                    for (uint32_t j = 0; j < cnt; ++j) sc.pkey[kstart + j] = t * 64 + (uint32_t)lane;
+            }
+            bool staged = wpt > 1u;  // one wavefront: grid velocities around the tile on first use
+            if constexpr (wpt > 1u) stage_velocities<T, DIM, (int)wpt>(t, g, reg, (int)wv);
+            tile_sync(wpt);
+            for (uint32_t c0 = 64u * wv; c0 < total; c0 += 64u * U * wpt) {
+                T off[U][DIM];
+                // every load of the group in flight, then its chunks are classified
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const uint32_t i = c0 + (uint32_t)(64 * WPT * u + lane);
-                if (c0 + (uint32_t)(64 * WPT * u) >= total) break;
-                bool near = false;
-                if (i < total) {
-                    T o[DIM];
-                    if constexpr (ABS) {
-                        int ci[3];
-                        particle_cells<T, DIM, true>(0u, off[u], g.inv_dx, ci, o);
-                    } else {
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t i = c0 + 64u * wpt * u + (uint32_t)lane;
+                    if (i < total) {
+                        const uint32_t pb = (start + i) * (uint32_t)sizeof(T);
 #pragma unroll
-                        for (int a = 0; a < DIM; ++a) o[a] = off[u][a];
+                        for (int a = 0; a < DIM; ++a) off[u][a] = *scalar_plane(P.off + a * P.s, pb);
                     }
-                    near = !keeps_key<T, DIM, DEG>(o, reach);
                 }
-                const uint64_t nm = ballot(near);
-                if (near) queue[queued + (uint32_t)popc64(nm & lanes_below(lane))] = i;
-                queued += (uint32_t)popc64(nm);
-            }
-            if (queued > 0u && !staged) {
-                stage_velocities<T, DIM>(t, g, reg);
-                staged = true;
-            }
-            wave_lds_sync();
-            for (uint32_t q0 = 0; q0 < queued; q0 += 64u) {
-                const uint32_t take = queued - q0 < 64u ? queued - q0 : 64u;
-                resolve_near<T, DIM, DEG, ABS>(P, g, prm, nxt, sc, queue + q0, take, t, start, origin, reg, left, busy);
-            }
-            wave_lds_sync();
-        }
-        tile_sync<WPT>();
-        if (wv == 0) {
-            uint32_t stay;
-            if (!busy) {
-                // the marks by key and level
-                uint32_t gone = 0u;
-                if (ballot(left[lane] != 0u)) {
-                    uint32_t level = 0;
-                    for (uint32_t j0 = 0; j0 < maxc; j0 += 4) {
-                        // four marks in flight; an absent level reads one that counts for nothing
-                        uint32_t word[4], at[4];
+                T reach[DIM];
+                tile_reach<T, DIM, ABS>(bounds, g, prm, reach);
+                uint32_t queued = 0;
 #pragma unroll
-                        for (uint32_t u = 0; u < 4; ++u) {
-                            const uint64_t mask = ballot(cnt > j0 + u);
-                            at[u] = level + (uint32_t)popc64(mask & lanes_below(lane));
-                            word[u] = left[(at[u] >> 5) & 63u];
-                            level += (uint32_t)popc64(mask);
+                for (int u = 0; u < U; ++u) {
+                    const uint32_t i = c0 + 64u * wpt * u + (uint32_t)lane;
+                    if (c0 + 64u * wpt * u >= total) break;
+                    bool near = false;
+                    if (i < total) {
+                        T o[DIM];
+                        if constexpr (ABS) {
+                            int ci[3];
+                            particle_cells<T, DIM, true>(0u, off[u], g.inv_dx, ci, o);
+                        } else {
+#pragma unroll
+                            for (int a = 0; a < DIM; ++a) o[a] = off[u][a];
                         }
-#pragma unroll
-                        for (uint32_t u = 0; u < 4; ++u)
-                            if (cnt > j0 + u) gone |= ((word[u] >> (at[u] & 31u)) & 1u) << (j0 + u);
+                        near = !keeps_key<T, DIM, DEG>(o, reach);
                     }
+                    const uint64_t nm = ballot(near);
+                    if (near) queue[queued + (uint32_t)popc64(nm & lanes_below(lane))] = i;
+                    queued += (uint32_t)popc64(nm);
                 }
-                stay = cnt - (uint32_t)__popc(gone);
-                ctab.kmov[(int64_t)t * 64 + lane] = gone;
-            } else {
-                // a busy tile's particles carry their key and rank themselves
-                stay = 0;
-                for (uint32_t j = 0; j < cnt; ++j)
-                    if (sc.pkey[kstart + j] == t * 64 + (uint32_t)lane) sc.prank[kstart + j] = kStayer | stay++;
+                if (queued > 0u && !staged) {
+                    stage_all<T, DIM, SPLIT ? 2 : 1>(t, g, reg);
+                    staged = true;
+                }
+                wave_lds_sync();
+                for (uint32_t q0 = 0; q0 < queued; q0 += 64u) {
+                    const uint32_t take = queued - q0 < 64u ? queued - q0 : 64u;
+                    resolve_near<T, DIM, DEG, ABS>(P, g, prm, nxt, sc, queue + q0, take, t, start, origin, reg, left, busy);
+                }
+                wave_lds_sync();
             }
-            sc.scount[(int64_t)t * 64 + lane] = stay;
-            if (lane == 0 && claim != nxt.gen) append_tile(t, nxt);
+            tile_sync(wpt);
+            if (wv == 0 && have) {
+                uint32_t stay;
+                if (!busy) {
+                    // the marks by key and level
+                    uint32_t gone = 0u;
+                    if (ballot(left[lane] != 0u)) {
+                        uint32_t level = 0;
+                        for (uint32_t j0 = 0; j0 < maxc; j0 += 4) {
+                            // four marks in flight; an absent level reads one that counts for nothing
+                            uint32_t word[4], at[4];
+#pragma unroll
+                            for (uint32_t u = 0; u < 4; ++u) {
+                                const uint64_t mask = ballot(cnt > j0 + u);
+                                at[u] = level + (uint32_t)popc64(mask & lanes_below(lane));
+                                word[u] = left[(at[u] >> 5) & 63u];
+                                level += (uint32_t)popc64(mask);
+                            }
+#pragma unroll
+                            for (uint32_t u = 0; u < 4; ++u)
+                                if (cnt > j0 + u) gone |= ((word[u] >> (at[u] & 31u)) & 1u) << (j0 + u);
+                        }
+                    }
+                    stay = cnt - (uint32_t)__popc(gone);
+                    ctab.kmov[(int64_t)t * 64 + lane] = gone;
+                } else {
+                    // a busy tile's particles carry their key and rank themselves
+                    stay = 0;
+                    for (uint32_t j = 0; j < cnt; ++j)
+                        if (sc.pkey[kstart + j] == t * 64 + (uint32_t)lane) sc.prank[kstart + j] = kStayer | stay++;
+                }
+                sc.scount[(int64_t)t * 64 + lane] = stay;
+                if (lane == 0 && claim != nxt.gen) append_tile(t, nxt);
+            }
+            if (wpt == 1u) wave_lds_sync();
         }
-        if (WPT == 1) wave_lds_sync();
-    }
+    };
+    if (items.whole)
+        walk_tiles(std::true_type{});
+    else
+        walk_tiles(std::false_type{});
 }
 
-template <typename T, int DIM, int DEG, bool ABS, int WPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(keys_min_waves<T, WPT>()))) void k_bin_keys_moved(
+template <typename T, int DIM, int DEG, bool ABS, bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(keys_min_waves<T, SPLIT>()))) void k_bin_keys_moved(
     Parts<T> P, BinLists cur, TileTables ctab, GridState<T> g, StepParams<T> prm, BinLists nxt, BinScratch sc) {
-    keys_body<T, DIM, DEG, ABS, WPT>(P, cur, ctab, g, prm, nxt, sc, blockIdx.x, gridDim.x);
+    keys_body<T, DIM, DEG, ABS, SPLIT>(P, cur, ctab, g, prm, nxt, sc, 1u, blockIdx.x, gridDim.x);
 }
 
-template <typename T, int DIM, int DEG, bool QUEUE, int WPT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 : keys_min_waves<T, WPT>()))) void k_bin_keys_moved_batch(
+template <typename T, int DIM, int DEG, bool QUEUE, bool SPLIT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 : keys_min_waves<T, SPLIT>()))) void k_bin_keys_moved_batch(
     const SceneDesc<T> *descs, const int32_t *start, int n, int k, BatchQueue q) {
     batch_items<QUEUE>(q, [&](uint32_t it) {
         const BatchStep<T> b = batch_step<T>(descs, start, n, k, it);
@@ -249,7 +292,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
         g.vmax = tile_bounds(table_struct(d.tab[b.sp.nxt].lvl_off));
         const StepParams<T> prm = table_struct(d.prm);
         const BinScratch sc = table_struct(d.sc);
-        keys_body<T, DIM, DEG, false, WPT>(P, b.cur, ctab, g, prm, b.nxt, sc, b.blk, b.nblk);
+        keys_body<T, DIM, DEG, false, SPLIT>(P, b.cur, ctab, g, prm, b.nxt, sc, (uint32_t)n, b.blk, b.nblk);
     });
 }
 
@@ -257,12 +300,12 @@ template <typename T, int DIM, int DEG>
 void launch_bin_keys_moved_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
                                  int blocks, int waves, hipStream_t st) {
     with_tile_waves<true>(waves, [&](auto w) {
-        constexpr int WPT = decltype(w)::value;
+        constexpr bool SPLIT = decltype(w)::value == 4;
         if (q.ctr)
-            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, true, WPT>), dim3((unsigned)blocks), dim3(256), 0,
+            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, true, SPLIT>), dim3((unsigned)blocks), dim3(256), 0,
                                st, descs, start, n, k, q);
         else
-            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, false, WPT>), dim3((unsigned)blocks), dim3(256), 0,
+            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, false, SPLIT>), dim3((unsigned)blocks), dim3(256), 0,
                                st, descs, start, n, k, q);
     });
 }
@@ -272,10 +315,10 @@ void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTab
                            const StepParams<T> &prm, const BinLists &nxt, const BinScratch &sc, int64_t max_records,
                            hipStream_t st) {
     with_tile_waves<true>(key_waves(P.n), [&](auto w) {
-        constexpr int WPT = decltype(w)::value;
-        const int64_t items = max_records + (P.n + 64 * WPT - 1) / (64 * WPT), tpb = 4 / WPT;
-        const int64_t blocks = std::min<int64_t>(std::max<int64_t>((items + tpb - 1) / tpb, 1), 4096);
-        hipLaunchKernelGGL((k_bin_keys_moved<T, DIM, DEG, ABS, WPT>), dim3((unsigned)blocks), dim3(256), 0, st, P, cur,
+        constexpr bool SPLIT = decltype(w)::value == 4;
+        const int64_t items = (SPLIT ? max_records : (max_records + 3) / 4) + (P.n + 255) / 256;
+        const int64_t blocks = std::min<int64_t>(std::max<int64_t>(items, 1), 4096);
+        hipLaunchKernelGGL((k_bin_keys_moved<T, DIM, DEG, ABS, SPLIT>), dim3((unsigned)blocks), dim3(256), 0, st, P, cur,
                            ctab, g, prm, nxt, sc);
     });
 }
@@ -298,51 +341,61 @@ void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTab
 // instantiation, so that fixed steps carry none of it.
 // FINISH: the new layout's bucket tables are found here, and its records numbered
 // (g2p_finishes).
-template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int WPT, bool FINISH>
+template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, bool SPLIT, bool FINISH>
 __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur,
                                          const TileTables &ctab, const BinLists &nxt, const TileTables &ntab,
                                          const BinScratch &sc, const GridState<T> &g, const StepParams<T> &prm_in,
-                                         uint32_t blk, uint32_t nblk) {
+                                         uint32_t scenes, uint32_t blk, uint32_t nblk) {
     const StepParams<T> prm = ADAPT ? with_step_dt(prm_in) : prm_in;
     using R = VtRegion<DIM>;
-    constexpr int TPB = 4 / WPT;  // tiles of a block
-    __shared__ T lds_vt[TPB * DIM * R::SIZE];
+    // the grid velocities around the tiles; before them (FINISH) the bucket tables
+    constexpr size_t VT = g2p_tiles<T, DIM, DEG, SPLIT>() * DIM * R::SIZE * sizeof(T);
+    __shared__ __attribute__((aligned(16))) char lds_all[FINISH && sizeof(BucketTables) > VT ? sizeof(BucketTables) : VT];
+    T *lds_vt = (T *)lds_all;
+    __shared__ uint32_t lds_bpre[FINISH ? kBuckets + 1 : 1];
+    constexpr int TILES = g2p_tiles<T, DIM, DEG, SPLIT>();
     __shared__ uint16_t lds_slot[4][64];  // key | level << 6 of the chunk's particles
-    __shared__ uint32_t lds_gone[TPB][64], lds_nlo[TPB][kMaxLevels];
-    __shared__ uint64_t lds_nmask[TPB][kMaxLevels];
+    __shared__ uint32_t lds_gone[TILES][64], lds_nlo[TILES][kMaxLevels];
+    __shared__ uint64_t lds_nmask[TILES][kMaxLevels];
     const int lane = lane_id(), wave = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int tl = wave / WPT, wv = wave % WPT;  // tile of the block, wavefront of the tile
-    T *reg = lds_vt + tl * (DIM * R::SIZE);
     uint16_t *slot = lds_slot[wave];
-    uint32_t *gone = lds_gone[tl], *nlo = lds_nlo[tl];
-    uint64_t *nmask = lds_nmask[tl];
     const TileWalk walk = tile_walk(cur);
-    __shared__ std::conditional_t<FINISH, BucketTables, int> lds_tables;
     if constexpr (FINISH) {
-        bucket_tables(nxt, lds_tables);
+        BucketTables &tables = *(BucketTables *)lds_all;
+        bucket_tables(nxt, tables, lds_bpre);
         // from the last block on: those of a launch sized for the capacity have no
         // tile, and the records end with the short ones
-        finish_layout(nxt, cur, lds_tables, nblk - 1u - blk, nblk);
+        finish_layout(nxt, cur, tables, lds_bpre, nblk - 1u - blk, nblk);
+        __syncthreads();
     }
     const auto base_at = [&](uint32_t b) {
         if constexpr (FINISH)
-            return lds_tables.bpre[b];
+            return lds_bpre[b];
         else
             return nxt.bpre[b];
     };
     const uint32_t live_nxt = base_at(kBuckets);
     const T dt_inv_dx = prm.dt * g.inv_dx, gs = prm.dt * g.inv_dx;
-    const uint32_t dead = dead_chunks(src.n, walk.live);
-    const uint32_t items = walk.nrec + (dead + WPT - 1) / WPT;
+    const TileItems items = tile_items<T, DIM, SPLIT, TILES>(walk, src.n, scenes);
+    // the wavefronts of a tile, which of them this one is, and the tile of the block
+    const bool whole = items.whole;
+    const uint32_t wpt = whole ? 4u : 4u / TILES, wv = (uint32_t)wave & (wpt - 1u);
+    const int tl = whole ? 0 : wave / (4 / TILES);
+    T *reg = lds_vt + tl * (DIM * R::SIZE);
+    uint32_t *gone = lds_gone[tl], *nlo = lds_nlo[tl];
+    uint64_t *nmask = lds_nmask[tl];
     const bool ids = src.id != nullptr;
     T cmax = T(0);  // CFL bound of the particles this lane writes (when asked)
-    for (uint32_t r = blk * TPB + (uint32_t)tl; r < items; r += nblk * TPB) {
-        if (r >= walk.nrec) {
-            const uint32_t c = (r - walk.nrec) * WPT + (uint32_t)wv;
-            if (c < dead) carry_dead<T, DIM>(src, dst, sc, walk.live, live_nxt, c);
+    for (uint32_t it = blk; it < items.count; it += nblk) {
+        if (it >= items.tiles) {
+            const uint32_t c = (it - items.tiles) * 4u + (uint32_t)wave;
+            if (c < items.dead) carry_dead<T, DIM>(src, dst, sc, walk.live, live_nxt, c);
             continue;
         }
-        const uint32_t t = cur.rec_tile[r];
+        const uint32_t r = whole ? it : it * TILES + (uint32_t)tl;
+        const bool have = r < walk.nrec;
+        if (TILES == 4 && !have) continue;
+        const uint32_t t = cur.rec_tile[have ? r : 0u];
         const uint32_t start = walk.bbase[bucket_of(t)] + ctab.off[t], total = ctab.tcount[t], maxc = ctab.maxc[t];
         const uint32_t cnt = ctab.kcount[(int64_t)t * 64 + lane];
         const uint32_t nbase = base_at(bucket_of(t)) + ntab.off[t];  // the tile's place in the new layout
@@ -356,22 +409,28 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
         // which now start mid-line), and the next step's transfer to grid
         // reads lines written whole.  The first chunk is in flight while the
         // grid velocities are staged and the tables filled.
-        const uint32_t head = nbase & 31u, span = total + head, first = start - head;
-        uint32_t e = (uint32_t)(wv * 64 + lane);
+        // (no second tile: nothing to do, but the waits for the others)
+        const uint32_t head = nbase & 31u, span = have ? total + head : 0u, first = start - head;
+        uint32_t e = wv * 64u + (uint32_t)lane;
         G2PRaw<T, DIM> raw;
         if (e >= head && e < span) g2p_load<T, DIM, ABS>(src, first + e, raw);
-        stage_velocities<T, DIM>(t, g, reg, wv, WPT);
+        if (__builtin_expect(whole, 1))
+            stage_velocities<T, DIM, 4>(t, g, reg, wave);
+        else if (TILES == 2)
+            stage_velocities<T, DIM, 2>(t, g, reg, (int)wv);
+        else
+            stage_all<T, DIM, 1>(t, g, reg);
         if (wv == 0) gone[lane] = ctab.kmov[(int64_t)t * 64 + lane];
-        if (wv == WPT - 1 && lane < kMaxLevels) {
+        if (wv == wpt - 1u && lane < kMaxLevels) {
             nlo[lane] = nbase + ntab.lvl_off[(int64_t)t * kMaxLevels + lane];
             nmask[lane] = ntab.lvl_mask[(int64_t)t * kMaxLevels + lane];
         }
-        tile_sync<WPT>();
+        tile_sync(wpt);
         uint32_t lv = 0, lv_off = 0;  // level the next chunk may start in, its first particle
-        for (uint32_t c0 = (uint32_t)wv * 64u; c0 < span; c0 += 64u * WPT, e += 64u * WPT) {
+        for (uint32_t c0 = wv * 64u; c0 < span; c0 += 64u * wpt, e += 64u * wpt) {
             // the wavefront's next chunk is in flight while this one is computed
             G2PRaw<T, DIM> raw_n;
-            if (e + 64u * WPT < span) g2p_load<T, DIM, ABS>(src, first + e + 64u * WPT, raw_n);
+            if (e + 64u * wpt < span) g2p_load<T, DIM, ABS>(src, first + e + 64u * wpt, raw_n);
             // key and level of the chunk's particles from the levels it meets
             while (lv < maxc && !busy) {
                 const uint64_t mask = ballot(cnt > lv);
@@ -425,20 +484,21 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
             raw = raw_n;
             wave_lds_sync();
         }
-        tile_sync<WPT>();
+        tile_sync(wpt);
     }
     if constexpr (ADAPT) cfl_raise(g.cfl, blk * 4 + (uint32_t)wave, (double)cmax);
     (void)cmax;
 }
 
-template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int WPT, bool FINISH>
+template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, bool SPLIT, bool FINISH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADAPT && DIM == 3 ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p(
     Parts<T> src, Parts<T> dst, BinLists cur, TileTables ctab, BinLists nxt, TileTables ntab, BinScratch sc,
     GridState<T> g, StepParams<T> prm) {
-    g2p_body<T, DIM, DEG, ADAPT, ABS, WPT, FINISH>(src, dst, cur, ctab, nxt, ntab, sc, g, prm, blockIdx.x, gridDim.x);
+    g2p_body<T, DIM, DEG, ADAPT, ABS, SPLIT, FINISH>(src, dst, cur, ctab, nxt, ntab, sc, g, prm, 1u, blockIdx.x,
+                                                    gridDim.x);
 }
 
-template <typename T, int DIM, int DEG, bool ADAPT, bool QUEUE, int WPT, bool FINISH>
+template <typename T, int DIM, int DEG, bool ADAPT, bool QUEUE, bool SPLIT, bool FINISH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p_batch(
     const SceneDesc<T> *descs, const int32_t *start, int n, int k, BatchQueue q) {
     batch_items<QUEUE>(q, [&](uint32_t it) {
@@ -452,8 +512,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
         const BinScratch sc = table_struct(d.sc);
         const GridState<T> g = table_struct(d.g);
         const StepParams<T> prm = table_struct(d.prm);
-        g2p_body<T, DIM, DEG, ADAPT, false, WPT, FINISH>(src, dst, b.cur, ctab, b.nxt, ntab, sc, g, prm, b.blk,
-                                                        b.nblk);
+        g2p_body<T, DIM, DEG, ADAPT, false, SPLIT, FINISH>(src, dst, b.cur, ctab, b.nxt, ntab, sc, g, prm, (uint32_t)n,
+                                                          b.blk, b.nblk);
     });
 }
 
@@ -471,19 +531,19 @@ void launch_g2p_batch(const SceneDesc<T> *descs, const int32_t *start, int n, in
                       bool adapt, int waves, bool finish, hipStream_t st) {
     const dim3 grid((unsigned)blocks), block(256);
     with_g2p_variant<T, DIM, DEG>(waves, finish, [&](auto w, auto f) {
-        constexpr int WPT = decltype(w)::value;
+        constexpr bool SPLIT = decltype(w)::value == 4;
         constexpr bool FINISH = decltype(f)::value;
         if (adapt && q.ctr)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, true, WPT, FINISH>), grid, block, 0, st, descs, start, n,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, true, SPLIT, FINISH>), grid, block, 0, st, descs, start, n,
                                k, q);
         else if (adapt)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, false, WPT, FINISH>), grid, block, 0, st, descs, start,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, false, SPLIT, FINISH>), grid, block, 0, st, descs, start,
                                n, k, q);
         else if (q.ctr)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, true, WPT, FINISH>), grid, block, 0, st, descs, start,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, true, SPLIT, FINISH>), grid, block, 0, st, descs, start,
                                n, k, q);
         else
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, false, WPT, FINISH>), grid, block, 0, st, descs, start,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, false, SPLIT, FINISH>), grid, block, 0, st, descs, start,
                                n, k, q);
     });
 }
@@ -564,18 +624,18 @@ void launch_g2p(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur, c
     Parts<T> s2 = src, d2 = dst;
     if (!src.id || !dst.id) s2.id = d2.id = nullptr;
     with_g2p_variant<T, DIM, DEG>(g2p_waves<T, DIM, DEG>(src.n), finish, [&](auto w, auto f) {
-        constexpr int WPT = decltype(w)::value;
+        constexpr bool SPLIT = decltype(w)::value == 4;
         constexpr bool FINISH = decltype(f)::value;
-        const int64_t items = max_records + (src.n + 64 * WPT - 1) / (64 * WPT), tpb = 4 / WPT;
-        const dim3 blocks((unsigned)std::min<int64_t>(std::max<int64_t>((items + tpb - 1) / tpb, 1), 4096));
+        const int64_t items = (SPLIT ? max_records : (max_records + 3) / 4) + (src.n + 255) / 256;
+        const dim3 blocks((unsigned)std::min<int64_t>(std::max<int64_t>(items, 1), 4096));
         if constexpr (!ABS) {
             if (g.cfl) {
-                hipLaunchKernelGGL((k_g2p<T, DIM, DEG, true, false, WPT, FINISH>), blocks, dim3(256), 0, st, s2, d2,
+                hipLaunchKernelGGL((k_g2p<T, DIM, DEG, true, false, SPLIT, FINISH>), blocks, dim3(256), 0, st, s2, d2,
                                    cur, ctab, nxt, ntab, sc, g, prm);
                 return;
             }
         }
-        hipLaunchKernelGGL((k_g2p<T, DIM, DEG, false, ABS, WPT, FINISH>), blocks, dim3(256), 0, st, s2, d2, cur, ctab,
+        hipLaunchKernelGGL((k_g2p<T, DIM, DEG, false, ABS, SPLIT, FINISH>), blocks, dim3(256), 0, st, s2, d2, cur, ctab,
                            nxt, ntab, sc, g, prm);
     });
 }

@@ -67,15 +67,17 @@ __device__ __forceinline__ void gather_node(const int *nc, const BinLists &gm, c
     for (int k = 0; k < NC; ++k) out[k] = COMP ? hi[k] + lo[k] : hi[k];
 }
 
-// Node tile tau is updated by exactly one wavefront: the one (of WPT, the node
-// tiles dealt to them in turn) of the first listed key tile, in the order e = 0, 1, ..., 2^DIM - 1, among the key tiles
-// tau - e whose slabs cover it.  In the interior every tile owns itself.
+// Node tile tau is updated by exactly one wavefront: the one (of grid_waves, the node
+// tiles dealt to them in turn) of the first listed key tile, in the order e = 0, 1,
+// ..., 2^DIM - 1, among the key tiles tau - e whose slabs cover it.  In the interior
+// every tile owns itself.
 // One load of 64 lanes (lane = corner c * 2^DIM + e) fetches the membership
 // tags and slab records of all key tiles around all 2^DIM candidate node
 // tiles t + c; they decide ownership and feed the slab gathers.
-template <typename T, int DIM, int DEG, bool COMP, int WPT>
+template <typename T, int DIM, int DEG, bool COMP>
 __device__ __forceinline__ void grid_update_body(const BinLists &cur, const Slabs<T> &slabs, const GridState<T> &g,
-                                                 const StepParams<T> &prm_in, uint32_t blk, uint32_t nblk) {
+                                                 const StepParams<T> &prm_in, uint32_t scenes, uint32_t blk,
+                                                 uint32_t nblk) {
     const StepParams<T> prm = with_step_dt(prm_in);
     using Gm = Geo<DIM, DEG>;
     constexpr int TE = Gm::TE, RN = Gm::RN, NC = Gm::NC, NCOR = 1 << DIM;
@@ -86,8 +88,9 @@ __device__ __forceinline__ void grid_update_body(const BinLists &cur, const Slab
     const int64_t G = g.d.G;
     const uint32_t nrec = cur.rpre[kBuckets];
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int wv = (int)(wave % WPT);
-    const WaveWalk ww = wave_walk<WPT>(blk, nblk, nrec);
+    const uint32_t wpt = grid_waves<T, DIM, COMP>(nrec, scenes);
+    const int wv = (int)(wave & (wpt - 1u));
+    const WaveWalk ww = wave_walk(wpt, blk, nblk, nrec);
     int lc[3] = {0, 0, 0};
     local_coords<DIM>(lane, lc);
     const int my_c = lane / NCOR, my_e = lane % NCOR;
@@ -131,7 +134,7 @@ __device__ __forceinline__ void grid_update_body(const BinLists &cur, const Slab
         for (int a = 0; a < DIM; ++a) own[a] = wave_uniform(ur[a]);
         const uint64_t lmask = ballot(listed);
         const uint64_t nmask = ballot(node_in && my_e == 0);
-        for (int c = wv; c < NCOR; c += WPT) {
+        for (int c = wv; c < NCOR; c += (int)wpt) {
             const uint32_t lst = (uint32_t)(lmask >> (c * NCOR)) & ((1u << NCOR) - 1u);
             // owned: node tile inside, and no listed key tile before e = c
             if (!((nmask >> (c * NCOR)) & 1ull) || (lst & ((1u << c) - 1u)) != 0u) continue;
@@ -224,13 +227,13 @@ __device__ __forceinline__ void grid_update_body(const BinLists &cur, const Slab
     }
 }
 
-template <typename T, int DIM, int DEG, bool COMP, int WPT>
+template <typename T, int DIM, int DEG, bool COMP>
 __global__ __launch_bounds__(256) void k_grid_update(BinLists cur, Slabs<T> slabs, GridState<T> g,
                                                      StepParams<T> prm) {
-    grid_update_body<T, DIM, DEG, COMP, WPT>(cur, slabs, g, prm, blockIdx.x, gridDim.x);
+    grid_update_body<T, DIM, DEG, COMP>(cur, slabs, g, prm, 1u, blockIdx.x, gridDim.x);
 }
 
-template <typename T, int DIM, int DEG, bool COMP, bool QUEUE, int WPT>
+template <typename T, int DIM, int DEG, bool COMP, bool QUEUE>
 __global__ __launch_bounds__(256) void k_grid_update_batch(const SceneDesc<T> *descs, const int32_t *start, int n,
                                                            int k, BatchQueue q) {
     batch_items<QUEUE>(q, [&](uint32_t it) {
@@ -242,32 +245,26 @@ __global__ __launch_bounds__(256) void k_grid_update_batch(const SceneDesc<T> *d
         GridState<T> g = table_struct(d.g);
         g.vmax = tile_bounds(table_struct(d.tab[b.sp.nxt].lvl_off));
         const StepParams<T> prm = table_struct(d.prm);
-        grid_update_body<T, DIM, DEG, COMP, WPT>(b.cur, slabs, g, prm, b.blk, b.nblk);
+        grid_update_body<T, DIM, DEG, COMP>(b.cur, slabs, g, prm, (uint32_t)n, b.blk, b.nblk);
     });
 }
 
 template <typename T, int DIM, int DEG, bool COMP>
 void launch_grid_update_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
-                              int blocks, int waves, hipStream_t st) {
-    with_tile_waves<true>(waves, [&](auto w) {
-        constexpr int WPT = decltype(w)::value;
-        if (q.ctr)
-            hipLaunchKernelGGL((k_grid_update_batch<T, DIM, DEG, COMP, true, WPT>), dim3((unsigned)blocks), dim3(256),
-                               0, st, descs, start, n, k, q);
-        else
-            hipLaunchKernelGGL((k_grid_update_batch<T, DIM, DEG, COMP, false, WPT>), dim3((unsigned)blocks), dim3(256),
-                               0, st, descs, start, n, k, q);
-    });
+                              int blocks, hipStream_t st) {
+    if (q.ctr)
+        hipLaunchKernelGGL((k_grid_update_batch<T, DIM, DEG, COMP, true>), dim3((unsigned)blocks), dim3(256), 0, st,
+                           descs, start, n, k, q);
+    else
+        hipLaunchKernelGGL((k_grid_update_batch<T, DIM, DEG, COMP, false>), dim3((unsigned)blocks), dim3(256), 0, st,
+                           descs, start, n, k, q);
 }
 
 template <typename T, int DIM, int DEG, bool COMP>
 void launch_grid_update(const BinLists &cur, const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm,
-                        int64_t n, int64_t max_records, hipStream_t st) {
-    with_tile_waves<true>(grid_waves<DIM>(n), [&](auto w) {
-        constexpr int WPT = decltype(w)::value;
-        hipLaunchKernelGGL((k_grid_update<T, DIM, DEG, COMP, WPT>), dim3(blocks_for(max_records, 4 / WPT, 4096)),
-                           dim3(256), 0, st, cur, slabs, g, prm);
-    });
+                        int64_t max_records, hipStream_t st) {
+    hipLaunchKernelGGL((k_grid_update<T, DIM, DEG, COMP>), dim3(blocks_for(max_records, 1, 4096)), dim3(256), 0, st,
+                       cur, slabs, g, prm);
 }
 
 // --- export: dense node-major copy of one field ------------------------------------
@@ -383,10 +380,10 @@ void launch_diag_grid(const BinLists &gm, const Slabs<T> &slabs, const GridState
 
 #define APIC_GRID_INST(T, DIM, DEG, COMP)                                                                         \
     template void launch_grid_update_batch<T, DIM, DEG, COMP>(const SceneDesc<T> *, const int32_t *, int, int,        \
-                                                              const BatchQueue &, int, int,                           \
+                                                              const BatchQueue &, int,                                \
                                                               hipStream_t);                                       \
     template void launch_grid_update<T, DIM, DEG, COMP>(const BinLists &, const Slabs<T> &, const GridState<T> &, \
-                                                        const StepParams<T> &, int64_t, int64_t, hipStream_t);   \
+                                                        const StepParams<T> &, int64_t, hipStream_t);            \
     template void launch_grid_export<T, DIM, DEG, COMP>(const BinLists &, const Slabs<T> &, const GridState<T> &, \
                                                         int, T *, hipStream_t);                                  \
     template void launch_diag_grid<T, DIM, DEG, COMP>(const BinLists &, const Slabs<T> &, const GridState<T> &,   \
