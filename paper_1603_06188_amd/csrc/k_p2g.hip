@@ -21,11 +21,11 @@
 namespace apic {
 
 // --- 3D, quadratic and cubic: one block of wavefronts per listed tile ---------------------
-// Lane = key in every wavefront.  Levels are taken several at a time: each
-// wavefront forms the terms of every key's particle of one level (stress,
-// weights, axis factors) and leaves them in LDS; then each wavefront adds the
-// terms of all these levels to the register sums of one plane of the slab (mass
-// or a momentum component) and at the end flushes that plane by itself.
+// Levels are taken several at a time: each wavefront forms the terms (stress,
+// weights, axis factors) of 64 of their particles and leaves them in LDS by key
+// and level; then, lane = key, each wavefront adds the terms of all these levels
+// to the register sums of one plane of the slab (mass or a momentum component)
+// and at the end flushes that plane by itself.
 //
 // One wavefront per tile has to hold all (1 + 3) K^3 sums of a key: 108
 // registers in binary32 quadratic (two wavefronts per SIMD), and more than there
@@ -39,6 +39,17 @@ namespace apic {
 // particles 86 -> 84 (VALU issue 48 us; a tile's chain of loads, barriers and
 // flush rounds is 17 us with four blocks on a CU), 80 since the plane addresses
 // are scalar adds.
+// Vector issue bounds it where tiles are many: the terms by a wavefront per level,
+// most lanes without a particle on the later ones, cost a scene of few particles
+// per key more than they saved.  By 64 particles at a time: binary32 quadratic 2.4M
+// particles at 8 per cell 126 -> 110 us, at 2 219 -> 185, at 1 321 -> 274, at 0.5 522
+// -> 459 (a wavefront per tile: 130, 180, 246, 375); cubic 1.0M at 8 79 -> 74;
+// binary64 quadratic 1.0M at 8 114 -> 102, cubic 264 -> 250; full levels (the cube at
+// rest) as before.
+// The mass plane by a loop of its own with half the multiply-adds: 110 -> 116 us (the
+// sums move between the two).  The next record's tables loaded ahead: 126 -> 130; the
+// flush by LDS atomics: binary32 several times slower, binary64 cubic 1.0M at 1 per
+// cell 755 -> 709 but 50,000 at 8 41.6 -> 43.5.
 // Binary32 adds by 4x4x1 matrix products (rows: slices, columns: a of one b, 16
 // keys a product) need the terms spread over the lanes again: twice the LDS
 // traffic, which then bounds the pass (cubic 670 us, quadratic 100).  The next
@@ -283,37 +294,61 @@ __device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur
     // the terms of NW levels; after the last of them the slab planes
     __shared__ __attribute__((aligned(16))) char lds[TERMS > SLAB ? TERMS : SLAB];
     __shared__ T lds_ref[3];
+    // key and level in the group of the particles whose terms a wavefront forms
+    using Slot = std::conditional_t<NW == 4, uint8_t, uint16_t>;
+    __shared__ Slot lds_slot[NW][64];
     const int lane = lane_id(), wv = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int comp = wv & 3, c0 = (wv >> 2) * CZ;  // its plane and z-slices
-    int lcoord[3] = {0, 0, 0};
-    local_coords<3>(lane, lcoord);
+    Slot *slot = lds_slot[wv];
+    // place in LDS of the slab values this lane stores
+    int pad[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) pad[i] = lane + 64 * i < RN ? kSlabPad<3, DEG>.at[lane + 64 * i] : 0;
     const TileWalk walk = tile_walk(cur);
-    T *terms = (T *)lds, *mine = terms + wv * LEVEL + lane * L::LANE;
+    T *terms = (T *)lds;
     U *hi = (U *)lds + comp * LP, *lo = (U *)lds + (NC + comp) * LP;
     for (uint32_t r = blk; r < walk.nrec; r += nblk) {
         uint32_t start, cnt, maxc, kstart;
         const uint32_t t = tile_of_record(walk, r, cur, tab, start, cnt, maxc, kstart);
-        int key[3] = {0, 0, 0};
-        tile_origin<3>(t, g.d.TN, key);
+        int origin[3] = {0, 0, 0};
+        tile_origin<3>(t, g.d.TN, origin);
+        const bool busy = maxc > (uint32_t)kMaxLevels;
+        // A group of NW levels from g0 on: its particles follow each other in the
+        // tile, from `first` on, `m` of them, and each wavefront forms the terms of 64.
+        // (A busy tile's do not: each wavefront forms those of a level, lane = key.)
+        // A lane past the last takes the last too: loads under a lane mask would keep
+        // the values before them alive.
+        uint32_t g0 = 0, first = start, m = 0;
+        auto count_group = [&] {
+            m = 0;
 #pragma unroll
-        for (int a = 0; a < 3; ++a) key[a] += lcoord[a];
-        // level of this wavefront in the current group and its first particle in the tile
-        uint32_t level = 0, j = (uint32_t)wv;
-        for (uint32_t i = 0; i < j; ++i) level += (uint32_t)popc64(ballot(cnt > i));
-        // its particle of this lane's key (a lane without one reads particle 0:
-        // loads under a lane mask would keep the values before them alive)
-        auto particle = [&] {
-            const uint64_t mask = ballot(cnt > j);
-            return cnt > j ? (uint32_t)particle_at(start, kstart, level, mask, j, maxc, lane) : 0u;
+            for (uint32_t i = 0; i < NW; ++i) m += (uint32_t)popc64(ballot(cnt > g0 + i));
         };
+        auto place = [&] {  // in the group
+            const uint32_t at = (uint32_t)(64 * wv + lane);
+            return at < m ? at : m - 1u;
+        };
+        auto particle = [&] {
+            if (busy) return cnt > g0 + (uint32_t)wv ? kstart + g0 + (uint32_t)wv : 0u;
+            return first + place();
+        };
+        auto has_work = [&] { return busy ? g0 + (uint32_t)wv < maxc : (uint32_t)(64 * wv) < m; };
+        count_group();
         P2GRaw<T, 3> raw;
-        if constexpr (L::AHEAD) p2g_load<T, 3, ABS>(P, particle(), raw);
+        if constexpr (L::AHEAD) {
+            if (has_work()) p2g_load<T, 3, ABS>(P, particle(), raw);
+        }
         // the tile's reference velocity, from the level-0 particles
         T uref[3];
         if (wv == 0) {
-            if constexpr (L::AHEAD)
-                reference_of_level0<T, 3>(raw.v, cnt > 0, uref);
-            else
+            if constexpr (L::AHEAD) {
+                // to the lanes of their keys
+                const int from = busy ? lane : popc64(ballot(cnt > 0) & lanes_below(lane));
+                T v[3];
+#pragma unroll
+                for (int a = 0; a < 3; ++a) v[a] = __shfl(raw.v[a], from, 64);
+                reference_of_level0<T, 3>(v, cnt > 0, uref);
+            } else
                 tile_reference<T, 3>(P, start, kstart, cnt, maxc, uref);
             if (lane == 0) {
 #pragma unroll
@@ -328,25 +363,45 @@ __device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur
         for (int a = 0; a < 3; ++a) uref[a] = wave_uniform(lds_ref[a]);
         PlaneSums<T, DEG> sums;
         sums.clear();
-        for (uint32_t g0 = 0; g0 < maxc; g0 += NW) {
-            if (j < maxc) {
-                if constexpr (L::AHEAD) {
-                    level_terms<T, DEG, ABS>(raw, cnt > j, key, prm, g.inv_dx, g.flags, uref, mine);
-                } else {
-                    P2GRaw<T, 3> now;
-                    p2g_load<T, 3, ABS>(P, particle(), now);
-                    level_terms<T, DEG, ABS>(now, cnt > j, key, prm, g.inv_dx, g.flags, uref, mine);
-                }
-            }
+        while (g0 < maxc) {
+            if (has_work()) {
+                if constexpr (!L::AHEAD) p2g_load<T, 3, ABS>(P, particle(), raw);
+                uint32_t k = (uint32_t)lane, lv = (uint32_t)wv;
+                bool has = true;
+                if (busy) {
+                    has = cnt > g0 + (uint32_t)wv;
+                } else if (m < 64u * NW) {  // (else every key has a particle on each level)
+                    uint32_t before = 0;
 #pragma unroll
-            for (uint32_t i = 0; i < NW; ++i) level += (uint32_t)popc64(ballot(cnt > j + i));
-            j += NW;
+                    for (uint32_t i = 0; i < NW; ++i) {
+                        const uint64_t mask = ballot(cnt > g0 + i);
+                        const uint32_t at = before + (uint32_t)popc64(mask & lanes_below(lane)) - (uint32_t)(64 * wv);
+                        if (cnt > g0 + i && at < 64u) slot[at] = (Slot)((uint32_t)lane | i << 6);
+                        before += (uint32_t)popc64(mask);
+                    }
+                    wave_lds_sync();
+                    const uint32_t x = slot[place() - (uint32_t)(64 * wv)];
+                    k = x & 63u;
+                    lv = x >> 6;
+                }
+                int key[3];
+                local_coords<3>((int)k, key);
+#pragma unroll
+                for (int a = 0; a < 3; ++a) key[a] += origin[a];
+                level_terms<T, DEG, ABS>(raw, has, key, prm, g.inv_dx, g.flags, uref,
+                                         terms + lv * LEVEL + k * L::LANE);
+            }
+            const uint32_t g_now = g0;
+            first += m;
+            g0 += NW;
+            count_group();
             if constexpr (L::AHEAD) {
-                if (j < maxc) p2g_load<T, 3, ABS>(P, particle(), raw);
+                if (has_work()) p2g_load<T, 3, ABS>(P, particle(), raw);
             }
             __syncthreads();
 #pragma unroll 1
-            for (uint32_t i = 0; i < NW && g0 + i < maxc; ++i) sums.add(terms + i * LEVEL, comp, c0);
+            for (uint32_t i = 0; i < NW && g_now + i < maxc; ++i)
+                if (cnt > g_now + i) sums.add(terms + i * LEVEL, comp, c0);
             __syncthreads();
         }
         if (c0 == 0) {
@@ -376,11 +431,10 @@ __device__ __forceinline__ void p2g_tile3(const Parts<T> &P, const BinLists &cur
             for (int i = 0; i < R; ++i) {
                 const int at = lane + 64 * i;
                 if (at < RN) {
-                    const int pad = kSlabPad<3, DEG>.at[at];
-                    const U sum = hi[pad];
+                    const U sum = hi[pad[i]];
                     const T v = (T)sum;
                     out[at] = v;
-                    if constexpr (COMP) out[NC * RN + at] = PAIR ? (T)lo[pad] : (T)(sum - (U)v);
+                    if constexpr (COMP) out[NC * RN + at] = PAIR ? (T)lo[pad[i]] : (T)(sum - (U)v);
                 }
             }
         }
