@@ -988,7 +988,12 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
     double updates = 0.0;
     int64_t all = 0;
     for (int32_t i = 0; i < n; ++i) all += scenes[i].p.n;
-    const int kwaves = key_waves(all), gwaves = g2p_waves<T, DIM, DEG>(all);
+    bool few = true;  // no scene has more tiles than a block per tile serves
+    for (int32_t i = 0; i < n; ++i) {
+        const Layout L = make_layout(&scenes[i].grid, 1);
+        few = few && few_tiles<T, DIM>((uint32_t)std::min<int64_t>(L.d.tiles, scenes[i].p.n), (uint32_t)n);
+    }
+    const int kmode = key_mode(all, few), gmode = g2p_mode<T, DIM, DEG>(all, few);
     const bool finish = g2p_finishes<T, DIM, DEG>(all);
     for (int32_t i = 0; i < n; ++i) {
         int64_t cap = 0;
@@ -1048,7 +1053,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         const int pb_p2g = p2g_block_per_tile(DIM, DEG) ? pb_tile : pb;
         // (the grid update of a batch that fills the chip takes a wavefront per tile)
         const int pb_grid = all < ((int64_t)1 << (DIM == 3 ? 22 : 20)) ? pb_tile : pb;
-        const int pb_keys = kwaves == 4 ? pb_tile : pb, pb_part = gwaves == 4 ? pb_tile : pb;
+        const int pb_keys = kmode != WAVE_PER_TILE ? pb_tile : pb, pb_part = gmode != WAVE_PER_TILE ? pb_tile : pb;
         const int share[BK_COUNT] = {share_blocks(np, pb_p2g, 4096), share_blocks(np, pb_grid, 8192),
                                      share_blocks(np, pb_keys, 4096), share_blocks(np, pb, 1024),
                                      share_blocks(np, pb_part, 4096), share_blocks(np, 1024, 4096),
@@ -1125,14 +1130,14 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
             timed(APIC_PHASE_BIN, s, [&] {
                 int nk = 0, nr = 0;
                 const BatchQueue qk = queue_of(BK_KEYS, nk);
-                launch_bin_keys_moved_batch<T, DIM, DEG>(dd, start_of(BK_KEYS), n, k, qk, nk, kwaves, s);
+                launch_bin_keys_moved_batch<T, DIM, DEG>(dd, start_of(BK_KEYS), n, k, qk, nk, kmode, s);
                 const BatchQueue qr = queue_of(BK_RECORDS, nr);
                 launch_bin_records_batch<T, DIM>(dd, start_of(BK_RECORDS), n, k, qr, nr, s);
                 if (!finish) launch_bin_finalize_batch<T>(dd, start_of(BK_FINAL), n, k, total[BK_FINAL], s);
             });
             q = queue_of(BK_G2P, nb);
             timed(APIC_PHASE_G2P, s,
-                  [&] { launch_g2p_batch<T, DIM, DEG>(dd, start_of(BK_G2P), n, k, q, nb, adaptive, gwaves, finish, s); });
+                  [&] { launch_g2p_batch<T, DIM, DEG>(dd, start_of(BK_G2P), n, k, q, nb, adaptive, gmode, finish, s); });
         }
         launch_copy_back_batch<T, DIM>(dd, start_of(BK_COPY), n, n_steps, total[BK_COPY], s);
     };
@@ -1163,7 +1168,7 @@ apic_status run_batch(apic_scene *scenes, int32_t n, int32_t n_steps, void *bws,
         key_put(key, DIM * 100 + DEG * 10 + (COMP ? 1 : 0));
         key_put(key, (int)adaptive);
         key_put(key, qblocks);
-        key_put(key, (kwaves * 8 + gwaves) * 2 + (finish ? 1 : 0));
+        key_put(key, (kmode * 8 + gmode) * 2 + (finish ? 1 : 0));
         key.append((const char *)starts.data(), starts.size() * 4);
         auto it = g_graphs.find(key);
         if (it == g_graphs.end()) {

@@ -16,7 +16,8 @@ constexpr int kDiagBlocks = 1024;
 // counts, and a tile of few chunks has no work for four.  What decides is the
 // number of tiles and of particles in them, which only the device knows, so the
 // kernels for n below the lines further down hold both and choose by the layout
-// they read: a block per tile up to one and a half times the tiles that the chip
+// they read (a grid that has no more tiles gets the block, without the choice: 2 % of
+// a step of 4,600 2D particles): a block per tile up to one and a half times the tiles that the chip
 // holds blocks for (four to a CU, binary64 3D two), or where the tiles are well
 // filled.  Transfer to particles, a block per tile against a wavefront:
 //   3D binary32 quadratic: 1,331 tiles of 94 particles 23.7 and 25.3 us, 2,197 of
@@ -30,18 +31,24 @@ constexpr int kDiagBlocks = 1024;
 //   depend on each other.
 //   Key pass and the passes after it: 17,576 of 28 113 and 89, 1,331 of 188 21.6
 //   and 25.5.
-//   In a batch the scenes share the chip, each with twice its part of the limit (a
-//   batch's scenes are of many sizes): 128 scenes of 216 tiles of 19 particles 567 us
-//   a step with a wavefront per tile and 713 with a block, 64 2D scenes of 324 tiles
-//   of 62 236 and 268, 24 bodies of 8 particles per cell 152 and 128.
-__host__ __device__ constexpr bool tiles_within(uint32_t tiles, uint32_t scenes, uint32_t limit) {
-    return (uint64_t)tiles * scenes <= (scenes > 1u ? 2u * limit : limit);
+//   In a batch the scenes share the chip, each with four times its part of the limit (a
+//   batch's scenes are of many sizes, and the full tiles of its bodies are long
+//   chains): 128 scenes of 216 tiles of 19 particles 567 us a step with a wavefront
+//   per tile and 713 with a block, 64 2D scenes of 324 tiles of 62 236 and 268, but 24
+//   bodies at 8 per cell 152 and 128, 40 of up to 30,000 234 and 223 with twice and
+//   four times the part.
+__host__ __device__ constexpr bool tiles_within(uint32_t tiles, uint32_t scenes, uint32_t limit, uint32_t part) {
+    return (uint64_t)tiles * scenes <= (scenes > 1u ? part * limit : limit);
+}
+template <typename T, int DIM>
+__host__ __device__ constexpr bool few_tiles(uint32_t tiles, uint32_t scenes) {
+    return tiles_within(tiles, scenes, sizeof(T) == 8 && DIM == 3 ? 768u : 1536u, 4u);
 }
 template <typename T, int DIM>
 __host__ __device__ constexpr bool block_per_tile(uint32_t tiles, uint32_t live, uint32_t scenes) {
-    return tiles_within(tiles, scenes, sizeof(T) == 8 && DIM == 3 ? 768u : 1536u) ||
-           (uint64_t)live >= (uint64_t)tiles * (DIM == 3 ? 256u : 192u);
+    return few_tiles<T, DIM>(tiles, scenes) || (uint64_t)live >= (uint64_t)tiles * (DIM == 3 ? 256u : 192u);
 }
+enum TileMode : int { WAVE_PER_TILE = 1, BLOCK_PER_TILE = 4, BY_LAYOUT = 0 };
 // Above these particle counts the kernels that hold both are the slower ones even
 // where they choose well:
 //   key pass (a wavefront holds the offsets of eight chunks): 512,000 particles 13
@@ -51,14 +58,17 @@ __host__ __device__ constexpr bool block_per_tile(uint32_t tiles, uint32_t live,
 //   four; 1,404,928 64 and 65; 2,097,152 101 and 90: little between them below 1.4M.  The others
 //   (two or three wavefronts per SIMD by their registers, or small 2D tiles) keep
 //   the choice at every size: cubic 9.0M 727 against 735 with one.
-constexpr int key_waves(int64_t n) { return n >= ((int64_t)1 << 19) ? 1 : 4; }
+// (few: no layout of the grids has more tiles than few_tiles allows.)
+constexpr int key_mode(int64_t n, bool few) {
+    return n >= ((int64_t)1 << 19) ? WAVE_PER_TILE : (few ? BLOCK_PER_TILE : BY_LAYOUT);
+}
 template <typename T, int DIM, int DEG>
-constexpr bool g2p_waves_choice() {
+constexpr bool g2p_wave_choice() {
     return sizeof(T) == 4 && DIM == 3 && DEG <= 2;
 }
 template <typename T, int DIM, int DEG>
-constexpr int g2p_waves(int64_t n) {
-    return g2p_waves_choice<T, DIM, DEG>() && n >= ((int64_t)1 << 20) ? 1 : 4;
+constexpr bool g2p_wave_per_tile(int64_t n) {
+    return g2p_wave_choice<T, DIM, DEG>() && n >= ((int64_t)1 << 20);
 }
 
 // Grid update: a tile at an edge of the body updates up to 2^dim node tiles, one
@@ -70,20 +80,8 @@ constexpr int g2p_waves(int64_t n) {
 // 6.3 and 6.4, 3,969 10.0 and 9.1; 64 scenes of 64 16.5 and 10.0.
 template <typename T, int DIM, bool COMP>
 __host__ __device__ constexpr uint32_t grid_waves(uint32_t tiles, uint32_t scenes) {
-    return tiles_within(tiles, scenes, DIM == 2 ? 2048u : (sizeof(T) == 8 || COMP ? 5120u : 3072u)) ? 4u : 1u;
+    return tiles_within(tiles, scenes, DIM == 2 ? 2048u : (sizeof(T) == 8 || COMP ? 5120u : 3072u), 2u) ? 4u : 1u;
 }
-// Runs f with the wavefronts per tile as a compile-time constant.
-template <bool CHOICE, typename F>
-inline void with_tile_waves(int waves, F &&f) {
-    if constexpr (CHOICE) {
-        if (waves == 1) {
-            f(std::integral_constant<int, 1>{});
-            return;
-        }
-    }
-    f(std::integral_constant<int, 4>{});
-}
-
 // The transfer to particles finds the bucket tables and numbers the records itself
 // in small scenes, instead of a launch for that before it: its blocks start later by
 // the scan (12k particles 8.6 -> 10.1 us, 4,096 12.7 -> 13.8, 227k 18.9 -> 21.5, 24
@@ -91,7 +89,12 @@ inline void with_tile_waves(int waves, F &&f) {
 // 512,000 26.1 -> 30.9, binary64 42.5 -> 52.4: no longer worth it).
 template <typename T, int DIM, int DEG>
 constexpr bool g2p_finishes(int64_t n) {
-    return n > 0 && n < ((int64_t)1 << 18) && g2p_waves<T, DIM, DEG>(n) == 4;
+    return n > 0 && n < ((int64_t)1 << 18);
+}
+template <typename T, int DIM, int DEG>
+constexpr int g2p_mode(int64_t n, bool few) {
+    if (g2p_wave_per_tile<T, DIM, DEG>(n)) return WAVE_PER_TILE;
+    return few && g2p_finishes<T, DIM, DEG>(n) ? BLOCK_PER_TILE : BY_LAYOUT;
 }
 
 // The transfer to grid takes a block per tile (else a wavefront).
@@ -185,13 +188,13 @@ void launch_grid_update_batch(const SceneDesc<T> *descs, const int32_t *start, i
                               int blocks, hipStream_t st);
 template <typename T, int DIM, int DEG>
 void launch_bin_keys_moved_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
-                                 int blocks, int waves, hipStream_t st);
+                                 int blocks, int mode, hipStream_t st);
 template <typename T, int DIM>
 void launch_bin_records_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
                               int blocks, hipStream_t st);
 template <typename T, int DIM, int DEG>
 void launch_g2p_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q, int blocks,
-                      bool adapt, int waves, bool finish, hipStream_t st);
+                      bool adapt, int mode, bool finish, hipStream_t st);
 // Adaptive batched steps: before each step, every scene's dt from its bound
 // slots (first: the slots cleared and raised by a pass over the particles
 // each scene starts the call with; blocks as the copy-back table).

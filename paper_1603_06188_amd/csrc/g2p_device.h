@@ -278,11 +278,13 @@ __device__ __forceinline__ void stage_all(uint32_t t, const GridState<T> &g, T *
 }
 
 // Occupancy target: binary32 3D quadratic and cubic fit 128 registers (4 waves
-// per SIMD), 2D 80 (6); binary64 cubic 3D runs at 2 (256 registers) rather than
-// the compiler's 1; other variants are left to the compiler.
+// per SIMD), 2D 80 (6); binary64 2D up to quadratic 128 (4); binary64 cubic 3D runs
+// at 2 (256 registers) rather than the compiler's 1; other variants are left to the
+// compiler.
 template <typename T, int DIM, int DEG>
 constexpr int g2p_min_waves() {
     if (sizeof(T) == 4 && DEG >= 2) return DIM == 2 ? 6 : 4;
+    if (sizeof(T) == 8 && DIM == 2 && DEG <= 2) return 4;
     return (sizeof(T) == 8 && DIM == 3 && DEG == 3) ? 2 : 1;
 }
 

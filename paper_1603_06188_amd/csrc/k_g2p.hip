@@ -5,8 +5,7 @@
 //   F_p = (I + dt sum_i vt_i grad w_ip^T) F_p
 //   x_p = x_p + dt v_p          (cell index + offset)
 // Both passes take the listed tiles of the current layout, a wavefront or a
-// block of four per tile: SPLIT kernels choose by the layout (block_per_tile), the
-// others take a wavefront.
+// block of four per tile (TileMode).
 // Pass 1 (k_bin_keys_moved) finds the particles whose key changes ("movers",
 // rare): each takes a place in its new key and is marked in a bit mask of its
 // old key's levels.  Pass 2 (k_g2p) stages the grid velocities around the tile
@@ -26,20 +25,20 @@ namespace apic {
 
 // Tiles of a block that takes several: four, each a wavefront's; two where the grid
 // velocities around four would keep blocks off a CU (binary64 3D).
-template <typename T, int DIM, bool SPLIT>
+template <typename T, int DIM, int MODE>
 constexpr int keys_tiles() {
-    return SPLIT && sizeof(T) == 8 && DIM == 3 ? 2 : 4;
+    return MODE == BLOCK_PER_TILE ? 1 : (MODE == BY_LAYOUT && sizeof(T) == 8 && DIM == 3 ? 2 : 4);
 }
-template <typename T, int DIM, int DEG, bool SPLIT>
+template <typename T, int DIM, int DEG, int MODE>
 constexpr int g2p_tiles() {
-    return SPLIT && sizeof(T) == 8 && DIM == 3 && DEG == 1 ? 2 : 4;
+    return MODE == BLOCK_PER_TILE ? 1 : (MODE == BY_LAYOUT && sizeof(T) == 8 && DIM == 3 && DEG == 1 ? 2 : 4);
 }
 
 // Waves per SIMD asked for: a wavefront per tile holds the offsets of eight
 // chunks (binary32: three).
-template <typename T, bool SPLIT>
+template <typename T, int MODE>
 constexpr int keys_min_waves() {
-    return !SPLIT && sizeof(T) == 4 ? 3 : 1;
+    return MODE == WAVE_PER_TILE && sizeof(T) == 4 ? 3 : 1;
 }
 
 // Waits for the wavefronts that work on a tile (all of a block's, where there are
@@ -57,10 +56,10 @@ struct TileItems {
     bool whole;
     uint32_t tiles, dead, count;
 };
-template <typename T, int DIM, bool SPLIT, int TILES>
+template <typename T, int DIM, int MODE, int TILES>
 __device__ __forceinline__ TileItems tile_items(const TileWalk &walk, int64_t n, uint32_t scenes) {
     TileItems it;
-    it.whole = SPLIT && block_per_tile<T, DIM>(walk.nrec, walk.live, scenes);
+    it.whole = MODE == BLOCK_PER_TILE || (MODE == BY_LAYOUT && block_per_tile<T, DIM>(walk.nrec, walk.live, scenes));
     it.tiles = it.whole ? walk.nrec : (walk.nrec + TILES - 1u) / TILES;
     it.dead = dead_chunks(n, walk.live);
     it.count = it.tiles + (it.dead + 3u) / 4u;
@@ -127,14 +126,14 @@ __device__ __forceinline__ void resolve_near(const Parts<T> &P, const GridState<
 
 constexpr uint32_t kStayer = 0x80000000u;  // prank of a busy tile's stayer: its rank with this bit
 
-template <typename T, int DIM, int DEG, bool ABS, bool SPLIT>
+template <typename T, int DIM, int DEG, bool ABS, int MODE>
 __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur, const TileTables &ctab,
                                           const GridState<T> &g, const StepParams<T> &prm_in, const BinLists &nxt,
                                           const BinScratch &sc, uint32_t scenes, uint32_t blk, uint32_t nblk) {
     const StepParams<T> prm = with_step_dt(prm_in);
     using R = VtRegion<DIM>;
-    constexpr int U = SPLIT ? kKeyChunks / 4 : kKeyChunks;  // chunks of a wavefront loaded together
-    constexpr int TILES = keys_tiles<T, DIM, SPLIT>();
+    constexpr int U = MODE == WAVE_PER_TILE ? kKeyChunks : kKeyChunks / 4;  // chunks of a wavefront loaded together
+    constexpr int TILES = keys_tiles<T, DIM, MODE>();
     __shared__ uint32_t lds_left[TILES][64];  // a bit per particle of a tile that is not busy
     static_assert(kMaxLevels * 64 <= 64 * 32, "a bit for each");
     __shared__ uint32_t lds_queue[4][64 * U];
@@ -142,7 +141,7 @@ __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur
     const int lane = lane_id(), wave = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint32_t *queue = lds_queue[wave];
     const TileWalk walk = tile_walk(cur);
-    const TileItems items = tile_items<T, DIM, SPLIT, TILES>(walk, P.n, scenes);
+    const TileItems items = tile_items<T, DIM, MODE, TILES>(walk, P.n, scenes);
     const auto walk_tiles = [&](auto w) {
         // the wavefronts of a tile, which of them this one is, and the tile of the block
         constexpr bool whole = decltype(w)::value;
@@ -219,7 +218,7 @@ __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur
                     queued += (uint32_t)popc64(nm);
                 }
                 if (queued > 0u && !staged) {
-                    stage_all<T, DIM, SPLIT ? 2 : 1>(t, g, reg);
+                    stage_all<T, DIM, MODE == WAVE_PER_TILE ? 1 : 2>(t, g, reg);
                     staged = true;
                 }
                 wave_lds_sync();
@@ -266,20 +265,26 @@ __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur
             if (wpt == 1u) wave_lds_sync();
         }
     };
-    if (items.whole)
+    if constexpr (MODE == BLOCK_PER_TILE) {
         walk_tiles(std::true_type{});
-    else
+    } else if constexpr (MODE == WAVE_PER_TILE) {
         walk_tiles(std::false_type{});
+    } else {
+        if (items.whole)
+            walk_tiles(std::true_type{});
+        else
+            walk_tiles(std::false_type{});
+    }
 }
 
-template <typename T, int DIM, int DEG, bool ABS, bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(keys_min_waves<T, SPLIT>()))) void k_bin_keys_moved(
+template <typename T, int DIM, int DEG, bool ABS, int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(keys_min_waves<T, MODE>()))) void k_bin_keys_moved(
     Parts<T> P, BinLists cur, TileTables ctab, GridState<T> g, StepParams<T> prm, BinLists nxt, BinScratch sc) {
-    keys_body<T, DIM, DEG, ABS, SPLIT>(P, cur, ctab, g, prm, nxt, sc, 1u, blockIdx.x, gridDim.x);
+    keys_body<T, DIM, DEG, ABS, MODE>(P, cur, ctab, g, prm, nxt, sc, 1u, blockIdx.x, gridDim.x);
 }
 
-template <typename T, int DIM, int DEG, bool QUEUE, bool SPLIT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 : keys_min_waves<T, SPLIT>()))) void k_bin_keys_moved_batch(
+template <typename T, int DIM, int DEG, bool QUEUE, int MODE>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 : keys_min_waves<T, MODE>()))) void k_bin_keys_moved_batch(
     const SceneDesc<T> *descs, const int32_t *start, int n, int k, BatchQueue q) {
     batch_items<QUEUE>(q, [&](uint32_t it) {
         const BatchStep<T> b = batch_step<T>(descs, start, n, k, it);
@@ -292,20 +297,31 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
         g.vmax = tile_bounds(table_struct(d.tab[b.sp.nxt].lvl_off));
         const StepParams<T> prm = table_struct(d.prm);
         const BinScratch sc = table_struct(d.sc);
-        keys_body<T, DIM, DEG, false, SPLIT>(P, b.cur, ctab, g, prm, b.nxt, sc, (uint32_t)n, b.blk, b.nblk);
+        keys_body<T, DIM, DEG, false, MODE>(P, b.cur, ctab, g, prm, b.nxt, sc, (uint32_t)n, b.blk, b.nblk);
     });
+}
+
+// Runs f with the mode as a compile-time constant.
+template <typename F>
+static void with_keys_mode(int mode, F &&f) {
+    if (mode == WAVE_PER_TILE)
+        f(std::integral_constant<int, WAVE_PER_TILE>{});
+    else if (mode == BLOCK_PER_TILE)
+        f(std::integral_constant<int, BLOCK_PER_TILE>{});
+    else
+        f(std::integral_constant<int, BY_LAYOUT>{});
 }
 
 template <typename T, int DIM, int DEG>
 void launch_bin_keys_moved_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q,
-                                 int blocks, int waves, hipStream_t st) {
-    with_tile_waves<true>(waves, [&](auto w) {
-        constexpr bool SPLIT = decltype(w)::value == 4;
+                                 int blocks, int mode, hipStream_t st) {
+    with_keys_mode(mode, [&](auto w) {
+        constexpr int MODE = decltype(w)::value;
         if (q.ctr)
-            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, true, SPLIT>), dim3((unsigned)blocks), dim3(256), 0,
+            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, true, MODE>), dim3((unsigned)blocks), dim3(256), 0,
                                st, descs, start, n, k, q);
         else
-            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, false, SPLIT>), dim3((unsigned)blocks), dim3(256), 0,
+            hipLaunchKernelGGL((k_bin_keys_moved_batch<T, DIM, DEG, false, MODE>), dim3((unsigned)blocks), dim3(256), 0,
                                st, descs, start, n, k, q);
     });
 }
@@ -314,11 +330,11 @@ template <typename T, int DIM, int DEG, bool ABS>
 void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTables &ctab, const GridState<T> &g,
                            const StepParams<T> &prm, const BinLists &nxt, const BinScratch &sc, int64_t max_records,
                            hipStream_t st) {
-    with_tile_waves<true>(key_waves(P.n), [&](auto w) {
-        constexpr bool SPLIT = decltype(w)::value == 4;
-        const int64_t items = (SPLIT ? max_records : (max_records + 3) / 4) + (P.n + 255) / 256;
+    with_keys_mode(key_mode(P.n, few_tiles<T, DIM>((uint32_t)max_records, 1u)), [&](auto w) {
+        constexpr int MODE = decltype(w)::value;
+        const int64_t items = (MODE == WAVE_PER_TILE ? (max_records + 3) / 4 : max_records) + (P.n + 255) / 256;
         const int64_t blocks = std::min<int64_t>(std::max<int64_t>(items, 1), 4096);
-        hipLaunchKernelGGL((k_bin_keys_moved<T, DIM, DEG, ABS, SPLIT>), dim3((unsigned)blocks), dim3(256), 0, st, P, cur,
+        hipLaunchKernelGGL((k_bin_keys_moved<T, DIM, DEG, ABS, MODE>), dim3((unsigned)blocks), dim3(256), 0, st, P, cur,
                            ctab, g, prm, nxt, sc);
     });
 }
@@ -341,7 +357,7 @@ void launch_bin_keys_moved(const Parts<T> &P, const BinLists &cur, const TileTab
 // instantiation, so that fixed steps carry none of it.
 // FINISH: the new layout's bucket tables are found here, and its records numbered
 // (g2p_finishes).
-template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, bool SPLIT, bool FINISH>
+template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int MODE, bool FINISH>
 __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur,
                                          const TileTables &ctab, const BinLists &nxt, const TileTables &ntab,
                                          const BinScratch &sc, const GridState<T> &g, const StepParams<T> &prm_in,
@@ -349,11 +365,11 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
     const StepParams<T> prm = ADAPT ? with_step_dt(prm_in) : prm_in;
     using R = VtRegion<DIM>;
     // the grid velocities around the tiles; before them (FINISH) the bucket tables
-    constexpr size_t VT = g2p_tiles<T, DIM, DEG, SPLIT>() * DIM * R::SIZE * sizeof(T);
+    constexpr size_t VT = g2p_tiles<T, DIM, DEG, MODE>() * DIM * R::SIZE * sizeof(T);
     __shared__ __attribute__((aligned(16))) char lds_all[FINISH && sizeof(BucketTables) > VT ? sizeof(BucketTables) : VT];
     T *lds_vt = (T *)lds_all;
     __shared__ uint32_t lds_bpre[FINISH ? kBuckets + 1 : 1];
-    constexpr int TILES = g2p_tiles<T, DIM, DEG, SPLIT>();
+    constexpr int TILES = g2p_tiles<T, DIM, DEG, MODE>();
     __shared__ uint16_t lds_slot[4][64];  // key | level << 6 of the chunk's particles
     __shared__ uint32_t lds_gone[TILES][64], lds_nlo[TILES][kMaxLevels];
     __shared__ uint64_t lds_nmask[TILES][kMaxLevels];
@@ -376,7 +392,7 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
     };
     const uint32_t live_nxt = base_at(kBuckets);
     const T dt_inv_dx = prm.dt * g.inv_dx, gs = prm.dt * g.inv_dx;
-    const TileItems items = tile_items<T, DIM, SPLIT, TILES>(walk, src.n, scenes);
+    const TileItems items = tile_items<T, DIM, MODE, TILES>(walk, src.n, scenes);
     // the wavefronts of a tile, which of them this one is, and the tile of the block
     const bool whole = items.whole;
     const uint32_t wpt = whole ? 4u : 4u / TILES, wv = (uint32_t)wave & (wpt - 1u);
@@ -490,15 +506,15 @@ __device__ __forceinline__ void g2p_body(const Parts<T> &src, const Parts<T> &ds
     (void)cmax;
 }
 
-template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, bool SPLIT, bool FINISH>
+template <typename T, int DIM, int DEG, bool ADAPT, bool ABS, int MODE, bool FINISH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(ADAPT && DIM == 3 ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p(
     Parts<T> src, Parts<T> dst, BinLists cur, TileTables ctab, BinLists nxt, TileTables ntab, BinScratch sc,
     GridState<T> g, StepParams<T> prm) {
-    g2p_body<T, DIM, DEG, ADAPT, ABS, SPLIT, FINISH>(src, dst, cur, ctab, nxt, ntab, sc, g, prm, 1u, blockIdx.x,
+    g2p_body<T, DIM, DEG, ADAPT, ABS, MODE, FINISH>(src, dst, cur, ctab, nxt, ntab, sc, g, prm, 1u, blockIdx.x,
                                                     gridDim.x);
 }
 
-template <typename T, int DIM, int DEG, bool ADAPT, bool QUEUE, bool SPLIT, bool FINISH>
+template <typename T, int DIM, int DEG, bool ADAPT, bool QUEUE, int MODE, bool FINISH>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 : g2p_min_waves<T, DIM, DEG>()))) void k_g2p_batch(
     const SceneDesc<T> *descs, const int32_t *start, int n, int k, BatchQueue q) {
     batch_items<QUEUE>(q, [&](uint32_t it) {
@@ -512,38 +528,50 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(QUEUE ? 1 :
         const BinScratch sc = table_struct(d.sc);
         const GridState<T> g = table_struct(d.g);
         const StepParams<T> prm = table_struct(d.prm);
-        g2p_body<T, DIM, DEG, ADAPT, false, SPLIT, FINISH>(src, dst, b.cur, ctab, b.nxt, ntab, sc, g, prm, (uint32_t)n,
+        g2p_body<T, DIM, DEG, ADAPT, false, MODE, FINISH>(src, dst, b.cur, ctab, b.nxt, ntab, sc, g, prm, (uint32_t)n,
                                                           b.blk, b.nblk);
     });
 }
 
-// Runs f with the wavefronts per tile and FINISH as compile-time constants.
+// Runs f with the mode and FINISH as compile-time constants.
 template <typename T, int DIM, int DEG, typename F>
-static void with_g2p_variant(int waves, bool finish, F &&f) {
-    if (finish)
-        f(std::integral_constant<int, 4>{}, std::true_type{});
-    else
-        with_tile_waves<g2p_waves_choice<T, DIM, DEG>()>(waves, [&](auto w) { f(w, std::false_type{}); });
+static void with_g2p_mode(int mode, bool finish, F &&f) {
+    using Block = std::integral_constant<int, BLOCK_PER_TILE>;
+    using Layout = std::integral_constant<int, BY_LAYOUT>;
+    if (finish) {
+        if (mode == BLOCK_PER_TILE)
+            f(Block{}, std::true_type{});
+        else
+            f(Layout{}, std::true_type{});
+        return;
+    }
+    if constexpr (g2p_wave_choice<T, DIM, DEG>()) {
+        if (mode == WAVE_PER_TILE) {
+            f(std::integral_constant<int, WAVE_PER_TILE>{}, std::false_type{});
+            return;
+        }
+    }
+    f(Layout{}, std::false_type{});
 }
 
 template <typename T, int DIM, int DEG>
 void launch_g2p_batch(const SceneDesc<T> *descs, const int32_t *start, int n, int k, const BatchQueue &q, int blocks,
-                      bool adapt, int waves, bool finish, hipStream_t st) {
+                      bool adapt, int mode, bool finish, hipStream_t st) {
     const dim3 grid((unsigned)blocks), block(256);
-    with_g2p_variant<T, DIM, DEG>(waves, finish, [&](auto w, auto f) {
-        constexpr bool SPLIT = decltype(w)::value == 4;
+    with_g2p_mode<T, DIM, DEG>(mode, finish, [&](auto w, auto f) {
+        constexpr int MODE = decltype(w)::value;
         constexpr bool FINISH = decltype(f)::value;
         if (adapt && q.ctr)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, true, SPLIT, FINISH>), grid, block, 0, st, descs, start, n,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, true, MODE, FINISH>), grid, block, 0, st, descs, start, n,
                                k, q);
         else if (adapt)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, false, SPLIT, FINISH>), grid, block, 0, st, descs, start,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, true, false, MODE, FINISH>), grid, block, 0, st, descs, start,
                                n, k, q);
         else if (q.ctr)
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, true, SPLIT, FINISH>), grid, block, 0, st, descs, start,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, true, MODE, FINISH>), grid, block, 0, st, descs, start,
                                n, k, q);
         else
-            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, false, SPLIT, FINISH>), grid, block, 0, st, descs, start,
+            hipLaunchKernelGGL((k_g2p_batch<T, DIM, DEG, false, false, MODE, FINISH>), grid, block, 0, st, descs, start,
                                n, k, q);
     });
 }
@@ -623,19 +651,20 @@ void launch_g2p(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur, c
     if (src.n == 0) return;
     Parts<T> s2 = src, d2 = dst;
     if (!src.id || !dst.id) s2.id = d2.id = nullptr;
-    with_g2p_variant<T, DIM, DEG>(g2p_waves<T, DIM, DEG>(src.n), finish, [&](auto w, auto f) {
-        constexpr bool SPLIT = decltype(w)::value == 4;
+    const int mode = g2p_mode<T, DIM, DEG>(src.n, few_tiles<T, DIM>((uint32_t)max_records, 1u));
+    with_g2p_mode<T, DIM, DEG>(mode, finish, [&](auto w, auto f) {
+        constexpr int MODE = decltype(w)::value;
         constexpr bool FINISH = decltype(f)::value;
-        const int64_t items = (SPLIT ? max_records : (max_records + 3) / 4) + (src.n + 255) / 256;
+        const int64_t items = (MODE == WAVE_PER_TILE ? (max_records + 3) / 4 : max_records) + (src.n + 255) / 256;
         const dim3 blocks((unsigned)std::min<int64_t>(std::max<int64_t>(items, 1), 4096));
         if constexpr (!ABS) {
             if (g.cfl) {
-                hipLaunchKernelGGL((k_g2p<T, DIM, DEG, true, false, SPLIT, FINISH>), blocks, dim3(256), 0, st, s2, d2,
+                hipLaunchKernelGGL((k_g2p<T, DIM, DEG, true, false, MODE, FINISH>), blocks, dim3(256), 0, st, s2, d2,
                                    cur, ctab, nxt, ntab, sc, g, prm);
                 return;
             }
         }
-        hipLaunchKernelGGL((k_g2p<T, DIM, DEG, false, ABS, SPLIT, FINISH>), blocks, dim3(256), 0, st, s2, d2, cur, ctab,
+        hipLaunchKernelGGL((k_g2p<T, DIM, DEG, false, ABS, MODE, FINISH>), blocks, dim3(256), 0, st, s2, d2, cur, ctab,
                            nxt, ntab, sc, g, prm);
     });
 }
