@@ -230,6 +230,10 @@ void launch_bin_records(const GridDims &d, const BinLists &nxt, const TileTables
 // parts of lines that several XCDs' caches held (2.1M binary32 particles in
 // lexicographic order: 805 us, the two passes now 18 and 216; 4,096 of them: 17
 // us, now 3 and 12, where launches and round trips bound both).
+// A tile stored key by key (a key of more than kMaxLevels) is ordered the same way,
+// in LDS or, if it has too many for that, in `prank`: gathered key after key by a
+// wavefront each, its reads and writes were scattered in time (1.0M particles at 27
+// per cell, given in order: 484 us with the passes before it, now 248).
 // FINISH: each block finds the bucket tables, and the layout is finished here.
 template <bool FINISH>
 __global__ __launch_bounds__(256) void k_bin_place(int64_t n, BinLists nxt, BinLists other, TileTables tab,
@@ -272,18 +276,22 @@ __global__ __launch_bounds__(256) void k_bin_gather(Parts<T> src, Parts<T> dst, 
         uint32_t start, cnt, maxc, kstart;
         const uint32_t t = tile_of_record(walk, r, nxt, tab, start, cnt, maxc, kstart);
         const uint32_t total = tab.tcount[t], kp = tab.kprefix[(int64_t)t * 64 + lane];
-        if (maxc > (uint32_t)kMaxLevels) {
-            // stored key by key: a particle's place is its rank in its key
+        const bool busy = maxc > (uint32_t)kMaxLevels;
+        if (total > 64u * (uint32_t)kMaxLevels) {
+            // (too many for the LDS; ranks are not needed any more: the order goes there)
             for (uint32_t j = (uint32_t)wv; j < cnt; j += 4u) {
                 const uint32_t p = src_of[kstart + j];
                 uint32_t rank = 0;
                 for (uint32_t i = 0; i < cnt; ++i) rank += src_of[kstart + i] < p ? 1u : 0u;
-                copy_particle<T, DIM>(src, dst, p, kstart + rank, ids);
+                sc.prank[kstart + rank] = p;
             }
+            __syncthreads();
+            for (uint32_t i = threadIdx.x; i < total; i += 256u)
+                copy_particle<T, DIM>(src, dst, sc.prank[start + i], start + i, ids);
             continue;
         }
         for (uint32_t i = threadIdx.x; i < total; i += 256u) listed[i] = src_of[start + i];
-        if (wv == 0 && lane < kMaxLevels) {
+        if (wv == 0 && lane < kMaxLevels && !busy) {
             lvl_off[lane] = tab.lvl_off[(int64_t)t * kMaxLevels + lane];
             lvl_mask[lane] = tab.lvl_mask[(int64_t)t * kMaxLevels + lane];
         }
@@ -292,7 +300,9 @@ __global__ __launch_bounds__(256) void k_bin_gather(Parts<T> src, Parts<T> dst, 
             const uint32_t p = listed[kp + j];
             uint32_t rank = 0;
             for (uint32_t i = 0; i < cnt; ++i) rank += listed[kp + i] < p ? 1u : 0u;
-            order[lvl_off[rank] + (uint32_t)popc64(lvl_mask[rank] & lanes_below(lane))] = p;
+            // (busy: key by key, a particle's place is its rank in its key)
+            const uint32_t at = busy ? kp + rank : lvl_off[rank] + (uint32_t)popc64(lvl_mask[rank] & lanes_below(lane));
+            order[at] = p;
         }
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < total; i += 256u) copy_particle<T, DIM>(src, dst, order[i], start + i, ids);
