@@ -55,10 +55,17 @@ enum TileMode : int { WAVE_PER_TILE = 1, BLOCK_PER_TILE = 4, BY_LAYOUT = 0 };
 //   us with four, 16 with one; 884,736 21 and 17; 2D 1.19M 29 and 23; cubic 9.0M
 //   235 and 163.
 //   transfer to particles, binary32 3D quadratic and multilinear: 884,736 40 with
-//   four; 1,404,928 64 and 65; 2,097,152 101 and 90: little between them below 1.4M.  The others
-//   (two or three wavefronts per SIMD by their registers, or small 2D tiles) keep
-//   the choice at every size: cubic 9.0M 727 against 735 with one.
+//   four; 1,404,928 64 and 65; 2,097,152 101 and 90: little between them below 1.4M.
+//   The others (two or three wavefronts per SIMD by their registers, or small 2D
+//   tiles) keep the choice at every size: cubic 9.0M 727 against 735 with one.
+//   But few tiles of very many particles each, which a wavefront walks too long,
+//   have a block (dense_tiles; the passes after it are in these figures): quadratic
+//   binary32 1.0M in 579 tiles (27 per cell) 55 and 38, binary64 56 and 54.5; 1.0M in
+//   256 tiles 94 and 53, 94 and 58; binary64 2.4M in 1,389 tiles 73 and 95.
 // (few: no layout of the grids has more tiles than few_tiles allows.)
+__host__ __device__ constexpr bool dense_tiles(uint32_t tiles, uint32_t live, uint32_t scenes) {
+    return tiles_within(tiles, scenes, 1024u, 1u) && (uint64_t)live >= (uint64_t)tiles * 1024u;
+}
 constexpr int key_mode(int64_t n, bool few) {
     return n >= ((int64_t)1 << 19) ? WAVE_PER_TILE : (few ? BLOCK_PER_TILE : BY_LAYOUT);
 }

@@ -141,7 +141,12 @@ __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur
     const int lane = lane_id(), wave = (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     uint32_t *queue = lds_queue[wave];
     const TileWalk walk = tile_walk(cur);
-    const TileItems items = tile_items<T, DIM, MODE, TILES>(walk, P.n, scenes);
+    TileItems items = tile_items<T, DIM, MODE, TILES>(walk, P.n, scenes);
+    if (MODE == WAVE_PER_TILE && dense_tiles(walk.nrec, walk.live, scenes)) {
+        items.whole = true;
+        items.tiles = walk.nrec;
+        items.count = walk.nrec + (items.dead + 3u) / 4u;
+    }
     const auto walk_tiles = [&](auto w) {
         // the wavefronts of a tile, which of them this one is, and the tile of the block
         constexpr bool whole = decltype(w)::value;
@@ -267,8 +272,6 @@ __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur
     };
     if constexpr (MODE == BLOCK_PER_TILE) {
         walk_tiles(std::true_type{});
-    } else if constexpr (MODE == WAVE_PER_TILE) {
-        walk_tiles(std::false_type{});
     } else {
         if (items.whole)
             walk_tiles(std::true_type{});
