@@ -667,9 +667,11 @@ __global__ __launch_bounds__(kMidBlock) void k_mid_sort_dead(Parts<double> P, Mi
 //   TILE_P2G:   node i receives w m and w (mv + Q r)                     (Sec. 3.2)
 //   TILE_FORCE: F_hat = (I + sum_i u_i grad w^T) F with u_i = dt/2 v_i + dt/4 dv_i
 //               (staged), the energy V Psi(F_hat) and node i receives
-//               -V P(F_hat) F^T grad w / dx; F_hat is kept for TILE_APPLY (Sec. 3.3, 4.1)
+//               -V P(F_hat) F^T grad w / dx; for TILE_APPLY F_hat^{-T} is kept (3D: W =
+//               F_hat^{-T} F^T) and mu - lambda ln J                    (Sec. 3.3, 4.1)
 //   TILE_APPLY: dF = (sum_i p_i grad w^T) F (p staged) and node i receives
 //               -V (dP/dF(F_hat) : dF) F^T grad w / dx                       (Sec. 4.2)
+// k_mid_tile: the transfer, and the elastic terms in 2D; k_mid_tile3: those in 3D.
 enum { TILE_P2G = 0, TILE_FORCE = 1, TILE_APPLY = 2 };
 
 template <int DIM, int DEG, int MODE>
@@ -680,6 +682,7 @@ __global__ __launch_bounds__(64) void k_mid_tile(
     constexpr int CIN = MODE == TILE_P2G ? 0 : DIM;
     constexpr int COUT = MODE == TILE_P2G ? 1 + DIM : DIM;
     constexpr int D2 = DIM * DIM;
+    static_assert(MODE == TILE_P2G || DIM == 2, "k_mid_tile3 has the elastic terms in 3D");
     __shared__ double acc[COUT * R];
     __shared__ double stage[(CIN > 0 ? CIN : 1) * R];
     if constexpr (MODE == TILE_APPLY) {
@@ -693,10 +696,9 @@ __global__ __launch_bounds__(64) void k_mid_tile(
     for (int k = lane; k < COUT * R; k += 64) acc[k] = 0.0;
     if constexpr (CIN > 0) {
         for (int k = lane; k < R; k += 64) {
-            const int rx = k % RE, ry = DIM == 3 ? (k / RE) % RE : k / RE, rz = DIM == 3 ? k / (RE * RE) : 0;
-            const int x = org[0] + rx, y = org[1] + ry, z = org[2] + rz;
-            const bool in = x < g.N[0] && y < g.N[1] && (DIM == 2 || z < g.N[2]);
-            const int64_t i = in ? node_slot<DIM>(g, x, y, z) : 0;
+            const int x = org[0] + k % RE, y = org[1] + k / RE;
+            const bool in = x < g.N[0] && y < g.N[1];
+            const int64_t i = in ? node_slot<DIM>(g, x, y, 0) : 0;
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
                 double u = 0.0;
@@ -752,8 +754,8 @@ __global__ __launch_bounds__(64) void k_mid_tile(
                 G[k] = 0.0;
             }
             // G = sum_i u_i grad w^T over the staged node values (cell units),
-            // per row: the x sums of w u and dw u, then the row's y, z factors
-            for_rows<DIM, DEG>(ax, [&](int j, int k, double c0, double c1, double c2, double, double) {
+            // per row: the x sums of w u and dw u, then the row's y factors
+            for_rows<DIM, DEG>(ax, [&](int j, int k, double c0, double c1, double, double, double) {
                 const int r0 = row_start(j, k);
                 double sw[DIM], sdw[DIM];
 #pragma unroll
@@ -773,7 +775,6 @@ __global__ __launch_bounds__(64) void k_mid_tile(
                 for (int a = 0; a < DIM; ++a) {
                     G[a * DIM] += sdw[a] * c0;
                     G[a * DIM + 1] += sw[a] * c1;
-                    if constexpr (DIM == 3) G[a * DIM + 2] += sw[a] * c2;
                 }
             });
 #pragma unroll
@@ -826,7 +827,7 @@ __global__ __launch_bounds__(64) void k_mid_tile(
                 for (int k = 0; k < D2; ++k) Pk[k] = mat.mu * dF[k] + cT * T2[k] + mat.lambda * tr * IT[k];
             }
             if (ok) {
-                // M = -V Pk F^T / dx; node i receives M grad w = dw_x (M e_x) c0 + w_x (M_y c1 + M_z c2)
+                // M = -V Pk F^T / dx; node i receives M grad w = dw_x (M e_x) c0 + w_x (M e_y) c1
                 double M[D2];
                 const double cm = -V * inv_dx;
 #pragma unroll
@@ -838,14 +839,13 @@ __global__ __launch_bounds__(64) void k_mid_tile(
                         for (int k = 0; k < DIM; ++k) sum += Pk[r * DIM + k] * F[c * DIM + k];
                         M[r * DIM + c] = cm * sum;
                     }
-                for_rows<DIM, DEG>(ax, [&](int j, int k, double c0, double c1, double c2, double, double) {
+                for_rows<DIM, DEG>(ax, [&](int j, int k, double c0, double c1, double, double, double) {
                     const int r0 = row_start(j, k);
                     double A[DIM], Bv[DIM];
 #pragma unroll
                     for (int a = 0; a < DIM; ++a) {
                         A[a] = M[a * DIM] * c0;
                         Bv[a] = M[a * DIM + 1] * c1;
-                        if constexpr (DIM == 3) Bv[a] += M[a * DIM + 2] * c2;
                     }
 #pragma unroll
                     for (int i = 0; i <= DEG; ++i)
