@@ -1642,7 +1642,8 @@ MidLayout mid_layout(const apic_grid_desc &gd, const int32_t *band, int64_t n) {
     L.count = take((size_t)(g.nodes + 1) * 4);
     L.cursor = take((size_t)(g.nodes + 1) * 4);
     L.start = take((size_t)(g.nodes + 2) * 4);
-    L.bsum = take((size_t)mid_scan_blocks(g.nodes + 1) * 4);
+    // (the scan over node slots, then the three over tiles together)
+    L.bsum = take((size_t)std::max(mid_scan_blocks(g.nodes + 1), 3 * mid_scan_blocks(g.tiles)) * 4);
     L.klist = take((size_t)g.tiles * 4);
     L.nlist = take((size_t)g.tiles * 4);
     L.slot = take((size_t)g.tiles * 4);
