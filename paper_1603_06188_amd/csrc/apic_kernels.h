@@ -17,9 +17,9 @@ constexpr int kDiagBlocks = 1024;
 // number of tiles and of particles in them, which only the device knows, so the
 // kernels for n below the lines further down hold both and choose by the layout
 // they read (a grid that has no more tiles gets the block, without the choice: 2 % of
-// a step of 4,600 2D particles): a block per tile up to one and a half times the tiles that the chip
-// holds blocks for (four to a CU, binary64 3D two), or where the tiles are well
-// filled.  Transfer to particles, a block per tile against a wavefront:
+// a step of 4,600 2D particles): a block per tile up to one and a half times the
+// tiles that the chip holds blocks for (four to a CU, binary64 3D two), or where the
+// tiles are well filled.  Transfer to particles, a block per tile against a wavefront:
 //   3D binary32 quadratic: 1,331 tiles of 94 particles 23.7 and 25.3 us, 2,197 of
 //   114 32.6 and 27.2, 17,576 of 28 109 and 63, 2,197 of 455 46.7 and 50.0;
 //   cubic: 5,832 tiles of 411 134 and 148, 17,576 of 57 168 and 110;
@@ -143,8 +143,8 @@ void launch_bin_gather(const Parts<T> &src, const Parts<T> &dst, const BinLists 
                        const TileTables &tab, const BinScratch &sc, int64_t max_records, hipStream_t st);
 
 // --- transfers ----------------------------------------------------------------
-// P2G over the layout `cur`; also zeroes the counters of `nxt` and the
-// bounds of max |vt| for the grid update and re-binning that follow.
+// P2G over the layout `cur` (the counters of the other layout were zeroed when this
+// one was finished; the bounds of |vt| per tile are stored by the grid update).
 template <typename T, int DIM, int DEG, bool COMP, bool ABS = false>
 void launch_p2g(const Parts<T> &P, const BinLists &cur, const TileTables &tab,
                 const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm, int64_t max_records,
@@ -176,8 +176,7 @@ void launch_g2p2g(const Parts<T> &src, const Parts<T> &dst, const BinLists &cur,
                   const GridState<T> &g, const StepParams<T> &prm, int64_t max_records, hipStream_t st);
 
 // Adds the contributions of the particles that changed key into the slabs
-// of layout `nxt` (after launch_g2p2g); zeroes the bounds of max |vt| and
-// the counters of layout `cur`, which the next step builds.
+// of layout `nxt` (after launch_g2p2g).
 template <typename T, int DEG, bool COMP>
 void launch_p2g_movers(const Parts<T> &P, const BinLists &cur, const BinLists &nxt, const TileTables &ntab,
                        const Slabs<T> &slabs, const GridState<T> &g, const StepParams<T> &prm, int64_t max_records,
@@ -242,7 +241,7 @@ void launch_cfl_bound(const Parts<T> &P, double c, double *partials, double *out
 template <typename T, int DIM>
 int launch_cfl_partials(const Parts<T> &P, double c, double *partials, hipStream_t st);
 // Adaptive step: dt = min(cap, nu_dx / max src[0..n)) (cap when the bound
-// is 0) into state[0], added to state[1]; zeroes the kVmaxSlots bound slots.
+// is 0) into state[0], added to state[1]; zeroes the kCflSlots bound slots.
 void launch_adapt_dt(const double *src, int n, unsigned long long *slots, double cap, double nu_dx, double *state,
                      hipStream_t st);
 
