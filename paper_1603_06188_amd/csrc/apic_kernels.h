@@ -61,7 +61,8 @@ enum TileMode : int { WAVE_PER_TILE = 1, BLOCK_PER_TILE = 4, BY_LAYOUT = 0 };
 //   But few tiles of very many particles each, which a wavefront walks too long,
 //   have a block (dense_tiles; the passes after it are in these figures): quadratic
 //   binary32 1.0M in 579 tiles (27 per cell) 55 and 38, binary64 56 and 54.5; 1.0M in
-//   256 tiles 94 and 53, 94 and 58; binary64 2.4M in 1,389 tiles 73 and 95.
+//   256 tiles 94 and 53, 94 and 58; binary64 2.4M in 1,389 tiles 73 and 95 (all before
+//   busy tiles' keys were read eight at a time).
 // (few: no layout of the grids has more tiles than few_tiles allows.)
 __host__ __device__ constexpr bool dense_tiles(uint32_t tiles, uint32_t live, uint32_t scenes) {
     return tiles_within(tiles, scenes, 1024u, 1u) && (uint64_t)live >= (uint64_t)tiles * 1024u;

@@ -76,6 +76,9 @@ __device__ __forceinline__ TileItems tile_items(const TileWalk &walk, int64_t n,
 // 40 us).  With the bound of |vt| per tile and axis instead of one over the grid,
 // and marks for the leavers instead of a count of the stayers, 9.0M particles of
 // two colliding spheres take 153 us against 278, 2D 1.19M 23 against 31.
+// Busy tiles: their keys written by all wavefronts of the tile and read back eight
+// at a time, 1.0M particles at 64 per cell 53 -> 42 (with the passes after it; one
+// by one and by the first wavefront alone before).
 constexpr int kKeyChunks = 8;  // chunks of a tile loaded together
 
 // Resolves queued particles lane < count (indices in the tile): movers take a
@@ -181,9 +184,9 @@ __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur
             if (wv == 0) {
                 left[lane] = 0u;
                 if (lane == 0 && total > 0u) claim = atomicExch(nxt.tile_gen + t, nxt.gen);
-                if (busy)
-                    for (uint32_t j = 0; j < cnt; ++j) sc.pkey[kstart + j] = t * 64 + (uint32_t)lane;
             }
+            if (busy)
+                for (uint32_t j = wv; j < cnt; j += wpt) sc.pkey[kstart + j] = t * 64 + (uint32_t)lane;
             bool staged = wpt > 1u;  // one wavefront: grid velocities around the tile on first use
             if constexpr (wpt > 1u) stage_velocities<T, DIM, (int)wpt>(t, g, reg, (int)wv);
             tile_sync(wpt);
@@ -260,9 +263,18 @@ __device__ __forceinline__ void keys_body(const Parts<T> &P, const BinLists &cur
                     ctab.kmov[(int64_t)t * 64 + lane] = gone;
                 } else {
                     // a busy tile's particles carry their key and rank themselves
+                    // (read eight at a time: the compiler must take each store for one
+                    // that may change the next read, a round trip per particle)
                     stay = 0;
-                    for (uint32_t j = 0; j < cnt; ++j)
-                        if (sc.pkey[kstart + j] == t * 64 + (uint32_t)lane) sc.prank[kstart + j] = kStayer | stay++;
+                    for (uint32_t j0 = 0; j0 < cnt; j0 += 8u) {
+                        uint32_t key[8];
+#pragma unroll
+                        for (uint32_t u = 0; u < 8u; ++u) key[u] = sc.pkey[kstart + (j0 + u < cnt ? j0 + u : j0)];
+#pragma unroll
+                        for (uint32_t u = 0; u < 8u; ++u)
+                            if (j0 + u < cnt && key[u] == t * 64 + (uint32_t)lane)
+                                sc.prank[kstart + j0 + u] = kStayer | stay++;
+                    }
                 }
                 sc.scount[(int64_t)t * 64 + lane] = stay;
                 if (lane == 0 && claim != nxt.gen) append_tile(t, nxt);
