@@ -45,7 +45,9 @@ namespace apic {
 // particles at 8 per cell 126 -> 110 us, at 2 219 -> 185, at 1 321 -> 274, at 0.5 522
 // -> 459 (a wavefront per tile: 130, 180, 246, 375); cubic 1.0M at 8 79 -> 74;
 // binary64 quadratic 1.0M at 8 114 -> 102, cubic 264 -> 250; full levels (the cube at
-// rest) as before.
+// rest) as before.  Few tiles of busy keys pay for the branches and counts that the
+// other tiles need, with a wavefront per SIMD and nothing beside it: 50,000 particles
+// at 27 per cell 57 -> 67 cubic, 81 -> 87 quadratic.
 // The mass plane by a loop of its own with half the multiply-adds: 110 -> 116 us (the
 // sums move between the two).  The next record's tables loaded ahead: 126 -> 130; the
 // flush by LDS atomics: binary32 several times slower, binary64 cubic 1.0M at 1 per

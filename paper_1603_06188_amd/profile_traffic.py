@@ -11,7 +11,9 @@ tell whether the kernels still match the counters.
 
 KERNELS (optional): comma-separated kernel-name prefixes to summarize instead
 of the explicit step's kernels; their keys keep the template arguments
-(k_mid_tile3<2, 2> -> k_mid_tile3_2_2).
+(k_mid_tile3<2, 2> -> k_mid_tile3_2_2).  So do, of the step's kernels, the keys of
+the instantiations launched less often than another one of the same name (the
+records pass of a sort, k_bin_records_3_true, beside the step's, k_bin_records).
 """
 from __future__ import annotations
 
@@ -57,7 +59,7 @@ def _per_kernel(path: str, counter: str):
         raise SystemExit(f"{path}: no copy kernel found for the calibration")
     big = max(g for g, _ in copies)
     calib = [v for g, v in copies if g == big]
-    return {k: sum(v) / len(v) for k, v in per.items()}, sum(calib) / len(calib)
+    return {k: sum(v) / len(v) for k, v in per.items()}, {k: len(v) for k, v in per.items()}, sum(calib) / len(calib)
 
 
 def read_summary(path: str):
@@ -81,8 +83,8 @@ def _key(name: str, templated: bool) -> str:
 def main(argv):
     fetch_csv, write_csv, out_path, command = argv[1:5]
     select = tuple(argv[5].split(",")) if len(argv) > 5 else None
-    fetch, fetch_copy = _per_kernel(fetch_csv, "FETCH_SIZE")
-    write, write_copy = _per_kernel(write_csv, "WRITE_SIZE")
+    fetch, calls, fetch_copy = _per_kernel(fetch_csv, "FETCH_SIZE")
+    write, _, write_copy = _per_kernel(write_csv, "WRITE_SIZE")
     fs, ws = COPY_KIB / fetch_copy, COPY_KIB / write_copy
     lines = [
         "HBM traffic per launch of the step kernels, from rocprofv3 FETCH_SIZE and WRITE_SIZE",
@@ -105,7 +107,8 @@ def main(argv):
         else:
             if not any(s in k for s in STEP_KERNELS):
                 continue
-            key = k.split("<")[0].replace("apic::", "")
+            most = max((o for o in fetch if o.split("<")[0] == k.split("<")[0]), key=calls.get, default=k)
+            key = _key(k, k != most)
         fb = fetch.get(k, 0.0) * 1024 * fs
         wb = write.get(k, 0.0) * 1024 * ws
         lines.append(f"{key}_fetch_bytes: {fb:.0f}")
