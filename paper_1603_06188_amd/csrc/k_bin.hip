@@ -300,9 +300,10 @@ __global__ __launch_bounds__(256) void k_bin_gather(Parts<T> src, Parts<T> dst, 
             const uint32_t p = listed[kp + j];
             uint32_t rank = 0;
             for (uint32_t i = 0; i < cnt; ++i) rank += listed[kp + i] < p ? 1u : 0u;
-            // (busy: key by key, a particle's place is its rank in its key)
-            const uint32_t at = busy ? kp + rank : lvl_off[rank] + (uint32_t)popc64(lvl_mask[rank] & lanes_below(lane));
-            order[at] = p;
+            if (busy)  // key by key: a particle's place is its rank in its key
+                order[kp + rank] = p;
+            else
+                order[lvl_off[rank] + (uint32_t)popc64(lvl_mask[rank] & lanes_below(lane))] = p;
         }
         __syncthreads();
         for (uint32_t i = threadIdx.x; i < total; i += 256u) copy_particle<T, DIM>(src, dst, order[i], start + i, ids);
